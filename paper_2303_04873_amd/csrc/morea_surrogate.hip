@@ -34,8 +34,6 @@ constexpr int kIn = 23, kInPad = 24, kHid = 128;
 constexpr int oW1 = 0, oB1 = oW1 + kHid * kIn, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kHid,
               oW3 = oB2 + kHid, oB3 = oW3 + kHid, kParams = oB3 + 1;   // 19,713
 constexpr int kRowTile = 32;
-constexpr int kWavePart = 3 * kHid + 2;   // per-wave partials: dw3, db2, db1, db3, loss
-constexpr int kSplitK = 16;
 constexpr int kGradTiles = 20;            // 16 tiles of W2, 4 of W1
 
 typedef short s4 __attribute__((ext_vector_type(4)));
@@ -742,182 +740,343 @@ __global__ __launch_bounds__(256) void k_predict_rows(const float* X, int n, con
 }
 
 // ------------------------------------------------------------- training
+// Loss and gradients of a batch in one kernel: a block of 4 waves takes 128
+// rows at a time, a wave 32 of them, through the forward pass, the backward
+// pass and the weight gradients, whose sums stay in accumulators over all the
+// block's rows.  v_mfma_f32_32x32x16 has the same lane and k layout for both
+// operands, so each product can be formed in either orientation from the
+// same fragments:
+//   z^T = W x^T  (lane = row, registers = units): relu(z1^T) is at once the
+//     other operand of layer 2, dz2^T that of the backward product, and the
+//     output layer sums over a lane's own registers;
+//   z = x W^T    (lane = unit, registers = rows): the contraction over rows
+//     of dW = dz^T h reads dz and h as they stand in the accumulators.
+// Both orientations are computed (the matrix cores have the time), so nothing
+// is transposed and no activation goes to memory; h1 and dz2 pass through LDS
+// as whole fragments, because wave w sums rows 32 w .. of dW2 over the rows of
+// all four waves (64 accumulators a wave; all of dW2 in every wave would take
+// 256 and spill).  The k slots of an accumulator used as an operand are in
+// the order of slot_unit, so W2 and its transpose are stored in that order.
+//
+// Bound: 154 KB of LDS (both orders of W2 and the fragments) leave one block
+// on a compute unit, one wave on a SIMD, so it is the chain of a block's
+// steps (152 MFMAs of 32 cycles and as long reading fragments) after loading
+// the weights: 8.3 us per 32,768 rows after 15 us.  65,536 rows: 32 us, then
+// 4.7 us to add the blocks' sums; a batch's loss and gradients went from 723
+// to 38 us (activations through memory, 320 waves for the weight gradients,
+// and one thread adding 2,048 partial sums per bias took 175 + 76 + 476 us).
+constexpr int kPartTiles = kGradTiles * 1024;              // entries of dW2 (16 tiles) and dW1 (4)
+constexpr int kPartSums = 3 * kHid + 2;                    // dw3, db2, db1, db3, loss
+constexpr int kPart = (kPartTiles + kPartSums + 63) / 64 * 64;   // floats per block
+constexpr int kTrainWaves = 4;
+constexpr int kTrainBlocks = 256;                          // one per compute unit
+constexpr int kXRow = kRowTile + 8;
 
-struct TrainBuf {
-  bf16* xT;     // [kInPad][Bpad]
-  bf16* h1T;    // [kHid][Bpad]
-  bf16* dz2T;   // [kHid][Bpad]
-  bf16* dz1T;   // [kHid][Bpad]
-  float* wpart; // [n_waves][kWavePart]
-  float* gpart; // [kSplitK][kGradTiles][32][32]
-  int bpad;
+__device__ __forceinline__ int unit_slot(int u) {   // inverse of slot_unit
+  return u < 8 ? 8 * (u >> 2) + (u & 3) : 8 * ((u - 8) >> 2) + 4 + (u & 3);
+}
+
+struct alignas(16) TrainLds {
+  bf16 w1[kHid][kW1Row];                   // W1[j][k], zeros beyond the features
+  union {
+    struct {
+      bf16 w2[kHid][kW2Row];               // W2[j][slot of k]
+      bf16 w2t[kHid][kW2Row];              // its transpose: [k][slot of j]
+    };
+    float sums[kTrainWaves][kPartSums];    // after the last rows
+  };
+  float b1[kHid], b2[kHid], w3[kHid];
+  bf16 x[kTrainWaves][kRowTile][kXRow];    // rows, features padded with zeros
+  float dy[kTrainWaves][kRowTile];
+  union {
+    struct {                               // fragments [wave][2 tile + slice][lane]
+      u4v h[kTrainWaves][8][64], d[kTrainWaves][8][64];
+    };
+    float dw1[kTrainWaves][4 * 1024];      // after the last rows
+  };
 };
+static_assert(sizeof(TrainLds) <= 160 * 1024, "one block's LDS");
 
-// Forward and backward (data) pass of one tile of 32 training rows.
-__global__ __launch_bounds__(128) void k_train_rows(const float* X, const float* t, int n,
-                                                     const bf16* w1b, const bf16* w2b,
-                                                     const float* params, TrainBuf B) {
-  __shared__ NetLds N;
-  __shared__ TileLds Tl[2];
-  __shared__ alignas(16) bf16 w2t[kHid][kHid];     // W2 transposed: w2t[k][j] = W2[j][k]
-  __shared__ alignas(16) bf16 dz2s[2][kRowTile][kHid];
-  __shared__ float dys[2][kRowTile];
-  __shared__ RedTile reds[2];
-  load_net(&N, w1b, w2b, params);
-  for (int q = threadIdx.x; q < kHid * kHid; q += blockDim.x) {
-    const int j = q / kHid, k = q % kHid;
-    w2t[k][j] = w2b[q];
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float fl2 __attribute__((ext_vector_type(2)));
+
+// Accumulators 8 g .. 8 g + 7 as one operand fragment (rounded to BF16).
+__device__ __forceinline__ bf8 pack_acc(const f16v& z, int g) {
+  u4v w;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const fl2 v = {z[8 * g + 2 * q], z[8 * g + 2 * q + 1]};
+    w[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
   }
+  return __builtin_bit_cast(bf8, w);
+}
+
+__device__ __forceinline__ f16v mma16(bf8 a, bf8 b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// The 16 values of v[32 n ..] at the rows of lane half h's accumulators.
+__device__ __forceinline__ f16v acc_rows(const float* v, int h) {
+  f16v r;
+#pragma unroll
+  for (int g = 0; g < 4; g++) {
+    const float4 q = *reinterpret_cast<const float4*>(v + 8 * g + 4 * h);
+    r[4 * g] = q.x;
+    r[4 * g + 1] = q.y;
+    r[4 * g + 2] = q.z;
+    r[4 * g + 3] = q.w;
+  }
+  return r;
+}
+
+__global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, const float* t, int n,
+                                                              const bf16* w1b, const bf16* w2b, const float* params,
+                                                              float* part) {
+  __shared__ TrainLds S;
+  constexpr int kThreads = 64 * kTrainWaves;
+#pragma unroll
+  for (int e0 = 0; e0 < kHid * kPreIn / 4; e0 += kThreads) {
+    const int e = e0 + threadIdx.x, j = e / (kPreIn / 4), k0 = e % (kPreIn / 4) * 4;
+    const s4 zero = {0, 0, 0, 0};
+    *reinterpret_cast<s4*>(&S.w1[j][k0]) = k0 < kInPad ? ld4(w1b + j * kInPad + k0) : zero;
+  }
+#pragma unroll
+  for (int e0 = 0; e0 < kHid * kHid / 4; e0 += kThreads) {
+    // consecutive lanes take consecutive j: the transposed stores fill whole
+    // LDS rows (consecutive k would be 16 lanes to a bank)
+    const int e = e0 + threadIdx.x, j = e % kHid, k0 = e / kHid * 4;
+    const s4 w = ld4(w2b + j * kHid + k0);
+    // four units of a slice are four slots in a row
+    *reinterpret_cast<s4*>(&S.w2[j][(k0 & ~15) + unit_slot(k0 & 15)]) = w;
+#pragma unroll
+    for (int q = 0; q < 4; q++) S.w2t[k0 + q][(j & ~15) + unit_slot(j & 15)] = static_cast<bf16>(w[q]);
+  }
+  if (threadIdx.x < kHid) {
+    S.b1[threadIdx.x] = params[oB1 + threadIdx.x];
+    S.b2[threadIdx.x] = params[oB2 + threadIdx.x];
+    S.w3[threadIdx.x] = params[oW3 + threadIdx.x];
+  }
+  const float b3 = params[oB3];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  int lane = lane_id(), i = lane & 31, h = lane >> 5;
+  bf16 (*xs)[kXRow] = S.x[wave];
+  for (int q = lane; q < kRowTile * kXRow; q += 64) xs[0][q] = 0;
+  const float two_n = 2.f / static_cast<float>(n);
+  f16v dw2[4], dw1[4];
+#pragma unroll
+  for (int a = 0; a < 4; a++) dw1[a] = dw2[a] = f16v{};
+  float gw3[4] = {}, gb2[4] = {}, gb1[4] = {}, gb3 = 0.f, loss = 0.f;
+  const int step = gridDim.x * kTrainWaves * kRowTile;
+  for (int first = blockIdx.x * kTrainWaves * kRowTile; first < n; first += step) {
+    // opaque lane indices: the weight fragments are read from LDS where they
+    // are used, not kept in 288 registers over the steps
+    asm volatile("" : "+v"(i), "+v"(h), "+v"(lane));
+    const int row0 = first + wave * kRowTile, rows = min(kRowTile, n - row0);   // rows <= 0: none
+    // all loads of the tile in flight together (clamped to the batch)
+    constexpr int kLoads = (kRowTile * kIn + 63) / 64;
+    const size_t x0 = static_cast<size_t>(row0) * kIn, x_last = static_cast<size_t>(n) * kIn - 1;
+    float xv[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; q++) xv[q] = X[min(x0 + 64 * q + lane, x_last)];
+    const float target = t[min(row0 + i, n - 1)];
+    __syncthreads();   // the weights (first step) or the last step's fragments are done with
+#pragma unroll
+    for (int q0 = 0; q0 < kLoads; q0++) {
+      const int q = 64 * q0 + lane;
+      if (q < kRowTile * kIn) xs[q / kIn][q % kIn] = f2bf(q < rows * kIn ? xv[q0] : 0.f);
+    }
+    wave_sync();
+    // the rows as an operand: lane = row, features 16 s + 8 h + 0..7, and
+    // transposed: lane = feature, the rows in accumulator order
+    bf8 xb[2], xu[2];
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+      xb[s] = ld8(&xs[i][16 * s + 8 * h]);
+      u4v w;
+#pragma unroll
+      for (int k = 0; k < 8; k += 2) {
+        const int r = 16 * s + (k < 4 ? 4 * h + k : 8 + 4 * h + k - 4);
+        w[k / 2] = static_cast<unsigned>(xs[r][i]) | static_cast<unsigned>(xs[r + 1][i]) << 16;
+      }
+      xu[s] = __builtin_bit_cast(bf8, w);
+    }
+    // layer 1 in both orientations
+    bf8 ht[8];
+    u4v hu[8];
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      const bf8 w0 = ld8(&S.w1[32 * a + i][8 * h]), w1 = ld8(&S.w1[32 * a + i][16 + 8 * h]);
+      f16v z = acc_rows(S.b1 + 32 * a, h), u;
+      const float bias = S.b1[32 * a + i];
+#pragma unroll
+      for (int r = 0; r < 16; r++) u[r] = bias;
+      z = mma16(w1, xb[1], mma16(w0, xb[0], z));
+      u = mma16(xb[1], w1, mma16(xb[0], w0, u));
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        z[r] = fmaxf(z[r], 0.f);
+        u[r] = fmaxf(u[r], 0.f);
+      }
+#pragma unroll
+      for (int g = 0; g < 2; g++) {
+        ht[2 * a + g] = pack_acc(z, g);
+        hu[2 * a + g] = __builtin_bit_cast(u4v, pack_acc(u, g));
+        S.h[wave][2 * a + g][lane] = hu[2 * a + g];
+      }
+    }
+    // layer 2 in both orientations; the output and its gradient
+    f16v zt[4], zu[4];
+    float y = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      zt[a] = acc_rows(S.b2 + 32 * a, h);
+      const float bias = S.b2[32 * a + i];
+#pragma unroll
+      for (int r = 0; r < 16; r++) zu[a][r] = bias;
+#pragma unroll
+      for (int sl = 0; sl < 8; sl++) {
+        const bf8 w = ld8(&S.w2[32 * a + i][16 * sl + 8 * h]);
+        zt[a] = mma16(w, ht[sl], zt[a]);
+        zu[a] = mma16(ht[sl], w, zu[a]);
+      }
+      const f16v w3 = acc_rows(S.w3 + 32 * a, h);
+#pragma unroll
+      for (int r = 0; r < 16; r++) y = fmaf(fmaxf(zt[a][r], 0.f), w3[r], y);
+    }
+    y += __shfl_xor(y, 32, 64) + b3;
+    const float diff = i < rows ? y - target : 0.f;
+    const float dy = diff * two_n;
+    if (h == 0) {
+      S.dy[wave][i] = dy;
+      loss = fmaf(diff, diff, loss);
+      gb3 += dy;
+    }
+    wave_sync();
+    // dz2 in both orientations, dw3 and db2
+    const f16v dyr = acc_rows(S.dy[wave], h);
+    bf8 dt[8];
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      const f16v w3r = acc_rows(S.w3 + 32 * a, h);
+      const float w3 = S.w3[32 * a + i];
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        zt[a][r] = zt[a][r] > 0.f ? dy * w3r[r] : 0.f;
+        const float z = zu[a][r], dz = z > 0.f ? dyr[r] * w3 : 0.f;
+        gw3[a] = fmaf(dyr[r], fmaxf(z, 0.f), gw3[a]);
+        gb2[a] += dz;
+        zu[a][r] = dz;
+      }
+#pragma unroll
+      for (int g = 0; g < 2; g++) {
+        dt[2 * a + g] = pack_acc(zt[a], g);
+        S.d[wave][2 * a + g][lane] = __builtin_bit_cast(u4v, pack_acc(zu[a], g));
+      }
+    }
+    // layer 1 backward: dh1 = dz2 W2, db1 and this wave's share of dW1
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      f16v z = {};
+#pragma unroll
+      for (int sl = 0; sl < 8; sl++) z = mma16(dt[sl], ld8(&S.w2t[32 * a + i][16 * sl + 8 * h]), z);
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        // relu'(z1): h1 is not negative, so any set bit means z1 > 0
+        const unsigned hb = hu[2 * a + r / 8][r % 8 / 2];
+        z[r] = ((r & 1) ? hb >> 16 : hb & 0xffffu) ? z[r] : 0.f;
+        gb1[a] += z[r];
+      }
+      dw1[a] = mma16(pack_acc(z, 1), xu[1], mma16(pack_acc(z, 0), xu[0], dw1[a]));
+    }
+    __syncthreads();
+    // rows 32 wave .. of dW2 over the block's 128 rows
+#pragma unroll
+    for (int v = 0; v < kTrainWaves; v++)
+#pragma unroll
+      for (int g = 0; g < 2; g++) {
+        const bf8 d = __builtin_bit_cast(bf8, S.d[v][2 * wave + g][lane]);
+#pragma unroll
+        for (int b = 0; b < 4; b++) dw2[b] = mma16(d, __builtin_bit_cast(bf8, S.h[v][2 * b + g][lane]), dw2[b]);
+      }
+  }
+  // the block's sums: lane halves, then waves in order
   __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = lane_id(), i = lane & 31, kh = lane >> 5;
-  const int gw = blockIdx.x * 2 + wave;
-  const int row0 = gw * kRowTile;
-  float* wp = B.wpart + static_cast<size_t>(gw) * kWavePart;
-  if (row0 >= B.bpad) return;
-  TileLds* T = &Tl[wave];
-  const bool valid = row0 + i < n;
-  for (int k = kh * 12; k < (kh ? kInPad : 12); k++) {
-    const bf16 v = f2bf(valid && k < kIn ? X[static_cast<size_t>(row0 + i) * kIn + k] : 0.f);
-    T->x[i][k] = v;
-    B.xT[static_cast<size_t>(k) * B.bpad + row0 + i] = v;
-  }
-  wave_sync();
-  f16v z2[4];
-  tile_forward(&N, T, reds[wave], z2);
-  // output gradient of the mean squared error
-  float lossp = 0.f, dyp = 0.f;
-  if (lane < kRowTile) {
-    const bool v = row0 + lane < n;
-    const float diff = v ? T->y[lane] - t[row0 + lane] : 0.f;
-    dys[wave][lane] = 2.f * diff / static_cast<float>(n);
-    lossp = diff * diff;
-    dyp = 2.f * diff / static_cast<float>(n);
-  }
-  wave_sync();
-  // layer 2 backward: dz2 = dy w3 relu'(z2); dw3 = sum dy h2; db2 = sum dz2
 #pragma unroll
-  for (int nt = 0; nt < 4; nt++) {
-    const int col = 32 * nt + i;
-    const float w = N.w3[col];
-    float gw3 = 0.f, gb2 = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int row = acc_row(r, kh);
-      const float z = z2[nt][r];
-      const float dy = dys[wave][row];
-      const float dz = z > 0.f ? dy * w : 0.f;
-      gw3 = fmaf(dy, fmaxf(z, 0.f), gw3);
-      gb2 += dz;
-      const bf16 dzb = f2bf(dz);
-      dz2s[wave][row][col] = dzb;
-      B.dz2T[static_cast<size_t>(col) * B.bpad + row0 + row] = dzb;
-    }
-    gw3 += __shfl_xor(gw3, 32, 64);
-    gb2 += __shfl_xor(gb2, 32, 64);
-    if (kh == 0) {
-      wp[col] = gw3;
-      wp[kHid + col] = gb2;
+  for (int a = 0; a < 4; a++) {
+    gw3[a] += __shfl_xor(gw3[a], 32, 64);
+    gb2[a] += __shfl_xor(gb2[a], 32, 64);
+    gb1[a] += __shfl_xor(gb1[a], 32, 64);
+    if (h == 0) {
+      S.sums[wave][32 * a + i] = gw3[a];
+      S.sums[wave][kHid + 32 * a + i] = gb2[a];
+      S.sums[wave][2 * kHid + 32 * a + i] = gb1[a];
     }
   }
-  // h1 transposed for the weight gradients
-  for (int q = lane; q < kRowTile * kHid; q += 64) {
-    const int row = q % kRowTile, k = q / kRowTile;
-    B.h1T[static_cast<size_t>(k) * B.bpad + row0 + row] = T->h1[row][k];
-  }
-  wave_sync();
-  // layer 1 backward: dh1 = dz2 W2 (MFMA with B[k=j][col] = W2[j][col]),
-  // dz1 = dh1 relu'(z1); db1 = sum dz1
-#pragma unroll
-  for (int nt = 0; nt < 4; nt++) {
-    f16v acc = {};
-#pragma unroll
-    for (int s = 0; s < kHid / 8; s++)
-      acc = mma(ld4(&dz2s[wave][i][8 * s + 4 * kh]), ld4(&w2t[32 * nt + i][8 * s + 4 * kh]), acc);
-    const int col = 32 * nt + i;
-    float gb1 = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; r++) {
-      const int row = acc_row(r, kh);
-      const float dz = bf2f(T->h1[row][col]) > 0.f ? acc[r] : 0.f;
-      gb1 += dz;
-      B.dz1T[static_cast<size_t>(col) * B.bpad + row0 + row] = f2bf(dz);
-    }
-    gb1 += __shfl_xor(gb1, 32, 64);
-    if (kh == 0) wp[2 * kHid + col] = gb1;
-  }
-  for (int d = 32; d >= 1; d >>= 1) {
-    lossp += __shfl_xor(lossp, d, 64);
-    dyp += __shfl_xor(dyp, d, 64);
+  for (int d = 16; d >= 1; d >>= 1) {
+    gb3 += __shfl_xor(gb3, d, 64);
+    loss += __shfl_xor(loss, d, 64);
   }
   if (lane == 0) {
-    wp[3 * kHid] = dyp;
-    wp[3 * kHid + 1] = lossp;
+    S.sums[wave][3 * kHid] = gb3;
+    S.sums[wave][3 * kHid + 1] = loss;
   }
-}
-
-// Weight gradients as GEMMs over the batch (K = rows), split into kSplitK
-// chunks: tile 0..15 = W2 (32 x 32 blocks), 16..19 = W1 (rows 32 tr..).
-__global__ __launch_bounds__(64) void k_weight_grads(TrainBuf B) {
-  const int tile = blockIdx.x % kGradTiles, split = blockIdx.x / kGradTiles;
-  const int lane = lane_id(), i = lane & 31, kh = lane >> 5;
-  const int chunk = (B.bpad / kSplitK + 7) / 8 * 8;
-  const int k0 = split * chunk, k1 = min(B.bpad, k0 + chunk);
-  const bf16 *A, *Bm;
-  bool bvalid = true;
-  if (tile < 16) {
-    const int tr = tile / 4, tc = tile % 4;
-    A = B.dz2T + static_cast<size_t>(32 * tr + i) * B.bpad;
-    Bm = B.h1T + static_cast<size_t>(32 * tc + i) * B.bpad;
-  } else {
-    const int tr = tile - 16;
-    A = B.dz1T + static_cast<size_t>(32 * tr + i) * B.bpad;
-    bvalid = i < kInPad;
-    Bm = B.xT + static_cast<size_t>(bvalid ? i : 0) * B.bpad;
-  }
-  f16v acc = {};
-  const s4 zero = {0, 0, 0, 0};
-  for (int k = k0; k < k1; k += 8) {
-    const s4 a = ld4(A + k + 4 * kh);
-    const s4 b = bvalid ? ld4(Bm + k + 4 * kh) : zero;
-    acc = mma(a, b, acc);
-  }
-  float* out = B.gpart + (static_cast<size_t>(split) * kGradTiles + tile) * 1024;
+  float* out = part + static_cast<size_t>(blockIdx.x) * kPart;
 #pragma unroll
-  for (int r = 0; r < 16; r++) out[acc_row(r, kh) * 32 + i] = acc[r];
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+      out[((4 * wave + a) * 16 + r) * 64 + lane] = dw2[a][r];
+      S.dw1[wave][(a * 16 + r) * 64 + lane] = dw1[a][r];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int e = threadIdx.x; e < 4 * 1024; e += kThreads)
+    out[16 * 1024 + e] = ((S.dw1[0][e] + S.dw1[1][e]) + S.dw1[2][e]) + S.dw1[3][e];
+  for (int e = threadIdx.x; e < kPart - kPartTiles; e += kThreads)
+    out[kPartTiles + e] = e < kPartSums ? ((S.sums[0][e] + S.sums[1][e]) + S.sums[2][e]) + S.sums[3][e] : 0.f;
 }
 
-// Gradient of every parameter (fixed-order sums of the partials), then
-// either the Adam update (FP32 master, BF16 copies refreshed) or a copy of
-// the gradient to `grad_out`.
-__global__ void k_reduce_update(TrainBuf B, int n_waves, float* params, float* m, float* v,
-                                bf16* w1b, bf16* w2b, float lr, float c1, float c2, float* grad_out,
-                                float* loss_out, int n) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p == 0 && loss_out) {
-    float l = 0.f;
-    for (int w = 0; w < n_waves; w++) l += B.wpart[static_cast<size_t>(w) * kWavePart + 3 * kHid + 1];
-    *loss_out = l / static_cast<float>(n);
+// Parameter of entry e of a block's partial sums, -1 for none, -2 the loss.
+__device__ __forceinline__ int part_param(int e) {
+  if (e < kPartTiles) {
+    const int q = e >> 10, r = (e >> 6) & 15, i = e & 31, h = (e >> 5) & 1;
+    const int row = acc_row(r, h);
+    if (q < 16) return oW2 + (32 * (q / 4) + row) * kHid + 32 * (q % 4) + i;
+    return i < kIn ? oW1 + (32 * (q - 16) + row) * kIn + i : -1;
   }
-  if (p >= kParams) return;
+  e -= kPartTiles;
+  if (e < kHid) return oW3 + e;
+  if (e < 2 * kHid) return oB2 + e - kHid;
+  if (e < 3 * kHid) return oB1 + e - 2 * kHid;
+  return e == 3 * kHid ? oB3 : (e == 3 * kHid + 1 ? -2 : -1);
+}
+
+// Gradient of every parameter from the blocks' partial sums (16 groups of
+// partials side by side, then the groups in order: a fixed order, and 16
+// chains instead of one, since a thread's sum is bound by the latency of its
+// loads), then either the Adam update (FP32 master, BF16 copies refreshed) or
+// a copy of the gradient to `grad_out`.
+constexpr int kSumGroups = 16;
+
+__global__ __launch_bounds__(64 * kSumGroups) void k_reduce_update(const float* part, int n_parts, float* params,
+                                                                  float* m, float* v, bf16* w1b, bf16* w2b, float lr,
+                                                                  float c1, float c2, float* grad_out,
+                                                                  float* loss_out, int n) {
+  __shared__ float s_sum[kSumGroups][64];
+  const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + col;
+  const int per = (n_parts + kSumGroups - 1) / kSumGroups;
+  const int b1_ = min(n_parts, (grp + 1) * per);
   float g = 0.f;
-  if (p < oB1) {                       // W1[j][k]
-    const int j = (p - oW1) / kIn, k = (p - oW1) % kIn;
-    for (int s = 0; s < kSplitK; s++)
-      g += B.gpart[(static_cast<size_t>(s) * kGradTiles + 16 + j / 32) * 1024 + (j % 32) * 32 + k];
-  } else if (p < oW2) {                // b1
-    for (int w = 0; w < n_waves; w++) g += B.wpart[static_cast<size_t>(w) * kWavePart + 2 * kHid + (p - oB1)];
-  } else if (p < oB2) {                // W2[j][k]
-    const int j = (p - oW2) / kHid, k = (p - oW2) % kHid;
-    const int tile = (j / 32) * 4 + k / 32;
-    for (int s = 0; s < kSplitK; s++)
-      g += B.gpart[(static_cast<size_t>(s) * kGradTiles + tile) * 1024 + (j % 32) * 32 + (k % 32)];
-  } else if (p < oW3) {                // b2
-    for (int w = 0; w < n_waves; w++) g += B.wpart[static_cast<size_t>(w) * kWavePart + kHid + (p - oB2)];
-  } else if (p < oB3) {                // w3
-    for (int w = 0; w < n_waves; w++) g += B.wpart[static_cast<size_t>(w) * kWavePart + (p - oW3)];
-  } else {                             // b3
-    for (int w = 0; w < n_waves; w++) g += B.wpart[static_cast<size_t>(w) * kWavePart + 3 * kHid];
-  }
+#pragma unroll 4
+  for (int b = grp * per; b < b1_; b++) g += part[static_cast<size_t>(b) * kPart + e];
+  s_sum[grp][col] = g;
+  __syncthreads();
+  if (grp != 0) return;
+  for (int q = 1; q < kSumGroups; q++) g += s_sum[q][col];
+  const int p = part_param(e);
+  if (p == -2 && loss_out) *loss_out = g / static_cast<float>(n);
+  if (p < 0) return;
   if (grad_out) {
     grad_out[p] = g;
     return;
@@ -1011,7 +1170,7 @@ struct morea_surrogate {
   float h_scale = 1.f;      // mean of (I_s - I_t)^2 over the grid (1 when 0)
   void* work = nullptr;     // pre-screen workspace: the parents' point means,
   size_t work_cap = 0;      // then the per-(tile, offspring) partial sums (bytes)
-  TrainBuf tb{};
+  float* part = nullptr;    // training: the blocks' partial sums
   int steps = 0;
   std::vector<void*> allocs;
 };
@@ -1095,24 +1254,25 @@ FeatureInputs feature_inputs(const morea_surrogate* s) {
   return FeatureInputs{s->img_s, s->img_t, s->bary, s->stats, s->h_scale, 1.f / s->h_scale};
 }
 
+int train_blocks(int rows) {
+  const int tiles = (rows + kRowTile - 1) / kRowTile;
+  return std::min(kTrainBlocks, (tiles + kTrainWaves - 1) / kTrainWaves);
+}
+
 morea_status train_launch(morea_surrogate* s, const float* X, const float* t, int n, float lr,
                           float* grad_out, float* loss_out, hipStream_t st) {
   if (!s || !X || !t) return sfail(MOREA_EINVAL, "NULL argument");
   if (n < 1 || n > s->max_rows) return sfail(MOREA_ERANGE, "rows %d outside [1, %d]", n, s->max_rows);
-  TrainBuf B = s->tb;
-  B.bpad = (n + kRowTile - 1) / kRowTile * kRowTile;
-  B.bpad = (B.bpad + 8 * kSplitK - 1) / (8 * kSplitK) * (8 * kSplitK);
-  const int n_waves = B.bpad / kRowTile;
-  hipLaunchKernelGGL(k_train_rows, dim3((n_waves + 1) / 2), dim3(128), 0, st, X, t, n, s->w1b, s->w2b,
-                     s->params, B);
-  hipLaunchKernelGGL(k_weight_grads, dim3(kGradTiles * kSplitK), dim3(64), 0, st, B);
+  const int blocks = train_blocks(n);
+  hipLaunchKernelGGL(k_train, dim3(blocks), dim3(64 * kTrainWaves), 0, st, X, t, n, s->w1b, s->w2b, s->params,
+                     s->part);
   float c1 = 1.f, c2 = 1.f;
   if (!grad_out) {
     s->steps += 1;
     c1 = 1.f / (1.f - powf(0.9f, static_cast<float>(s->steps)));
     c2 = 1.f / (1.f - powf(0.999f, static_cast<float>(s->steps)));
   }
-  hipLaunchKernelGGL(k_reduce_update, dim3((kParams + 255) / 256), dim3(256), 0, st, B, n_waves,
+  hipLaunchKernelGGL(k_reduce_update, dim3(kPart / 64), dim3(64 * kSumGroups), 0, st, s->part, blocks,
                      s->params, s->adam_m, s->adam_v, s->w1b, s->w2b, lr, c1, c2, grad_out, loss_out, n);
   return sdev(hipGetLastError(), "training kernels");
 }
@@ -1133,8 +1293,6 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
   s->p = p;
   s->max_rows = max_rows;
   const int NT = p->view.n_tets;
-  const int bmax = ((max_rows + 8 * kSplitK - 1) / (8 * kSplitK) + 1) * (8 * kSplitK) + kRowTile;
-  s->tb.bpad = bmax;
   morea_status st = MOREA_OK;
   auto ok = [&](morea_status r) { if (st == MOREA_OK) st = r; return st == MOREA_OK; };
   ok(salloc(s, &s->params, sizeof(float) * kParams));
@@ -1144,12 +1302,7 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
   ok(salloc(s, &s->w2b, sizeof(bf16) * kHid * kHid));
   ok(salloc(s, &s->stats, sizeof(float) * 8 * NT));
   ok(salloc(s, &s->counts, sizeof(int) * NT));
-  ok(salloc(s, &s->tb.xT, sizeof(bf16) * kInPad * static_cast<size_t>(bmax)));
-  ok(salloc(s, &s->tb.h1T, sizeof(bf16) * kHid * static_cast<size_t>(bmax)));
-  ok(salloc(s, &s->tb.dz2T, sizeof(bf16) * kHid * static_cast<size_t>(bmax)));
-  ok(salloc(s, &s->tb.dz1T, sizeof(bf16) * kHid * static_cast<size_t>(bmax)));
-  ok(salloc(s, &s->tb.wpart, sizeof(float) * kWavePart * static_cast<size_t>(bmax / kRowTile + 4)));
-  ok(salloc(s, &s->tb.gpart, sizeof(float) * kSplitK * kGradTiles * 1024));
+  ok(salloc(s, &s->part, sizeof(float) * kPart * static_cast<size_t>(train_blocks(max_rows))));
   ok(salloc(s, &s->ref, sizeof(float) * 3 * p->view.n_points));
   ok(salloc(s, &s->img_s, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
   ok(salloc(s, &s->img_t, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
