@@ -8,11 +8,15 @@
 // none the displacement 0; a tet with a vertex coordinate that is not finite
 // or has |x| >= 512 voxels is skipped.
 //
-// Two passes of one 64-lane wave per (direction, tet), lanes over the voxels
-// of the tet's bounding box: the first claims each covered centre with an
-// atomic minimum of the tet index and counts the covering tets, the second
-// lets the owner write the displacement (FP64 barycentric image, rounded once
-// to FP32).
+// One pass over the (direction, tet) pairs: 64 rows of the tet's box at a
+// time, one per lane, whose x-intervals are solved exactly from the four face
+// planes; the voxels of the rows then go to the lanes in order.  Every
+// covering tet lowers the centre's owner to its index, counts itself when it
+// is not the first, and writes its displacement; where a centre is covered
+// once that is the result, and a last pass over the voxels completes the
+// counts and writes the others (0 for a centre in no tet, the owner's
+// displacement for one in several).  The displacement is the FP64
+// barycentric image rounded once to FP32.
 //
 // The same exact point location gives the point-based guidance error of the
 // paper's prior work, which Sec. 4.1.3 replaces by the continuous form: every
@@ -24,9 +28,11 @@
 #include <math.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "morea_internal.h"
+#include "morea_raster.h"
 
 namespace morea {
 namespace dvf {
@@ -34,6 +40,12 @@ namespace dvf {
 typedef __int128 i128;
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // 6 x signed volume (exact in 128 bits for any coordinates below 2^21)
 __device__ __forceinline__ i128 vol6(const int64_t a[3], const int64_t b[3], const int64_t c[3], const int64_t d[3]) {
@@ -80,24 +92,190 @@ __device__ __forceinline__ bool inside(const int64_t v[4][3], int sgn, const int
   return true;
 }
 
-__global__ void k_dvf_clear(size_t V, int* owner, uint32_t* cover, float* fwd, float* inv) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= 2 * V) return;
-  owner[i] = 0x7fffffff;
-  cover[i] = 0u;
-  float* out = i < V ? fwd + 3 * i : inv + 3 * (i - V);
-  out[0] = out[1] = out[2] = 0.f;
+constexpr int kNoOwner = 0x7fffffff;
+constexpr int kClearPer = 4;   // voxels per thread, a block's width apart
+
+__global__ __launch_bounds__(256) void k_dvf_clear(size_t n, int* owner, uint32_t* cover) {
+  const size_t first = static_cast<size_t>(blockIdx.x) * (256 * kClearPer) + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < kClearPer; q++) {
+    const size_t i = first + 256 * q;
+    if (i < n) {
+      owner[i] = kNoOwner;
+      cover[i] = 0u;
+    }
+  }
 }
 
-template <bool WRITE>
-__global__ __launch_bounds__(256) void k_dvf_pass(ProblemView P, const float* cand, int* owner, uint32_t* cover,
-                                                float* fwd, float* inv) {
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int item = blockIdx.x * 4 + wave;
-  if (item >= 2 * P.n_tets) return;
-  const int d = item / P.n_tets, t = item % P.n_tets;
+// Face planes of a tet about the box corner lo: for voxel lo + (j, y, z) the
+// value s_i = A_i j + PY_i y + PZ_i z + B_i is 6 |V| times the barycentric
+// coordinate of vertex i, an exact integer; T is double for extents up to
+// 2^16 units (every sum below 2^53) and int64 otherwise.  lex_i: a centre on
+// face i belongs to the tet (the first nonzero component of the inward normal
+// is positive).
+template <typename T>
+struct Planes {
+  T A[4], PY[4], PZ[4], B[4];
+  int lex[4];
+};
+
+template <typename T>
+__device__ __forceinline__ Planes<T> tet_planes(const int own[4][3], const int lo[3], int sgn) {
+  Planes<T> P;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int b = i == 0 ? 1 : 0, u0 = i == 0 ? 2 : (i == 1 ? 2 : (i == 2 ? 3 : 1)),
+              w0 = i == 0 ? 3 : (i == 1 ? 3 : (i == 2 ? 1 : 2));
+    T u[3], w[3], o[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      u[k] = static_cast<T>(own[u0][k] - own[b][k]);
+      w[k] = static_cast<T>(own[w0][k] - own[b][k]);
+      o[k] = static_cast<T>(1024 * lo[k] - own[b][k]);
+    }
+    const T f = static_cast<T>(i == 0 ? -sgn : sgn);
+    const T x = f * (u[1] * w[2] - u[2] * w[1]), y = f * (u[2] * w[0] - u[0] * w[2]),
+            z = f * (u[0] * w[1] - u[1] * w[0]);
+    P.lex[i] = (x > 0 || (x == 0 && (y > 0 || (y == 0 && z > 0)))) ? 1 : 0;
+    P.A[i] = x * 1024;
+    P.PY[i] = y * 1024;
+    P.PZ[i] = z * 1024;
+    P.B[i] = x * o[0] + y * o[1] + z * o[2];
+  }
+  return P;
+}
+
+// Snapped vertices of tet t in the sampled mesh d and in the other one;
+// false when a coordinate is invalid.
+__device__ __forceinline__ bool load_tet(const ProblemView& P, const float* cand, int d, int t, int own[4][3],
+                                         int oth[4][3]) {
+  const int4 tv = P.tets[t];
+  const int vs[4] = {tv.x, tv.y, tv.z, tv.w};
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      const float x = cand[(d * 3 + k) * P.n_points + vs[i]], y = cand[((1 - d) * 3 + k) * P.n_points + vs[i]];
+      const bool fine = fabsf(x) < kCoordLimit && fabsf(y) < kCoordLimit;
+      ok = ok && fine;
+      own[i][k] = fine ? static_cast<int>(rintf(x * kFixOne)) : 0;
+      oth[i][k] = fine ? static_cast<int>(rintf(y * kFixOne)) : 0;
+    }
+  return ok;
+}
+
+__device__ __forceinline__ int64_t det6(const int v[4][3]) {   // |coordinates| < 2^19: below 2^63
+  const int64_t a0 = v[1][0] - v[0][0], a1 = v[1][1] - v[0][1], a2 = v[1][2] - v[0][2];
+  const int64_t b0 = v[2][0] - v[0][0], b1 = v[2][1] - v[0][1], b2 = v[2][2] - v[0][2];
+  const int64_t c0 = v[3][0] - v[0][0], c1 = v[3][1] - v[0][1], c2 = v[3][2] - v[0][2];
+  return a0 * (b1 * c2 - b2 * c1) - a1 * (b0 * c2 - b2 * c0) + a2 * (b0 * c1 - b1 * c0);
+}
+
+// Displacement of a voxel from the face values of vertices 1..3 there.
+__device__ __forceinline__ void displacement(const double val[3], double inv_absD, const int oth[4][3],
+                                             const int pv[3], float out[3]) {
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    double q = static_cast<double>(oth[0][a]);
+#pragma unroll
+    for (int i = 0; i < 3; i++) q += val[i] * inv_absD * static_cast<double>(oth[i + 1][a] - oth[0][a]);
+    out[a] = static_cast<float>(q * (1.0 / 1024.0) - pv[a]);
+  }
+}
+
+struct __attribute__((aligned(4))) F3 {
+  float v[3];
+};
+
+// Rows [64 (part + k parts), ..) of a tet's box.  `mark` is 64 words of LDS
+// of the wave.
+template <typename T>
+__device__ __forceinline__ void raster_rows(const ProblemView& P, const int own[4][3], const int oth[4][3], int t,
+                                            int64_t D, const int lo[3], const int ext[3], int part, int parts,
+                                            int* mark, int* owner, uint32_t* cover, float* out) {
   const int lane = lane_id();
+  const Planes<T> pl = tet_planes<T>(own, lo, D > 0 ? 1 : -1);
+  const double inv_absD = 1.0 / static_cast<double>(D > 0 ? D : -D);
+  double invA[4];
+  int kind[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    kind[i] = (pl.A[i] > 0) - (pl.A[i] < 0);
+    // an estimate (clip_face corrects the row's end by the exact value)
+    const double a = static_cast<double>(pl.A[i]), r = __builtin_amdgcn_rcp(a);
+    invA[i] = kind[i] != 0 ? fma(fma(-a, r, 1.0), r, r) : 0.0;
+  }
+  const int rows = ext[1] * ext[2];
+  int tag = 0;
+  for (int rb = 64 * part; rb < rows; rb += 64 * parts) {
+    const int r = rb + lane, zr = r / ext[1], yr = r - zr * ext[1];
+    int js = 0, je = r < rows ? ext[0] - 1 : -1;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const T b = pl.PY[i] * yr + pl.PZ[i] * zr + pl.B[i] + pl.lex[i];
+      clip_face<T>(kind[i], pl.A[i], invA[i], b, ext[0] - 1, js, je);
+    }
+    const int len = max(0, je - js + 1);
+    // the voxels of the 64 rows form one stream; `at` is the row's first
+    int at = len;
+    at += __builtin_amdgcn_update_dpp(0, at, 0x111, 0xf, 0xf, false);   // within rows of 16 lanes: shifts by 1, 2,
+    at += __builtin_amdgcn_update_dpp(0, at, 0x112, 0xf, 0xf, false);   // 4 and 8
+    at += __builtin_amdgcn_update_dpp(0, at, 0x114, 0xf, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, 0x118, 0xf, 0xf, false);
+    at += __builtin_amdgcn_update_dpp(0, at, 0x142, 0xa, 0xf, false);   // lane 15 -> rows 1, 3
+    at += __builtin_amdgcn_update_dpp(0, at, 0x143, 0xc, 0xf, false);   // lane 31 -> rows 2, 3
+    const int total = __builtin_amdgcn_readlane(at, 63);
+    at -= len;
+    const int packed = js | yr << 10 | zr << 20;
+    for (int s = 0; s < total; s += 64) {
+      // row of voxel s + lane: the last non-empty one that starts at or
+      // before it -- one that starts inside the batch marks its place there
+      tag += 64;
+      if (len > 0 && at > s && at < s + 64) mark[at - s] = tag + lane;
+      const int first = __builtin_ctzll(__ballot(len > 0 && at <= s && at + len > s));
+      wave_sync();
+      const int mk = mark[lane];
+      const uint64_t starts = __ballot(mk >= tag);
+      wave_sync();
+      const uint64_t upto = starts & (~0ull >> (63 - lane));
+      const int src = upto ? 63 - __builtin_clzll(upto) : lane;
+      const int marked = __shfl(mk, src, 64) & 63;
+      const int row = upto ? marked : first;
+      const int u = s + lane, w = __shfl(packed, row, 64), u0 = __shfl(at, row, 64);
+      if (u >= total) continue;
+      const int j = (w & 1023) + u - u0, y = (w >> 10) & 1023, z = w >> 20;
+      double val[3];
+#pragma unroll
+      for (int i = 0; i < 3; i++)
+        val[i] = static_cast<double>(pl.A[i + 1] * j + pl.PY[i + 1] * y + pl.PZ[i + 1] * z + pl.B[i + 1]);
+      const int pv[3] = {lo[0] + j, lo[1] + y, lo[2] + z};
+      const size_t v = (static_cast<size_t>(pv[2]) * P.ny + pv[1]) * P.nx + pv[0];
+      F3 o;
+      displacement(val, inv_absD, oth, pv, o.v);
+      *reinterpret_cast<F3*>(out + 3 * v) = o;
+      if (atomicMin(&owner[v], t) != kNoOwner) atomicAdd(&cover[v], 1u);
+    }
+  }
+}
+
+// One wave per (direction, tet, part of its rows).  Bound: the atomics on the
+// owners, one request per row of a tet (128x128x96 voxels, 3,402 tets: 52 us,
+// 27 of them without any atomic or store; with the count as a second atomic
+// per voxel 72), then a wave's chain of loads, spans and batches.  Testing
+// every voxel of the boxes in 128-bit integers, twice, took 536 + 576 us.
+__global__ __launch_bounds__(256) void k_dvf(ProblemView P, const float* cand, int parts, int* owner,
+                                           uint32_t* cover, float* fwd, float* inv) {
+  __shared__ int marks[4][64];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  marks[wave][lane_id()] = 0;
+  const int64_t w = static_cast<int64_t>(blockIdx.x) * 4 + wave;
+  const int64_t item = w / parts;
+  if (item >= 2 * static_cast<int64_t>(P.n_tets)) return;
+  const int part = static_cast<int>(w - item * parts);
+  const int d = item >= P.n_tets, t = static_cast<int>(item - (d ? P.n_tets : 0));
   // lane l < 24: mesh (l < 12 ? sampled : other), vertex (l % 12) / 3, axis l % 3
+  const int lane = lane_id();
   const int4 tv = P.tets[t];
   float x = 0.f;
   if (lane < 24) {
@@ -108,7 +286,7 @@ __global__ __launch_bounds__(256) void k_dvf_pass(ProblemView P, const float* ca
   }
   if (__ballot(lane < 24 && !(fabsf(x) < kCoordLimit)) != 0ull) return;
   const int fix = lane < 24 ? static_cast<int>(rintf(x * kFixOne)) : 0;
-  int64_t own[4][3], oth[4][3];
+  int own[4][3], oth[4][3];
 #pragma unroll
   for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -116,54 +294,58 @@ __global__ __launch_bounds__(256) void k_dvf_pass(ProblemView P, const float* ca
       own[i][k] = __builtin_amdgcn_readlane(fix, 3 * i + k);
       oth[i][k] = __builtin_amdgcn_readlane(fix, 12 + 3 * i + k);
     }
-  const i128 D = vol6(own[0], own[1], own[2], own[3]);
+  const int64_t D = det6(own);
   if (D == 0) return;
-  const int sgn = D > 0 ? 1 : -1;
-  const double inv_absD = 1.0 / static_cast<double>(D > 0 ? D : -D);
   const int dims[3] = {P.nx, P.ny, P.nz};
-  int lo[3], ext[3];
+  int lo[3], ext[3], wide = 0;
 #pragma unroll
   for (int k = 0; k < 3; k++) {
-    int64_t mn = own[0][k], mx = own[0][k];
-#pragma unroll
-    for (int i = 1; i < 4; i++) {
-      mn = min(mn, own[i][k]);
-      mx = max(mx, own[i][k]);
-    }
-    // ceil(mn / 1024) and floor(mx / 1024), clipped to the grid
-    const int64_t c = mn >= 0 ? (mn + 1023) / 1024 : -((-mn) / 1024);
-    const int64_t f = mx >= 0 ? mx / 1024 : -((-mx + 1023) / 1024);
-    lo[k] = static_cast<int>(max<int64_t>(c, 0));
-    ext[k] = static_cast<int>(min<int64_t>(f, dims[k] - 1)) - lo[k] + 1;
+    const int mn = min(min(own[0][k], own[1][k]), min(own[2][k], own[3][k]));
+    const int mx = max(max(own[0][k], own[1][k]), max(own[2][k], own[3][k]));
+    wide = max(wide, mx - mn);
+    lo[k] = max((mn + 1023) >> 10, 0);                        // ceil(mn / 1024), floor(mx / 1024)
+    ext[k] = min(mx >> 10, dims[k] - 1) - lo[k] + 1;
   }
   if (ext[0] <= 0 || ext[1] <= 0 || ext[2] <= 0) return;
   const size_t V = static_cast<size_t>(P.nx) * P.ny * P.nz;
-  const int64_t box = static_cast<int64_t>(ext[0]) * ext[1] * ext[2];
-  for (int64_t q = lane; q < box; q += 64) {
-    const int xv = lo[0] + static_cast<int>(q % ext[0]);
-    const int yv = lo[1] + static_cast<int>((q / ext[0]) % ext[1]);
-    const int zv = lo[2] + static_cast<int>(q / (static_cast<int64_t>(ext[0]) * ext[1]));
-    const int64_t p[3] = {static_cast<int64_t>(xv) * 1024, static_cast<int64_t>(yv) * 1024,
-                          static_cast<int64_t>(zv) * 1024};
-    i128 val[4];
-    if (!inside(own, sgn, p, val)) continue;
-    const size_t v = (static_cast<size_t>(zv) * P.ny + yv) * P.nx + xv;
-    if (!WRITE) {
-      atomicMin(&owner[d * V + v], t);
-      atomicAdd(&cover[d * V + v], 1u);
-    } else if (owner[d * V + v] == t) {
-      float* out = (d == 0 ? fwd : inv) + 3 * v;
-      const int pv[3] = {xv, yv, zv};
-#pragma unroll
-      for (int a = 0; a < 3; a++) {
-        double qa = static_cast<double>(oth[0][a]);
-#pragma unroll
-        for (int i = 1; i < 4; i++)
-          qa += static_cast<double>(val[i]) * inv_absD * static_cast<double>(oth[i][a] - oth[0][a]);
-        out[a] = static_cast<float>(qa * (1.0 / 1024.0) - pv[a]);
-      }
-    }
+  int* ow = owner + d * V;
+  uint32_t* cv = cover + d * V;
+  float* out = d == 0 ? fwd : inv;
+  if (wide <= kFastExtent)
+    raster_rows<double>(P, own, oth, t, D, lo, ext, part, parts, marks[wave], ow, cv, out);
+  else
+    raster_rows<long long>(P, own, oth, t, D, lo, ext, part, parts, marks[wave], ow, cv, out);
+}
+
+// The counts, and the centres covered by no tet or by several (one thread per
+// centre; `cover` holds the covering tets beyond the first).
+__global__ __launch_bounds__(256) void k_dvf_rest(ProblemView P, const float* cand, const int* owner,
+                                                uint32_t* cover, float* fwd, float* inv) {
+  const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+  const size_t V = static_cast<size_t>(P.nx) * P.ny * P.nz;
+  if (i >= 2 * V) return;
+  const int t = owner[i];
+  const uint32_t c = t == kNoOwner ? 0u : cover[i] + 1u;
+  if (c != 0u) cover[i] = c;
+  if (c == 1u) return;
+  const int d = i >= V;
+  const size_t v = i - (d ? V : 0);
+  float o[3] = {0.f, 0.f, 0.f};
+  if (c > 1u) {
+    const int pv[3] = {static_cast<int>(v % P.nx), static_cast<int>(v / P.nx % P.ny),
+                       static_cast<int>(v / (static_cast<size_t>(P.nx) * P.ny))};
+    int own[4][3], oth[4][3];
+    load_tet(P, cand, d, t, own, oth);
+    const int64_t D = det6(own);
+    const Planes<long long> pl = tet_planes<long long>(own, pv, D > 0 ? 1 : -1);
+    const double val[3] = {static_cast<double>(pl.B[1]), static_cast<double>(pl.B[2]),
+                           static_cast<double>(pl.B[3])};
+    displacement(val, 1.0 / static_cast<double>(D > 0 ? D : -D), oth, pv, o);
   }
+  float* out = (d ? inv : fwd) + 3 * v;
+  out[0] = o[0];
+  out[1] = o[1];
+  out[2] = o[2];
 }
 
 // Point-based guidance: one block of 4 waves per candidate; wave w takes the
@@ -340,11 +522,17 @@ morea_status launch_dvf(morea_problem* p, const float* cand, float* fwd, float* 
                         hipStream_t s) {
   const ProblemView& P = p->view;
   const size_t V = static_cast<size_t>(P.nx) * P.ny * P.nz;
-  const int items = 2 * P.n_tets;
-  hipLaunchKernelGGL(dvf::k_dvf_clear, dim3(static_cast<unsigned>((2 * V + 255) / 256)), dim3(256), 0, s, V, work,
-                     cover, fwd, inv);
-  hipLaunchKernelGGL(dvf::k_dvf_pass<false>, dim3((items + 3) / 4), dim3(256), 0, s, P, cand, work, cover, fwd, inv);
-  hipLaunchKernelGGL(dvf::k_dvf_pass<true>, dim3((items + 3) / 4), dim3(256), 0, s, P, cand, work, cover, fwd, inv);
+  // one wave per 512 voxels of an average tet, so that a mesh of a few large
+  // tets fills the chip too (a wave takes about 10 us for its set-up and as
+  // long for 512 voxels); parts beyond a tet's rows return at once
+  const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(256, static_cast<int64_t>(V) / P.n_tets / 512));
+  const int64_t waves = 2 * static_cast<int64_t>(P.n_tets) * parts;
+  hipLaunchKernelGGL(dvf::k_dvf_clear, dim3(static_cast<unsigned>((2 * V + 256 * dvf::kClearPer - 1) / (256 * dvf::kClearPer))),
+                     dim3(256), 0, s, 2 * V, work, cover);
+  hipLaunchKernelGGL(dvf::k_dvf, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, s, P, cand,
+                     static_cast<int>(parts), work, cover, fwd, inv);
+  hipLaunchKernelGGL(dvf::k_dvf_rest, dim3(static_cast<unsigned>((2 * V + 255) / 256)), dim3(256), 0, s, P, cand,
+                     work, cover, fwd, inv);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     char buf[256];

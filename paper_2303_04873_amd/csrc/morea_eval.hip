@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "morea_internal.h"
+#include "morea_raster.h"
 
 namespace morea {
 
@@ -253,28 +254,6 @@ __device__ __forceinline__ bool exact_foreground(const ProblemView& P, const voi
         if (cx >= 0 && cy >= 0 && cz >= 0 && cx < nx && cy < ny && cz < nz)
           fg |= ld_img<ST>(img, (cz + 1) * P.pxy + (cy + 1) * P.px + cx + 1) > 0.0f;
   return fg;
-}
-
-// Exact x-interval update for one face: the j with A j + b > 0.  The FP64
-// quotient estimate is corrected by one exact evaluation on each side; T is
-// double (exact for extents <= 2^16) or int64.
-template <typename T>
-__device__ __forceinline__ void clip_face(int kind, T A, double invA, T b, int W, int& js, int& je) {
-  if (kind > 0) {
-    const double t = fmin(fmax(-static_cast<double>(b) * invA, -2.0), W + 1.0);
-    int j = static_cast<int>(floor(t)) + 1;
-    if (A * static_cast<T>(j) + b <= 0) j += 1;
-    else if (A * static_cast<T>(j - 1) + b > 0) j -= 1;
-    js = max(js, j);
-  } else if (kind < 0) {
-    const double t = fmin(fmax(-static_cast<double>(b) * invA, -2.0), W + 1.0);
-    int j = static_cast<int>(ceil(t)) - 1;
-    if (A * static_cast<T>(j) + b <= 0) j -= 1;
-    else if (A * static_cast<T>(j + 1) + b > 0) j += 1;
-    je = min(je, j);
-  } else if (!(b > 0)) {
-    je = -1;
-  }
 }
 
 // x-interval [js, je] (relative to the box start, within [0, W]) of row

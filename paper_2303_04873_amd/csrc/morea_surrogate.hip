@@ -1030,8 +1030,10 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, c
     }
   __syncthreads();
 #pragma unroll
-  for (int e = threadIdx.x; e < 4 * 1024; e += kThreads)
+  for (int e0 = 0; e0 < 4 * 1024; e0 += kThreads) {
+    const int e = e0 + threadIdx.x;
     out[16 * 1024 + e] = ((S.dw1[0][e] + S.dw1[1][e]) + S.dw1[2][e]) + S.dw1[3][e];
+  }
   for (int e = threadIdx.x; e < kPart - kPartTiles; e += kThreads)
     out[kPartTiles + e] = e < kPartSums ? ((S.sums[0][e] + S.sums[1][e]) + S.sums[2][e]) + S.sums[3][e] : 0.f;
 }
