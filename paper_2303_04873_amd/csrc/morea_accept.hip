@@ -166,51 +166,90 @@ __global__ __launch_bounds__(kBlock) void k_write_back(int n_evals, int n_parent
 //   the cluster of a valid solution: its nearest leader (ties to the lower
 //     cluster); -1 for an invalid one.
 constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / kWave;
 
 struct SelShared {
-  double key[kSelThreads];
-  int idx[kSelThreads];
-  int scan[kSelThreads];
-  int count;
+  union {
+    uint32_t dom[kSelThreads / 32][kSelThreads];   // [word][solution] dominators, bit by bit
+    struct {                                       // once the fronts are known
+      double norm[3][kSelThreads];                 // normalised objectives of the population
+      double sel[3][kSelThreads];                  // and of the selected solutions, in order
+      double key[kSelThreads];                     // distances to the leaders of a pass
+      int leader[kSelThreads];
+      int who[kSelThreads];                        // index of each selected solution
+    };
+  };
+  // feasible: the objectives, infeasible: the violation (folds, excess, 0);
+  // w: bit 0 valid, bit 1 feasible
+  float4 sol[kSelThreads];
+  uint32_t left[kSelThreads / 32];
+  double wkey[kSelThreads / 16];
+  int widx[kSelThreads / 16];
+  int wsum[kSelWaves];
 };
+
+// One step of the lexicographic minimum of (key, idx) over the 16 lanes of a
+// DPP row, by the lane permutation `ctrl`.
+template <int ctrl>
+__device__ __forceinline__ void argmin_step(double& key, int& idx) {
+  const uint64_t u = static_cast<uint64_t>(__double_as_longlong(key));
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), ctrl, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), ctrl, 0xf, 0xf, false);
+  const double k2 = __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(hi) << 32 | lo));
+  const int i2 = __builtin_amdgcn_update_dpp(0, idx, ctrl, 0xf, 0xf, false);
+  const bool less = k2 < key || (k2 == key && i2 < idx);
+  key = less ? k2 : key;
+  idx = less ? i2 : idx;
+}
+
+__device__ __forceinline__ void argmin_row(double& key, int& idx) {
+  argmin_step<0xb1>(key, idx);     // quad_perm 1 0 3 2
+  argmin_step<0x4e>(key, idx);     // quad_perm 2 3 0 1
+  argmin_step<0x141>(key, idx);    // row_half_mirror
+  argmin_step<0x140>(key, idx);    // row_mirror
+}
 
 // Block-wide minimum of (key, idx) (lexicographic); every thread returns it.
 __device__ void block_argmin(SelShared& S, double key, int idx, double& out_key, int& out_idx) {
-  const int t = threadIdx.x;
-  S.key[t] = key;
-  S.idx[t] = idx;
-  __syncthreads();
-  for (int d = kSelThreads / 2; d > 0; d >>= 1) {
-    if (t < d) {
-      const double k2 = S.key[t + d];
-      const int i2 = S.idx[t + d];
-      if (k2 < S.key[t] || (k2 == S.key[t] && i2 < S.idx[t])) {
-        S.key[t] = k2;
-        S.idx[t] = i2;
-      }
-    }
-    __syncthreads();
+  const int lane = threadIdx.x & 63;
+  argmin_row(key, idx);
+  if ((lane & 15) == 0) {
+    S.wkey[threadIdx.x >> 4] = key;
+    S.widx[threadIdx.x >> 4] = idx;
   }
-  out_key = S.key[0];
-  out_idx = S.idx[0];
+  __syncthreads();
+  key = S.wkey[lane];              // 64 rows of 16 threads
+  idx = S.widx[lane];
+  argmin_row(key, idx);
+#pragma unroll
+  for (int d = 16; d <= 32; d <<= 1) {
+    const double k2 = __shfl_xor(key, d, 64);
+    const int i2 = __shfl_xor(idx, d, 64);
+    const bool less = k2 < key || (k2 == key && i2 < idx);
+    key = less ? k2 : key;
+    idx = less ? i2 : idx;
+  }
+  out_key = key;
+  out_idx = idx;
   __syncthreads();
 }
 
-// Block-wide exclusive prefix sum of v; *total receives the sum.
-__device__ int block_scan(SelShared& S, int v, int* total) {
-  const int t = threadIdx.x;
-  S.scan[t] = v;
+// Block-wide exclusive prefix sum of a flag; *total receives the sum.
+__device__ int block_scan(SelShared& S, bool v, int* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t m = __ballot(v);
+  if (lane == 0) S.wsum[w] = __popcll(m);
   __syncthreads();
-  for (int d = 1; d < kSelThreads; d <<= 1) {
-    const int x = t >= d ? S.scan[t - d] : 0;
-    __syncthreads();
-    S.scan[t] += x;
-    __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < kSelWaves; k++) {
+    const int s = S.wsum[k];
+    before += k < w ? s : 0;
+    all += s;
   }
-  const int incl = S.scan[t];
-  *total = S.scan[kSelThreads - 1];
   __syncthreads();
-  return incl - v;
+  *total = all;
+  return before + __popcll(m & ((1ull << lane) - 1ull));
 }
 
 __device__ __forceinline__ double dist3(const double* a, const double* b) {
@@ -224,6 +263,14 @@ __device__ __forceinline__ double dist3(const double* a, const double* b) {
   return s;
 }
 
+// Bound: the latency and issue of one block (every step needs the one before);
+// 512 solutions, 179 selected into 10 clusters: 83 us, before 337.  The
+// dominator rows are split over all threads (several to a solution when the
+// population is smaller than the block) and tested without branches (with
+// them 106 us of the kernel), the reductions run on DPP rows and 64 row
+// results (1.8 us each over shuffles of whole waves), and the clusters'
+// members are ranked for as many clusters at a time as the block holds copies
+// of the selection.
 __global__ __launch_bounds__(kSelThreads) void k_select(int n, int size, int k, float gmax,
                                                         const float* __restrict__ obj,
                                                         const uint8_t* __restrict__ flags,
@@ -233,83 +280,79 @@ __global__ __launch_bounds__(kSelThreads) void k_select(int n, int size, int k, 
                                                         int* __restrict__ cluster_of) {
 #pragma clang fp contract(off)
   __shared__ SelShared S;
-  __shared__ float s_o[3][kSelThreads];
-  __shared__ float s_fold[kSelThreads], s_exc[kSelThreads];
-  __shared__ uint8_t s_feas[kSelThreads], s_left[kSelThreads];
-  __shared__ double s_norm[3][kSelThreads];
-  __shared__ int s_leader[kSelThreads];
   const int i = threadIdx.x;
   const bool in = i < n;
-  float o0 = 0.f, o1 = 0.f, o2 = 0.f, fold = 0.f, exc = 0.f;
-  bool valid = false, feas = false;
-  if (in) {
-    o0 = obj[3 * i];
-    o1 = obj[3 * i + 1];
-    o2 = obj[3 * i + 2];
-    const uint8_t f = flags[i];
-    const float sv = sev[i];
-    valid = !((f & 4u) || !isfinite(o0) || !isfinite(o1) || !isfinite(o2) || !isfinite(sv));
-    feas = feasible_of(o0, o1, o2, f, sv, gmax, fold, exc);
+  float o[3] = {0.f, 0.f, 0.f};
+  bool valid = false;
+  {
+    float fold = 0.f, exc = 0.f;
+    bool feas = false;
+    if (in) {
+      for (int q = 0; q < 3; q++) o[q] = obj[3 * i + q];
+      const uint8_t f = flags[i];
+      const float sv = sev[i];
+      valid = !((f & 4u) || !isfinite(o[0]) || !isfinite(o[1]) || !isfinite(o[2]) || !isfinite(sv));
+      feas = feasible_of(o[0], o[1], o[2], f, sv, gmax, fold, exc);
+    }
+    S.sol[i] = make_float4(feas ? o[0] : fold, feas ? o[1] : exc, feas ? o[2] : 0.f,
+                           __int_as_float((valid ? 1 : 0) | (feas ? 2 : 0)));
   }
-  s_o[0][i] = o0;
-  s_o[1][i] = o1;
-  s_o[2][i] = o2;
-  s_fold[i] = fold;
-  s_exc[i] = exc;
-  s_feas[i] = feas;
-  s_left[i] = valid;
+  const uint64_t vm = __ballot(valid);
+  if ((i & 31) == 0) S.left[i >> 5] = static_cast<uint32_t>(vm >> (i & 32));
   __syncthreads();
-  // dominators of each solution as a bit row (32 words of 32 solutions),
-  // then fronts by peeling until `size` solutions are covered: a solution
-  // joins the front when none of its dominators is left
-  __shared__ uint32_t s_left_bits[kSelThreads / 32];
-  if (i < kSelThreads / 32) s_left_bits[i] = 0u;
-  __syncthreads();
-  if (valid) atomicOr(&s_left_bits[i >> 5], 1u << (i & 31));
-  uint32_t dm[kSelThreads / 32];
-#pragma unroll
-  for (int w = 0; w < kSelThreads / 32; w++) {
-    uint32_t bits = 0u;
-    if (valid && w * 32 < n)
-      for (int b = 0; b < 32; b++) {
-        const int j = w * 32 + b;
-        if (j >= n || j == i || !s_left[j]) continue;
-        bool dom;
-        if (s_feas[j] && s_feas[i])
-          dom = pareto(s_o[0][j], s_o[1][j], s_o[2][j], s_o[0][i], s_o[1][i], s_o[2][i]);
-        else if (s_feas[j] != s_feas[i])
-          dom = s_feas[j];
-        else
-          dom = s_fold[j] < s_fold[i] || (s_fold[j] == s_fold[i] && s_exc[j] < s_exc[i]);
-        bits |= dom ? (1u << b) : 0u;
+  // dominators of each solution as bits; thread i takes every parts-th word
+  // of solution i % rows
+  const int n_words = (n + 31) / 32;
+  {
+    int rows = kWave;
+    while (rows < n) rows <<= 1;
+    const int me = i & (rows - 1), parts = kSelThreads / rows;
+    const float4 a = S.sol[me];
+    const bool a_feas = (__float_as_int(a.w) & 2) != 0;
+    for (int w = i / rows; w < n_words; w += parts) {
+      uint32_t bits = 0u;
+#pragma unroll 16
+      for (int j = 0; j < 32; j++) {    // solutions beyond n are not valid
+        const float4 b = S.sol[32 * w + j];
+        const int bm = __float_as_int(b.w);
+        const bool b_feas = (bm & 2) != 0;
+        // without branches: both feasible, both infeasible, or one of each
+        const bool lt = b.x < a.x, eq = b.x == a.x, lt1 = b.y < a.y, le1 = b.y <= a.y;
+        const bool par = (lt | eq) & le1 & (b.z <= a.z) & (lt | lt1 | (b.z < a.z));
+        const bool less = lt | (eq & lt1);
+        const bool same = a_feas ? par : less;
+        const bool dom = ((a_feas == b_feas) ? same : b_feas) & ((bm & 1) != 0);
+        bits |= static_cast<uint32_t>(dom) << j;
       }
-    dm[w] = bits;
+      S.dom[w][me] = bits;              // a solution does not dominate itself
+    }
   }
   __syncthreads();
-  int rank = -1, covered = 0, r = 0;
-  bool left = valid;
+  // fronts by peeling until `size` solutions are covered: a solution joins
+  // the front when none of its dominators is left
+  bool left = valid, chosen = false;
+  int covered = 0;
   while (covered < size) {
     uint32_t hit = 0u;
-#pragma unroll
-    for (int w = 0; w < kSelThreads / 32; w++) hit |= dm[w] & s_left_bits[w];
+    if (left)
+      for (int w = 0; w < n_words; w++) hit |= S.dom[w][i] & S.left[w];
     const bool front = left && hit == 0u;
     int n_front;
-    const int before = block_scan(S, front ? 1 : 0, &n_front);
+    const int before = block_scan(S, front, &n_front);   // its barriers end the reads of `left`
     if (n_front == 0) break;
+    // the last front needed is cut in ascending index
     if (front) {
       left = false;
-      atomicAnd(&s_left_bits[i >> 5], ~(1u << (i & 31)));
-      // the last front needed is cut in ascending index
-      if (covered + before < size) rank = r;
+      chosen = covered + before < size;
     }
+    const uint64_t lm = __ballot(left);
+    if ((i & 31) == 0) S.left[i >> 5] = static_cast<uint32_t>(lm >> (i & 32));
     covered += n_front;
-    r++;
     __syncthreads();
   }
-  const bool chosen = rank >= 0;
   int n_sel;
-  const int pos = block_scan(S, chosen ? 1 : 0, &n_sel);
-  if (chosen) sel_out[pos] = i;
+  const int pos = block_scan(S, chosen, &n_sel);
+  if (chosen) sel_out[pos] = S.who[pos] = i;
   if (i == 0) *n_sel_out = n_sel;
   const int k_eff = min(k, n_sel);
   const int m = n_sel == 0 ? 0 : min(n_sel, (2 * n_sel + k - 1) / k);
@@ -319,73 +362,74 @@ __global__ __launch_bounds__(kSelThreads) void k_select(int n, int size, int k, 
     return;
   }
   // normalisation over the selection (exact minima and maxima)
-  double lo[3], hi[3];
-  for (int o = 0; o < 3; o++) {
-    double mn, mx;
-    int dummy;
-    block_argmin(S, chosen ? static_cast<double>(s_o[o][i]) : INFINITY, i, mn, dummy);
-    block_argmin(S, chosen ? -static_cast<double>(s_o[o][i]) : INFINITY, i, mx, dummy);
-    lo[o] = mn;
-    hi[o] = -mx;
-  }
   double me[3];
-  for (int o = 0; o < 3; o++) {
-    const double v = static_cast<double>(s_o[o][i]);
-    me[o] = hi[o] > lo[o] ? (v - lo[o]) / (hi[o] - lo[o]) : 0.0;
-    s_norm[o][i] = me[o];
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+    double lo, hi;
+    int dummy;
+    const double v = static_cast<double>(o[q]);
+    block_argmin(S, chosen ? v : INFINITY, 0, lo, dummy);
+    block_argmin(S, chosen ? -v : INFINITY, 0, hi, dummy);
+    hi = -hi;
+    me[q] = hi > lo ? (v - lo) / (hi - lo) : 0.0;
+    S.norm[q][i] = me[q];
+    if (chosen) S.sel[q][pos] = me[q];
   }
   __syncthreads();
   // leaders: smallest first objective, then farthest points
   double kk;
   int first;
   block_argmin(S, chosen ? me[0] : INFINITY, chosen ? i : 0x7fffffff, kk, first);
-  if (i == 0) s_leader[0] = first;
-  double lead[3] = {s_norm[0][first], s_norm[1][first], s_norm[2][first]};
+  if (i == 0) S.leader[0] = first;
+  double lead[3] = {S.norm[0][first], S.norm[1][first], S.norm[2][first]};
   double nearest = chosen ? dist3(me, lead) : 0.0;
+  // cluster of every valid solution: the nearest leader, ties to the lower
+  int best = 0;
+  double best_d = dist3(me, lead);
   for (int j = 1; j < k_eff; j++) {
     int nxt;
     block_argmin(S, chosen ? -nearest : INFINITY, chosen ? i : 0x7fffffff, kk, nxt);
-    if (i == 0) s_leader[j] = nxt;
-    const double ln[3] = {s_norm[0][nxt], s_norm[1][nxt], s_norm[2][nxt]};
+    if (i == 0) S.leader[j] = nxt;
+    const double ln[3] = {S.norm[0][nxt], S.norm[1][nxt], S.norm[2][nxt]};
     const double d = dist3(me, ln);
     if (chosen && d < nearest) nearest = d;
+    if (d < best_d) {
+      best_d = d;
+      best = j;
+    }
   }
+  if (in) cluster_of[i] = valid ? best : -1;
   __syncthreads();
-  // members of each cluster: the m nearest selected solutions, ascending index
-  for (int j = 0; j < k_eff; j++) {
-    const int L = s_leader[j];
-    const double ln[3] = {s_norm[0][L], s_norm[1][L], s_norm[2][L]};
-    const double dme = dist3(me, ln);
-    S.key[i] = chosen ? dme : INFINITY;
+  // members of each cluster: the m nearest selected solutions, ascending
+  // index; `group` clusters per pass, thread i taking selected solution q of
+  // cluster j0 + g
+  const int group = max(1, kSelThreads / n_sel), g = i / n_sel, q = i - g * n_sel;
+  for (int j0 = 0; j0 < k_eff; j0 += group) {
+    const bool mine = g < group && j0 + g < k_eff;
+    double dme = 0.0;
+    if (mine) {
+      const int L = S.leader[j0 + g];
+      const double ln[3] = {S.norm[0][L], S.norm[1][L], S.norm[2][L]};
+      const double mq[3] = {S.sel[0][q], S.sel[1][q], S.sel[2][q]};
+      dme = dist3(mq, ln);
+      S.key[i] = dme;
+    }
     __syncthreads();
     int closer = 0;
-    if (chosen)
-      for (int q = 0; q < n; q++) {
-        const double dq = S.key[q];
-        closer += (dq < dme || (dq == dme && q < i)) ? 1 : 0;
+    if (mine) {
+      const double* keys = &S.key[g * n_sel];
+#pragma unroll 8
+      for (int r = 0; r < n_sel; r++) {
+        const double dq = keys[r];
+        closer += (dq < dme || (dq == dme && r < q)) ? 1 : 0;
       }
-    const bool member = chosen && closer < m;
+    }
+    const bool member = mine && closer < m;
     int cnt;
-    const int at = block_scan(S, member ? 1 : 0, &cnt);
-    // exactly m members by the (distance, index) order; the bound keeps every
-    // write inside cluster j's m slots whatever the keys hold
-    if (member && at < m) clu_members[j * m + at] = i;
-  }
-  // cluster of every valid solution: the nearest leader
-  if (in) {
-    int best = -1;
-    double bd = INFINITY;
-    if (valid)
-      for (int j = 0; j < k_eff; j++) {
-        const int L = s_leader[j];
-        const double ln[3] = {s_norm[0][L], s_norm[1][L], s_norm[2][L]};
-        const double d = dist3(me, ln);
-        if (best < 0 || d < bd) {
-          bd = d;
-          best = j;
-        }
-      }
-    cluster_of[i] = best;
+    // exactly m members by the (distance, index) order in every cluster of
+    // the pass; the bound keeps every write inside cluster j's m slots
+    const int at = block_scan(S, member, &cnt) - g * m;
+    if (member && at >= 0 && at < m) clu_members[(j0 + g) * m + at] = S.who[q];
   }
 }
 

@@ -31,12 +31,17 @@
 //     or the stretch has reached 25, c = 0.9 c; a c below 1 whose stretch is
 //     under 25 is reset to 1.
 //
-// The update is one block of 1,024 threads holding up to 4,096 candidates
-// in LDS: the members ordered by a bitonic sort of their stamps, domination
-// and duplicates by comparisons against LDS (broadcast reads; members only
-// against the offers, since they are mutually non-dominated and distinct),
-// and each resolution of the thinning's search by a bitonic sort of the
-// stayers' (box key, candidate) pairs.
+// The update is two kernels.  The domination tests (members against the
+// offers, since members are mutually non-dominated and distinct; offers
+// against every candidate) take one wave per candidate over the whole chip
+// and leave their verdicts in the archive itself: a member that does not stay
+// has its stamp replaced by kGone, an offer's verdict goes to `inserted`.
+// Then one block of 1,024 threads, a candidate's values in its thread's
+// registers, counts the boxes of each resolution in a hash table in LDS (the
+// number of different keys does not depend on the order of insertion; the
+// earliest candidate of a box is the smallest order value written to its
+// entry, a member's stamp or, above all stamps, the offer's index) and hands
+// out the slots by block prefixes.
 #include <math.h>
 #include <stdio.h>
 
@@ -47,50 +52,26 @@ namespace archive {
 
 constexpr int kThreads = 1024;
 constexpr int kMax = 4096;                 // members + offers per update
-constexpr int kPer = kMax / kThreads;
+constexpr int kPer = kMax / kThreads;      // slots per thread
 constexpr int kMaxLevels = 1024;           // boxes per objective (10-bit fields of a key)
 constexpr uint32_t kNoKey = 0xffffffffu;
+constexpr int kGone = INT32_MIN;           // stamp of a member that leaves, between the two kernels
+constexpr int kTable = 8192;               // hash entries: at most half full
+constexpr int kChunk = 8;                  // 64-candidate loads in flight per wave
 
+// without branches, so that the loads behind the arguments go out together
 __device__ __forceinline__ bool pareto(float a0, float a1, float a2, float b0, float b1, float b2) {
-  return a0 <= b0 && a1 <= b1 && a2 <= b2 && (a0 < b0 || a1 < b1 || a2 < b2);
+  return (a0 <= b0) & (a1 <= b1) & (a2 <= b2) & ((a0 < b0) | (a1 < b1) | (a2 < b2));
 }
 
 struct Shared {
-  float o[3][kMax];      // candidate objective vectors, in candidate order
-  int src[kMax];         // slot of a member, -1 - index of an offer
-  // sort keys: (stamp, slot) of the members, then (box key, candidate) of
-  // the stayers; afterwards the occupancy of the slots (low words)
-  uint64_t sortbuf[kMax];
-  int flag[kMax];        // first candidate of its box; then the free slots in ascending order
+  uint32_t key[kTable];      // box keys present
+  uint32_t order[kTable];    // smallest order value of the box
+  int free_slot[kMax];       // free slots in ascending order
   int wsum[kThreads / 64];
   float wmin[kThreads / 64];
   float wmax[kThreads / 64];
 };
-
-// Ascending bitonic sort of a[0 .. n2) (n2 a power of two, at most kMax) by
-// the whole block; ends with a barrier.
-__device__ void bitonic_sort(uint64_t* a, int n2) {
-  for (int k = 2; k <= n2; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += kThreads) {
-        const int l = i ^ j;
-        if (l > i) {
-          const uint64_t x = a[i], y = a[l];
-          if ((x > y) == ((i & k) == 0)) {
-            a[i] = y;
-            a[l] = x;
-          }
-        }
-      }
-      __syncthreads();
-    }
-}
-
-__device__ __forceinline__ int pow2_at_least(int n) {
-  int p = 1;
-  while (p < n) p <<= 1;
-  return p;
-}
 
 // Exclusive prefix over the block of one value per thread; *total gets the sum.
 __device__ int block_excl(Shared& S, int v, int* total) {
@@ -136,230 +117,229 @@ __device__ float block_max(Shared& S, float v) {
   return r;
 }
 
-__device__ __forceinline__ int box_of(float v, double lo, double hi, int L) {
+// Box along one axis of a value at the fraction t of the range.
+__device__ __forceinline__ int box_of(double t, int L) {
 #pragma clang fp contract(off)
-  if (!(hi > lo)) return 0;
-  const double t = (static_cast<double>(v) - lo) / (hi - lo);
-  const double s = t * static_cast<double>(L);
-  const int b = static_cast<int>(floor(s));
+  const int b = static_cast<int>(floor(t * static_cast<double>(L)));
   return b < L - 1 ? b : L - 1;
 }
 
-__global__ __launch_bounds__(kThreads) void k_update(int n_off, const float* __restrict__ offer_obj,
-                                                     const uint8_t* __restrict__ offer_flags,
-                                                     const float* __restrict__ offer_sev, float gmax, int cap,
+struct Offers {
+  const float* obj;
+  const uint8_t* flags;
+  const float* sev;
+  int n;
+};
+
+__device__ __forceinline__ bool feasible(const float b[3], unsigned flags, float sev) {
+  const bool f0 = isfinite(b[0]), f1 = isfinite(b[1]), f2 = isfinite(b[2]), fs = isfinite(sev);
+  return (flags == 0) & f0 & f1 & f2 & fs;
+}
+
+// Verdicts of the domination tests, one wave per candidate: slots 0 .. cap - 1,
+// then the offers.  Bound: latency (the arrays were written on another XCD, so
+// the first reads miss its L2; a wave has 8 x 64 candidates in flight);
+// capacity 2000 and 512 offers: 9 us on the whole chip (16 us when each
+// step's tests waited for a flag byte), most of the 415 us that the one block
+// took which did it before.
+__global__ __launch_bounds__(256) void k_dominate(Offers F, float gmax, int cap, const float* arc_obj,
+                                                int* arc_stamp, uint8_t* inserted) {
+  const int x = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  const int lane = threadIdx.x & 63;
+  if (x >= cap + F.n) return;
+  const int me = x - cap;                                  // offer index, negative for a member
+  float a[3];
+  bool ok;
+  if (me < 0) {
+    if (arc_stamp[x] < 0) return;
+    for (int o = 0; o < 3; o++) a[o] = arc_obj[3 * x + o];
+    ok = !(a[2] > gmax);
+  } else {
+    for (int o = 0; o < 3; o++) a[o] = F.obj[3 * me + o];
+    ok = feasible(a, F.flags[me], F.sev[me]) && !(a[2] > gmax);
+    for (int y0 = 0; y0 < cap && ok; y0 += 64 * kChunk) {
+      bool beaten = false;
+#pragma unroll
+      for (int q = 0; q < kChunk; q++) {
+        const int y = min(y0 + 64 * q + lane, cap - 1);     // a slot read twice changes nothing
+        const int st = arc_stamp[y];
+        const float b0 = arc_obj[3 * y], b1 = arc_obj[3 * y + 1], b2 = arc_obj[3 * y + 2];
+        // a member marked as gone meanwhile is a candidate all the same
+        const bool par = pareto(b0, b1, b2, a[0], a[1], a[2]);
+        const bool twin = (b0 == a[0]) & (b1 == a[1]) & (b2 == a[2]);
+        beaten |= ((st >= 0) | (st == kGone)) & !(b2 > gmax) & (par | twin);
+      }
+      ok = __ballot(beaten) == 0;
+    }
+  }
+  for (int y0 = 0; y0 < F.n && ok; y0 += 64 * kChunk) {
+    bool beaten = false;
+    float b[kChunk][3], sv[kChunk];
+    unsigned fl[kChunk];
+#pragma unroll
+    for (int q = 0; q < kChunk; q++) {     // every load of the step before the first test
+      const int y = min(y0 + 64 * q + lane, F.n - 1);
+      for (int o = 0; o < 3; o++) b[q][o] = F.obj[3 * y + o];
+      sv[q] = F.sev[y];
+      fl[q] = F.flags[y];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < kChunk; q++) {
+      const int y = min(y0 + 64 * q + lane, F.n - 1);
+      const bool feas = feasible(b[q], fl[q], sv[q]), par = pareto(b[q][0], b[q][1], b[q][2], a[0], a[1], a[2]);
+      const bool twin = (y < me) & (b[q][0] == a[0]) & (b[q][1] == a[1]) & (b[q][2] == a[2]);
+      beaten |= feas & (y != me) & !(b[q][2] > gmax) & (par | twin);
+    }
+    ok = __ballot(beaten) == 0;
+  }
+  if (lane != 0) return;
+  if (me >= 0)
+    inserted[me] = ok ? 1 : 0;
+  else if (!ok)
+    arc_stamp[x] = kGone;
+}
+
+// Entry of `key`, inserted when it is new (*fresh counts insertions).
+__device__ __forceinline__ int table_entry(Shared& S, uint32_t key, int* fresh) {
+  int h = static_cast<int>((key * 2654435761u) >> 19);
+  static_assert(kTable == 1 << 13, "hash width");
+  for (;;) {
+    const uint32_t old = atomicCAS(&S.key[h], kNoKey, key);
+    if (old == kNoKey) *fresh += 1;
+    if (old == kNoKey || old == key) return h;
+    h = (h + 1) & (kTable - 1);
+  }
+}
+
+// Thinning and slots.  One block: 11 passes over the box resolutions when
+// the capacity is exceeded (a pass is a cleared table and one insertion a
+// stayer instead of a bitonic sort of 78 steps), otherwise four prefixes, 6 us.
+__global__ __launch_bounds__(kThreads) void k_update(int n_off, const float* __restrict__ offer_obj, int cap,
                                                      float* __restrict__ arc_obj, int* __restrict__ arc_stamp,
                                                      int* __restrict__ arc_state, float* __restrict__ best_out,
                                                      uint8_t* __restrict__ inserted, int* __restrict__ slot_of) {
   __shared__ Shared S;
   const int t = threadIdx.x;
-  // ---- members in stamp order: sort (stamp, slot) of the occupied slots
-  const int ncap = pow2_at_least(cap);
-  int n_occ_mine = 0;
-  for (int s = t; s < ncap; s += kThreads) {
-    const int st = s < cap ? arc_stamp[s] : -1;
-    S.sortbuf[s] = st >= 0 ? (static_cast<uint64_t>(st) << 32 | static_cast<uint32_t>(s)) : ~0ull;
-    n_occ_mine += st >= 0 ? 1 : 0;
-  }
-  int nm;
-  block_excl(S, n_occ_mine, &nm);     // its barriers publish the keys
-  bitonic_sort(S.sortbuf, ncap);
-  for (int r = t; r < nm; r += kThreads) {
-    const int s = static_cast<int>(S.sortbuf[r] & 0xffffffffu);
-    S.o[0][r] = arc_obj[3 * s];
-    S.o[1][r] = arc_obj[3 * s + 1];
-    S.o[2][r] = arc_obj[3 * s + 2];
-    S.src[r] = s;
-  }
-  // ---- feasible offers after them, in index order
-  bool feas = false;
-  float f0 = 0.f, f1 = 0.f, f2 = 0.f;
-  if (t < n_off) {
-    f0 = offer_obj[3 * t];
-    f1 = offer_obj[3 * t + 1];
-    f2 = offer_obj[3 * t + 2];
-    const float sv = offer_sev[t];
-    feas = offer_flags[t] == 0 && isfinite(f0) && isfinite(f1) && isfinite(f2) && isfinite(sv);
-  }
-  int n_feas;
-  const int at = nm + block_excl(S, feas ? 1 : 0, &n_feas);
-  if (feas) {
-    S.o[0][at] = f0;
-    S.o[1][at] = f1;
-    S.o[2][at] = f2;
-    S.src[at] = -1 - t;
-  }
-  const int N = nm + n_feas;
-  __syncthreads();
-  // ---- stayers: inside the steering window, not dominated, first of equals.
-  // The members are mutually non-dominated and distinct (every update leaves
-  // them so), so a member can only be dominated by an offer and is never the
-  // later of two equal vectors; an offer is tested against every candidate.
-  bool stay[kPer];
-  int n_stay_mine = 0;
+  const int next = arc_state[1];
+  // candidates of this thread: slots t, t + 1024, .. and offer t
+  bool held[kPer], stay[kPer + 1];
+  float v[kPer + 1][3];
+  uint32_t order[kPer + 1];
+  int n_mine = 0;
 #pragma unroll
   for (int j = 0; j < kPer; j++) {
-    const int x = t + j * kThreads;
-    bool ok = x < N && !(S.o[2][x] > gmax);
-    if (ok) {
-      const float a0 = S.o[0][x], a1 = S.o[1][x], a2 = S.o[2][x];
-      for (int y = x < nm ? nm : 0; y < N; y++) {
-        const float b0 = S.o[0][y], b1 = S.o[1][y], b2 = S.o[2][y];
-        if (y == x || b2 > gmax) continue;
-        if (pareto(b0, b1, b2, a0, a1, a2) || (y < x && b0 == a0 && b1 == a1 && b2 == a2)) {
-          ok = false;
-          break;
-        }
-      }
-    }
-    stay[j] = ok;
-    n_stay_mine += ok ? 1 : 0;
+    const int s = t + j * kThreads;
+    const int st = s < cap ? arc_stamp[s] : -1;
+    held[j] = st >= 0 || st == kGone;
+    stay[j] = st >= 0;
+    order[j] = static_cast<uint32_t>(st);
+#pragma unroll
+    for (int o = 0; o < 3; o++) v[j][o] = stay[j] ? arc_obj[3 * s + o] : 0.f;
   }
+  stay[kPer] = t < n_off && inserted[t] != 0;
+  order[kPer] = 0x80000000u + t;                // after every member
+#pragma unroll
+  for (int o = 0; o < 3; o++) v[kPer][o] = stay[kPer] ? offer_obj[3 * t + o] : 0.f;
+#pragma unroll
+  for (int j = 0; j <= kPer; j++) n_mine += stay[j] ? 1 : 0;
   int n_stay;
-  block_excl(S, n_stay_mine, &n_stay);
-  // ---- thinning by boxes above capacity: per resolution, the stayers'
-  // (box key, candidate) sorted; the first entry of each key is its box's
-  // earliest candidate
+  block_excl(S, n_mine, &n_stay);
+  // ---- thinning by boxes above capacity
   int levels = 0;
   if (n_stay > cap) {
-    double lo[3], hi[3];
+    double at[kPer + 1][3];     // place in the stayers' range, per objective
+#pragma unroll
     for (int o = 0; o < 3; o++) {
       float mn = INFINITY, mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < kPer; j++) {
-        const int x = t + j * kThreads;
-        if (stay[j]) {
-          mn = fminf(mn, S.o[o][x]);
-          mx = fmaxf(mx, S.o[o][x]);
-        }
+      for (int j = 0; j <= kPer; j++) {
+        mn = stay[j] ? fminf(mn, v[j][o]) : mn;
+        mx = stay[j] ? fmaxf(mx, v[j][o]) : mx;
       }
-      lo[o] = block_min(S, mn);
-      hi[o] = block_max(S, mx);
+      const double lo = block_min(S, mn), hi = block_max(S, mx);
+#pragma unroll
+      for (int j = 0; j <= kPer; j++) at[j][o] = hi > lo ? (static_cast<double>(v[j][o]) - lo) / (hi - lo) : 0.0;
     }
-    const int n2 = pow2_at_least(N);
     int a = 1, b = cap < kMaxLevels ? cap : kMaxLevels;
-    // the last pass (a == b) sorts at the chosen resolution
+    // the last pass (a == b) takes the boxes' earliest candidates
     for (;;) {
       const int L = a < b ? (a + b + 1) / 2 : a;
-      for (int x = t; x < n2; x += kThreads) S.sortbuf[x] = ~0ull;
-      __syncthreads();
 #pragma unroll
-      for (int j = 0; j < kPer; j++) {
-        const int x = t + j * kThreads;
-        if (x < N && stay[j]) {
-          const uint32_t key = static_cast<uint32_t>(box_of(S.o[0][x], lo[0], hi[0], L)) |
-                               static_cast<uint32_t>(box_of(S.o[1][x], lo[1], hi[1], L)) << 10 |
-                               static_cast<uint32_t>(box_of(S.o[2][x], lo[2], hi[2], L)) << 20;
-          S.sortbuf[x] = static_cast<uint64_t>(key) << 32 | static_cast<uint32_t>(x);
-        }
+      for (int q = 0; q < kTable / kThreads; q++) {
+        S.key[t + q * kThreads] = kNoKey;
+        S.order[t + q * kThreads] = 0xffffffffu;
       }
       __syncthreads();
-      bitonic_sort(S.sortbuf, n2);
-      int n_first_mine = 0;
-      for (int i = t; i < n2; i += kThreads) {
-        const uint64_t v = S.sortbuf[i];
-        const bool first = v != ~0ull && (i == 0 || (S.sortbuf[i - 1] >> 32) != (v >> 32));
-        n_first_mine += first ? 1 : 0;
+      int fresh = 0, entry[kPer + 1];
+#pragma unroll
+      for (int j = 0; j <= kPer; j++) {
+        entry[j] = 0;
+        if (!stay[j]) continue;
+        const uint32_t key = static_cast<uint32_t>(box_of(at[j][0], L)) |
+                             static_cast<uint32_t>(box_of(at[j][1], L)) << 10 |
+                             static_cast<uint32_t>(box_of(at[j][2], L)) << 20;
+        entry[j] = table_entry(S, key, &fresh);
+        if (a == b) atomicMin(&S.order[entry[j]], order[j]);
       }
       int cnt;
-      block_excl(S, n_first_mine, &cnt);    // its barriers also end the key reads
-      if (a == b) break;
+      block_excl(S, fresh, &cnt);    // its barriers also end the table's use
+      if (a == b) {
+        levels = a;
+        n_mine = 0;
+#pragma unroll
+        for (int j = 0; j <= kPer; j++) {
+          stay[j] = stay[j] && S.order[entry[j]] == order[j];
+          n_mine += stay[j] ? 1 : 0;
+        }
+        break;
+      }
       if (cnt <= cap) a = L;
       else b = L - 1;
     }
-    levels = a;
-    // keep the first candidate of each box
-    for (int x = t; x < N; x += kThreads) S.flag[x] = 0;
-    __syncthreads();
-    for (int i = t; i < n2; i += kThreads) {
-      const uint64_t v = S.sortbuf[i];
-      if (v != ~0ull && (i == 0 || (S.sortbuf[i - 1] >> 32) != (v >> 32)))
-        S.flag[static_cast<uint32_t>(v)] = 1;
-    }
-    __syncthreads();
-    n_stay_mine = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; j++) {
-      const int x = t + j * kThreads;
-      stay[j] = stay[j] && S.flag[x] != 0;
-      n_stay_mine += stay[j] ? 1 : 0;
-    }
-    block_excl(S, n_stay_mine, &n_stay);
+    block_excl(S, n_mine, &n_stay);
   }
-  // ---- slots: occupancy after the update (low words of sortbuf)
-  uint32_t* occ = reinterpret_cast<uint32_t*>(S.sortbuf);
-  for (int s = t; s < cap; s += kThreads) occ[s] = 0u;
-  __syncthreads();
+  // ---- members that do not stay free their slots; the free slots in order
+  int n_free = 0;
 #pragma unroll
   for (int j = 0; j < kPer; j++) {
-    const int x = t + j * kThreads;
-    if (x >= N) continue;
-    const int src = S.src[x];
-    if (src >= 0) {
-      if (stay[j]) {
-        occ[src] = 1u;
-      } else {
-        arc_stamp[src] = -1;
-        arc_obj[3 * src] = INFINITY;
-        arc_obj[3 * src + 1] = INFINITY;
-        arc_obj[3 * src + 2] = INFINITY;
-      }
+    const int s = t + j * kThreads;
+    if (held[j] && !stay[j]) {
+      arc_stamp[s] = -1;
+      arc_obj[3 * s] = INFINITY;
+      arc_obj[3 * s + 1] = INFINITY;
+      arc_obj[3 * s + 2] = INFINITY;
     }
-  }
-  __syncthreads();
-  // free slots in ascending order: thread t scans slots 4t .. 4t + 3
-  {
-    int fr[kPer], nf = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; j++) {
-      const int s = kPer * t + j;
-      fr[j] = (s < cap && occ[s] == 0u) ? 1 : 0;
-      nf += fr[j];
-    }
-    int total;
-    int pos = block_excl(S, nf, &total);
-#pragma unroll
-    for (int j = 0; j < kPer; j++)
-      if (fr[j]) S.flag[pos++] = kPer * t + j;
-  }
-  // staying offers take the free slots in candidate order (x = t + j * 1024,
-  // so one pass per j, each ranked by a block prefix)
-  if (t < n_off) {
-    inserted[t] = 0;
-    slot_of[t] = -1;
-  }
-  __syncthreads();
-  const int next = arc_state[1];
-  int base = 0;
-#pragma unroll
-  for (int j = 0; j < kPer; j++) {
-    const int x = t + j * kThreads;
-    const bool nw = x < N && stay[j] && S.src[x] < 0;
+    if (j * kThreads >= cap) continue;          // uniform: no slots in this pass
+    const bool is_free = s < cap && !stay[j];
     int cnt;
-    const int r = base + block_excl(S, nw ? 1 : 0, &cnt);
-    if (nw) {
-      const int s = S.flag[r];
-      const int i = -1 - S.src[x];
-      arc_obj[3 * s] = S.o[0][x];
-      arc_obj[3 * s + 1] = S.o[1][x];
-      arc_obj[3 * s + 2] = S.o[2][x];
-      arc_stamp[s] = next + r;
-      inserted[i] = 1;
-      slot_of[i] = s;
+    const int r = n_free + block_excl(S, is_free ? 1 : 0, &cnt);
+    if (is_free) S.free_slot[r] = s;
+    n_free += cnt;
+  }
+  // ---- staying offers take them in index order
+  int n_new;
+  const int r = block_excl(S, stay[kPer] ? 1 : 0, &n_new);   // its barriers publish the free slots
+  if (t < n_off) {
+    int slot = -1;
+    if (stay[kPer]) {
+      slot = S.free_slot[r];
+      arc_obj[3 * slot] = v[kPer][0];
+      arc_obj[3 * slot + 1] = v[kPer][1];
+      arc_obj[3 * slot + 2] = v[kPer][2];
+      arc_stamp[slot] = next + r;
     }
-    base += cnt;
+    inserted[t] = stay[kPer] ? 1 : 0;
+    slot_of[t] = slot;
   }
   // best guidance among the members after the update
   float g = INFINITY;
 #pragma unroll
-  for (int j = 0; j < kPer; j++) {
-    const int x = t + j * kThreads;
-    if (x < N && stay[j]) g = fminf(g, S.o[2][x]);
-  }
+  for (int j = 0; j <= kPer; j++) g = stay[j] ? fminf(g, v[j][2]) : g;
   g = block_min(S, g);
   if (t == 0) {
     arc_state[0] = n_stay;
-    arc_state[1] = next + base;
+    arc_state[1] = next + n_new;
     arc_state[2] = levels;
     arc_state[3] = 0;
     best_out[0] = g;
@@ -479,9 +459,11 @@ extern "C" morea_status morea_archive_update(int32_t n_offers, const float* offe
   if (morea_status st = arc_pending()) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // slot_of is needed by the point copy even when the caller does not want it
-  hipLaunchKernelGGL(archive::k_update, dim3(1), dim3(archive::kThreads), 0, s, n_offers, offer_obj, offer_flags,
-                     offer_sev, guidance_max, capacity, arc_obj, arc_stamp, arc_state, best_guidance, inserted,
-                     slot_of);
+  const archive::Offers offers{offer_obj, offer_flags, offer_sev, n_offers};
+  hipLaunchKernelGGL(archive::k_dominate, dim3((capacity + n_offers + 3) / 4), dim3(256), 0, s, offers, guidance_max,
+                     capacity, arc_obj, arc_stamp, inserted);
+  hipLaunchKernelGGL(archive::k_update, dim3(1), dim3(archive::kThreads), 0, s, n_offers, offer_obj, capacity,
+                     arc_obj, arc_stamp, arc_state, best_guidance, inserted, slot_of);
   if (morea_status st = arc_launched("archive update kernel")) return st;
   if (arc_pts && n_offers > 0) {
     hipLaunchKernelGGL(archive::k_copy_points, dim3(n_offers), dim3(256), 0, s, n_offers, 6 * n_points, offer_pts,
