@@ -523,8 +523,10 @@ morea_status morea_debug_distance_map(morea_problem *p, int32_t image, int32_t s
  * waves beyond the actual item count returning at once) on the given inputs
  * with HIP events and keeps the fastest for later morea_eval_partial calls.
  * Synchronous; overwrites the output arrays.  *best_ms (may be NULL) receives
- * the best time.  Untuned, the shape is 4 persistent blocks per compute unit
- * (at most the occupancy limit) and 8 items per pop.  Errors as
+ * the best time.  Untuned, every call takes the grid form unless its bound is
+ * far above the items, and else 4 persistent blocks per compute unit (at most
+ * the occupancy limit) and 8 items per pop, the shape that
+ * morea_partial_shape reports until one is tuned or set.  Errors as
  * morea_eval_partial. */
 morea_status morea_tune_partial(morea_problem *p, const float *parent_pts, int32_t n_parents,
                                 const void *parent_cache, int32_t n_evals,

@@ -87,8 +87,8 @@ void ensure_partial_shape(morea_problem* p) {
   int cus = 0, per_cu = 0;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
   per_cu = partial_blocks_per_cu(p->storage);
-  // the tuner's choice on the 128x128x96 workloads: 4 blocks per compute
-  // unit (at most the occupancy limit), 8 items per queue pop
+  // the best persistent shape on the 128x128x96 workloads: 4 blocks per
+  // compute unit (at most the occupancy limit), 8 items per queue pop
   p->partial_blocks = std::max(1, cus) * std::max(1, std::min(4, per_cu));
   p->partial_chunk = 8;
 }
@@ -497,6 +497,7 @@ morea_status morea_set_groups(morea_problem* p, int32_t n_groups, const int32_t*
   }
   p->n_groups = n_groups;
   p->max_dep = max_dep;
+  p->mean_dep = (dep_off[n_groups] + n_groups - 1) / n_groups;
   p->max_group = max_group;
   return MOREA_OK;
 }
@@ -580,13 +581,27 @@ static hipError_t partial_launch(morea_problem* p, const float* parent_pts, int3
   const Record* prec = static_cast<const Record*>(parent_cache);
   const Totals* ptot = reinterpret_cast<const Totals*>(
       static_cast<const char*>(parent_cache) + static_cast<size_t>(n_parents) * p->view.n_tets * 2 * sizeof(Record));
-  if (chunk == 0) {   // grid form: one wave per item pair up to the bound n_evals x max_dep
+  int per_wave = 2;
+  if (chunk == 0) {   // grid form: waves up to the bound n_evals x max_dep of the item count
     const long long bound = static_cast<long long>(n_evals) * std::max(p->max_dep, 1);
-    blocks = static_cast<int>(std::min<long long>((bound + 7) / 8, 0x7fffffffLL));
+    per_wave = items_per_wave(p->view, static_cast<long long>(n_evals) * p->mean_dep);
+    blocks = static_cast<int>(std::min<long long>((bound + 4 * per_wave - 1) / (4 * per_wave), 0x7fffffffLL));
   }
   return launch_partial(p->view, p->storage, I, n_parents, p->n_groups, prec, ptot,
-                        p->d_partial_records, p->d_queue, blocks, chunk, obj, flags, severity,
+                        p->d_partial_records, p->d_queue, blocks, chunk, per_wave, obj, flags, severity,
                         counts, s);
+}
+
+// Shape of a call without a tuned or set one: the grid form, which launches
+// waves for n_evals x the largest dependent-tet list (128x128x96, 512 x 64
+// groups: 37.8 ms, 4 persistent blocks per compute unit with 8 items per pop
+// 40.5; 32^3, 16 x 8 groups: 55 us against 154, where a wave takes its 8
+// items one after the other).  The waves beyond the items return at once:
+// 21 million of them cost 0.3 ms beside 0.36 million items in 5.9 ms (6.7 ms
+// persistent), so the forms meet where the bound is about 150 times the items;
+// the line is at 64, and where a launch would exceed 2^32 threads.
+static bool grid_bound_ok(const morea_problem* p, int32_t n_evals) {
+  return p->max_dep <= 64 * p->mean_dep && static_cast<long long>(n_evals) * p->max_dep <= (1LL << 26);
 }
 
 morea_status morea_eval_partial(morea_problem* p, const float* parent_pts, int32_t n_parents,
@@ -603,7 +618,9 @@ morea_status morea_eval_partial(morea_problem* p, const float* parent_pts, int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const void* key[9] = {parent_pts, parent_cache, eval_parent, eval_group, new_coords, obj, flags,
                         severity, counts};
-  const int key_n[4] = {n_parents, n_evals, p->partial_blocks, p->partial_chunk};
+  const bool grid = !p->partial_chosen && grid_bound_ok(p, n_evals);
+  const int use_blocks = grid ? 0 : p->partial_blocks, use_chunk = grid ? 0 : p->partial_chunk;
+  const int key_n[4] = {n_parents, n_evals, use_blocks, use_chunk};
   morea_problem::GraphSlot* slot = nullptr;
   for (auto& g : p->graphs)
     if (g.exec && memcmp(key, g.key, sizeof(key)) == 0 && memcmp(key_n, g.key_n, sizeof(key_n)) == 0) slot = &g;
@@ -621,7 +638,7 @@ morea_status morea_eval_partial(morea_problem* p, const float* parent_pts, int32
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     hipError_t le = partial_launch(p, parent_pts, n_parents, parent_cache, n_evals, eval_parent,
                                    eval_group, new_coords, obj, flags, severity, counts,
-                                   p->partial_blocks, p->partial_chunk, p->capture_stream);
+                                   use_blocks, use_chunk, p->capture_stream);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(p->capture_stream, &g);
     if (le != hipSuccess) {
@@ -704,6 +721,7 @@ morea_status morea_tune_partial(morea_problem* p, const float* parent_pts, int32
   (void)hipEventDestroy(b);
   p->partial_blocks = best_blocks;
   p->partial_chunk = best_chunk;
+  p->partial_chosen = true;
   drop_graph(p);
   if (best_ms) *best_ms = best / 2.0f;
   return MOREA_OK;
@@ -725,6 +743,7 @@ morea_status morea_set_partial_shape(morea_problem* p, int32_t blocks, int32_t c
   if (p->partial_blocks != blocks || p->partial_chunk != chunk) drop_graph(p);
   p->partial_blocks = blocks;
   p->partial_chunk = chunk;
+  p->partial_chosen = true;
   return MOREA_OK;
 }
 

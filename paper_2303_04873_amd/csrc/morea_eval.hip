@@ -1228,7 +1228,7 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 
 // Full evaluation: one wave per two (candidate, tet) items, item = tet * pop
 // + candidate, so the 4 waves of a block take 8 consecutive candidates of one
-// tet (fewer at a tet boundary).
+// tet (fewer at a tet boundary); or one per wave (items_per_wave).
 __device__ __forceinline__ void split_item(const FullItems& F, int item, int& tet, int& cand) {
   // item = tet * pop + cand, split with the reciprocal (wave-uniform values)
   tet = static_cast<int>(static_cast<double>(item) * F.inv_pop);
@@ -1246,12 +1246,12 @@ __device__ __forceinline__ void split_item(const FullItems& F, int item, int& te
 
 template <int ST>
 __global__ __launch_bounds__(256, 5) void k_eval_full(ProblemView P, FullItems F, Record* rec,
-                                                    int n_items) {
+                                                    int n_items, int per_wave) {
   __shared__ WaveLds lds[4];
   const int wave = uniform_i(static_cast<int>(threadIdx.x >> 6));
-  const int item0 = 2 * (xcd_block(blockIdx.x, gridDim.x) * 4 + wave);
+  const int item0 = per_wave * (xcd_block(blockIdx.x, gridDim.x) * 4 + wave);
   if (item0 >= n_items) return;
-  const bool has1 = item0 + 1 < n_items;
+  const bool has1 = per_wave == 2 && item0 + 1 < n_items;
   int tet0, cand0, tet1 = 0, cand1 = 0;
   split_item(F, item0, tet0, cand0);
   if (has1) split_item(F, item0 + 1, tet1, cand1);
@@ -1270,9 +1270,9 @@ __global__ __launch_bounds__(256, 5) void k_eval_full(ProblemView P, FullItems F
                &rec[(static_cast<size_t>(cand1) * P.n_tets + tet1) * 2]);
 }
 
-template __global__ void k_eval_full<kF32>(ProblemView, FullItems, Record*, int);
-template __global__ void k_eval_full<kBF16>(ProblemView, FullItems, Record*, int);
-template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int);
+template __global__ void k_eval_full<kF32>(ProblemView, FullItems, Record*, int, int);
+template __global__ void k_eval_full<kBF16>(ProblemView, FullItems, Record*, int, int);
+template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int, int);
 
 // Per-candidate reduction over all tets in a fixed order, with compensated
 // sums; writes the objective vector, flags, severity, counts and (when
@@ -1401,21 +1401,35 @@ hipError_t launch_distance_maps(int nx, int ny, int nz, int n_sets, const int* s
   return hipGetLastError();
 }
 
+// Items that one wave evaluates.  Two share the set-up (one per half-wave) and
+// then take turns, which issues least; one per wave is the shorter chain and
+// wins while the chip is not full, the longer the larger the tets.  One
+// against two per wave, full evaluation in us: tets of 85 voxels 20.6 : 27.0
+// at 384 items, 26.5 : 29.7 at 4,608, 37.6 : 36.0 at 6,144; of 350 voxels
+// 55.7 : 58.9 at 6,000, 81 : 95 at 12,000, 110 : 115 at 18,000; of 480 voxels
+// 153 : 170 at 17,500.  5,120 waves are resident (five on a SIMD).
+int items_per_wave(const ProblemView& P, long long n_items) {
+  const long long voxels = static_cast<long long>(P.nx) * P.ny * P.nz;
+  const bool large = voxels / P.n_tets >= 256;
+  return n_items <= (large ? 20480 : 5120) ? 1 : 2;
+}
+
 hipError_t launch_eval_full(const ProblemView& P, int storage, const float* pts, int pop,
                             Record* rec, hipStream_t s) {
   const size_t n_items = static_cast<size_t>(pop) * P.n_tets;
   if (n_items == 0) return hipSuccess;
-  const int blocks = static_cast<int>((n_items + 7) / 8);
+  const int per_wave = items_per_wave(P, static_cast<long long>(n_items));
+  const int blocks = static_cast<int>((n_items + 4 * per_wave - 1) / (4 * per_wave));
   FullItems F{pts, pop, 1.0 / pop};
   switch (storage) {
     case kF32:
-      hipLaunchKernelGGL(k_eval_full<kF32>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items);
+      hipLaunchKernelGGL(k_eval_full<kF32>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items, per_wave);
       break;
     case kBF16:
-      hipLaunchKernelGGL(k_eval_full<kBF16>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items);
+      hipLaunchKernelGGL(k_eval_full<kBF16>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items, per_wave);
       break;
     default:
-      hipLaunchKernelGGL(k_eval_full<kF16>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items);
+      hipLaunchKernelGGL(k_eval_full<kF16>, dim3(blocks), dim3(256), 0, s, P, F, rec, (int)n_items, per_wave);
       break;
   }
   return hipGetLastError();
@@ -1551,6 +1565,67 @@ __global__ __launch_bounds__(1024) void k_prep_groups(PartialItems I, int n_grou
   }
 }
 
+// The four launches as one block, for lists of at most 1,024 evaluations: a
+// launch costs 4.5 us there and its work less (32^3, 16 x 8 groups: 55 us a
+// call with four, XX with one).
+constexpr int kPrepSmall = 1024;
+
+// Exclusive prefix sums of a pair over the block; totals to every thread.
+__device__ void prep_scan2(int (*s_wave)[kPrepSmall / kWave], int& a, int& b, int& total_a, int& total_b) {
+  const int w = threadIdx.x >> 6;
+  const int xa = wave_excl_scan(a), xb = wave_excl_scan(b);
+  if ((threadIdx.x & 63) == 63) {
+    s_wave[0][w] = xa + a;
+    s_wave[1][w] = xb + b;
+  }
+  __syncthreads();
+  int ba = 0, bb = 0;
+  total_a = total_b = 0;
+#pragma unroll
+  for (int k = 0; k < kPrepSmall / kWave; k++) {
+    ba += k < w ? s_wave[0][k] : 0;
+    bb += k < w ? s_wave[1][k] : 0;
+    total_a += s_wave[0][k];
+    total_b += s_wave[1][k];
+  }
+  __syncthreads();
+  a = ba + xa;
+  b = bb + xb;
+}
+
+__global__ __launch_bounds__(kPrepSmall) void k_prep_small(PartialItems I, int n_parents, int n_groups, int* queue) {
+  __shared__ int s_wave[2][kPrepSmall / kWave];
+  const int e = threadIdx.x;
+  for (int g = e; g < n_groups; g += kPrepSmall) I.grp_count[g] = 0;
+  int rows = 0, items = 0, all_rows, all_items;
+  if (e < I.n_evals) eval_sizes(I, e, n_parents, n_groups, rows, items);
+  prep_scan2(s_wave, rows, items, all_rows, all_items);   // its barriers order the counters' clearing
+  if (e < I.n_evals) {
+    const_cast<int*>(I.row_off)[e] = rows;
+    const_cast<int*>(I.item_off)[e] = items;
+    const int g = I.eval_group[e], par = I.eval_parent[e];
+    if (g >= 0 && g < n_groups && par >= 0 && par < n_parents) I.eval_rank[e] = atomicAdd(&I.grp_count[g], 1);
+  }
+  if (e == 0) {
+    const_cast<int*>(I.item_off)[I.n_evals] = all_items;
+    *queue = 0;
+  }
+  __threadfence();
+  __syncthreads();
+  int carry = 0;
+  for (int g0 = 0; g0 < n_groups; g0 += kPrepSmall) {
+    const int g = g0 + e;
+    int v = 0, unused = 0, sum, none;
+    // the counters are where the atomics left them, in L2
+    if (g < n_groups)
+      v = __hip_atomic_load(&I.grp_count[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) *
+          (I.dep_off[g + 1] - I.dep_off[g]);
+    prep_scan2(s_wave, v, unused, sum, none);
+    if (g < n_groups) I.grp_base[g] = carry + v;
+    carry += sum;
+  }
+}
+
 // Per-item records of the partial launch, one wave per evaluation: for
 // dependent tet j of evaluation e (rank r in its group g of c evaluations)
 // the processing position is grp_base[g] + j c + r; the record there names
@@ -1630,20 +1705,21 @@ __global__ __launch_bounds__(256, 4) void k_eval_partial(ProblemView P, PartialI
   }
 }
 
-// Grid form: wave w evaluates items 2 w and 2 w + 1 (in processing order);
-// the grid covers a bound of the item count known on the host, and the
-// waves beyond the actual count return at once.  Without the persistent
+// Grid form: wave w evaluates items 2 w and 2 w + 1 (in processing order), or
+// item w; the grid covers a bound of the item count known on the host, and
+// the waves beyond the actual count return at once.  Without the persistent
 // loop the kernel fits five waves per SIMD.
 template <int ST>
-__global__ __launch_bounds__(256, 5) void k_eval_partial_grid(ProblemView P, PartialItems I, Record* out) {
+__global__ __launch_bounds__(256, 5) void k_eval_partial_grid(ProblemView P, PartialItems I, Record* out,
+                                                              int per_wave) {
   __shared__ WaveLds lds[4];
   const int wave = uniform_i(static_cast<int>(threadIdx.x >> 6));
   const int lane = lane_id();
   const int total = I.item_off[I.n_evals];
-  const long long idx_l = 2 * (static_cast<long long>(blockIdx.x) * 4 + wave);
+  const long long idx_l = per_wave * (static_cast<long long>(blockIdx.x) * 4 + wave);
   if (idx_l >= total) return;
   const int idx = static_cast<int>(idx_l);
-  const bool has1 = idx + 1 < total;
+  const bool has1 = per_wave == 2 && idx + 1 < total;
   const int4 it0 = I.item_info[idx];
   const int4 it1 = has1 ? I.item_info[idx + 1] : it0;
   const int tet0 = uniform_i(it0.y), tet1 = uniform_i(it1.y);
@@ -1657,9 +1733,9 @@ __global__ __launch_bounds__(256, 5) void k_eval_partial_grid(ProblemView P, Par
 template __global__ void k_eval_partial<kF32>(ProblemView, PartialItems, Record*, int*, int);
 template __global__ void k_eval_partial<kBF16>(ProblemView, PartialItems, Record*, int*, int);
 template __global__ void k_eval_partial<kF16>(ProblemView, PartialItems, Record*, int*, int);
-template __global__ void k_eval_partial_grid<kF32>(ProblemView, PartialItems, Record*);
-template __global__ void k_eval_partial_grid<kBF16>(ProblemView, PartialItems, Record*);
-template __global__ void k_eval_partial_grid<kF16>(ProblemView, PartialItems, Record*);
+template __global__ void k_eval_partial_grid<kF32>(ProblemView, PartialItems, Record*, int);
+template __global__ void k_eval_partial_grid<kBF16>(ProblemView, PartialItems, Record*, int);
+template __global__ void k_eval_partial_grid<kF16>(ProblemView, PartialItems, Record*, int);
 
 __device__ __forceinline__ void df_wave_sum(float& hi, float& lo) {
 #pragma unroll
@@ -1761,20 +1837,24 @@ namespace morea {
 
 hipError_t launch_partial(const ProblemView& P, int storage, const PartialItems& I, int n_parents,
                           int n_groups, const Record* parent_rec, const Totals* parent_tot,
-                          Record* new_rec, int* queue, int blocks, int chunk, float* obj,
+                          Record* new_rec, int* queue, int blocks, int chunk, int per_wave, float* obj,
                           uint8_t* flags, float* severity, uint32_t* counts, hipStream_t s) {
   if (I.n_evals == 0) return hipSuccess;
   const int prep_blocks = (I.n_evals + kPrepBlock - 1) / kPrepBlock;
-  hipLaunchKernelGGL(k_prep_local, dim3(prep_blocks), dim3(kPrepBlock), 0, s, I, n_parents, n_groups);
-  hipLaunchKernelGGL(k_prep_blocks, dim3(1), dim3(1024), 0, s, I, prep_blocks, n_groups, queue);
-  hipLaunchKernelGGL(k_prep_offsets, dim3(prep_blocks), dim3(kPrepBlock), 0, s, I, n_parents, n_groups);
-  hipLaunchKernelGGL(k_prep_groups, dim3(1), dim3(1024), 0, s, I, n_groups);
+  if (I.n_evals <= kPrepSmall) {
+    hipLaunchKernelGGL(k_prep_small, dim3(1), dim3(kPrepSmall), 0, s, I, n_parents, n_groups, queue);
+  } else {
+    hipLaunchKernelGGL(k_prep_local, dim3(prep_blocks), dim3(kPrepBlock), 0, s, I, n_parents, n_groups);
+    hipLaunchKernelGGL(k_prep_blocks, dim3(1), dim3(1024), 0, s, I, prep_blocks, n_groups, queue);
+    hipLaunchKernelGGL(k_prep_offsets, dim3(prep_blocks), dim3(kPrepBlock), 0, s, I, n_parents, n_groups);
+    hipLaunchKernelGGL(k_prep_groups, dim3(1), dim3(1024), 0, s, I, n_groups);
+  }
   hipLaunchKernelGGL(k_partial_items, dim3((I.n_evals + 3) / 4), dim3(256), 0, s, I, n_parents, n_groups);
   if (chunk == 0) {   // grid form: `blocks` covers the bound of the item count
     switch (storage) {
-      case kF32: hipLaunchKernelGGL(k_eval_partial_grid<kF32>, dim3(blocks), dim3(256), 0, s, P, I, new_rec); break;
-      case kBF16: hipLaunchKernelGGL(k_eval_partial_grid<kBF16>, dim3(blocks), dim3(256), 0, s, P, I, new_rec); break;
-      default: hipLaunchKernelGGL(k_eval_partial_grid<kF16>, dim3(blocks), dim3(256), 0, s, P, I, new_rec); break;
+      case kF32: hipLaunchKernelGGL(k_eval_partial_grid<kF32>, dim3(blocks), dim3(256), 0, s, P, I, new_rec, per_wave); break;
+      case kBF16: hipLaunchKernelGGL(k_eval_partial_grid<kBF16>, dim3(blocks), dim3(256), 0, s, P, I, new_rec, per_wave); break;
+      default: hipLaunchKernelGGL(k_eval_partial_grid<kF16>, dim3(blocks), dim3(256), 0, s, P, I, new_rec, per_wave); break;
     }
   } else {
     switch (storage) {

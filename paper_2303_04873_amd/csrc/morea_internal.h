@@ -159,6 +159,8 @@ struct morea_problem {
   // autotuned persistent launch shape
   int partial_blocks = 0;    // persistent blocks, or 0 with partial_chunk 0: the grid form
   int partial_chunk = -1;    // items per queue pop; -1 until a shape is chosen
+  bool partial_chosen = false;   // the shape was tuned or set (else each call's sizes decide)
+  int mean_dep = 0;              // dependent tets of a group, on average (rounded up)
   // captured partial-evaluation graphs, each with the arguments it bakes in;
   // a call whose arguments match an entry replays it, otherwise the least
   // recently used entry is replaced (a generation alternates one argument set
@@ -200,6 +202,7 @@ morea_status static_scratch_init(int device);
 void ensure_partial_shape(morea_problem* p);   // untuned persistent launch shape, once
 hipError_t launch_partial(const ProblemView& P, int storage, const PartialItems& I, int n_parents,
                           int n_groups, const Record* parent_rec, const Totals* parent_tot,
-                          Record* new_rec, int* queue, int blocks, int chunk, float* obj,
+                          Record* new_rec, int* queue, int blocks, int chunk, int per_wave, float* obj,
                           uint8_t* flags, float* severity, uint32_t* counts, hipStream_t s);
+int items_per_wave(const ProblemView& P, long long n_items);   // 1 or 2
 }  // namespace morea
