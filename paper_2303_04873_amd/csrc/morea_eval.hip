@@ -45,9 +45,10 @@ __device__ __forceinline__ float ld_img(const void* base, int idx) {
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
-__device__ __forceinline__ int bits_below(uint64_t m) {
+// `from` plus the set bits of m below this lane.
+__device__ __forceinline__ int bits_below(uint64_t m, int from = 0) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), from));
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -72,12 +73,25 @@ __device__ __forceinline__ int wave_excl_scan(int v) {
   return x - v;
 }
 
-// Butterfly sum: every lane ends with the same value, in a fixed order.
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+// Sum over the wave, complete in lane 63: within rows of 16 lanes by DPP
+// shifts, then across rows by the broadcasts of lanes 15 and 31 (6 VALU
+// instructions; shuffles would be 6 LDS round trips), in a fixed order.
+template <int ctrl, int rows>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, false));
+}
+
+__device__ __forceinline__ float wave_sum_63(float v) {
+  v += dpp_f<0x111, 0xf>(v);
+  v += dpp_f<0x112, 0xf>(v);
+  v += dpp_f<0x114, 0xf>(v);
+  v += dpp_f<0x118, 0xf>(v);
+  v += dpp_f<0x142, 0xa>(v);
+  v += dpp_f<0x143, 0xc>(v);
   return v;
 }
+
+__device__ __forceinline__ int wave_sum_63i(int v) { return wave_excl_scan(v) + v; }
 
 __device__ __forceinline__ int wave_sum_i(int v) {
 #pragma unroll
@@ -92,11 +106,6 @@ __device__ __forceinline__ double rcp64(double x) {
   r = fma(fma(-x, r, 1.0), r, r);
   r = fma(fma(-x, r, 1.0), r, r);
   return r;
-}
-
-__device__ __forceinline__ int64_t floor_div_pos(int64_t a, int64_t b) {  // b > 0
-  int64_t q = a / b;
-  return (q * b > a) ? q - 1 : q;
 }
 
 // Two consecutive floats read by one 8-byte load at 4-byte alignment.
@@ -138,23 +147,22 @@ struct DirConst {
     };
   };
   double invA[4];
-  // x position of face i's plane on row (yr, zr): t_i = TA yr + TB zr + TG
-  // (= -(PY yr + PZ zr + B0) / A); for a face with A = 0 the same three
-  // numbers hold PY, PZ, B0 (so "t" is the face value itself).  TE bounds the
-  // FP64 error of t.
-  double TA[4], TB[4], TG[4], TE[4];
-  int kind[4];                                 // sign of A_i
+  // x position of face i's plane on row (yr, zr): t_i = T.x yr + T.y zr + T.z
+  // (= -(PY yr + PZ zr + B0) / A) in FP32, T.w a bound of its error
+  float4 T[4];
+  int kind[4];                                 // sign of A_i, doubled where FP32 cannot place the crossing
   int lex[4];                                  // tie-break bit of face i
   double M[3][3];
   double qlo[3];
   double gthr[3];                              // 0.5 - FP64 error bound of q: near-grid iff |frac(q) - 0.5| >= gthr
-  float thr_f[3];                              // the same test on the FP32 fraction (wider margin)
+  float thr_f[3];                              // near-grid margin of the FP32 fraction (wider)
   int64_t absD;
   int fast;                                    // extent <= 2^16: FP64 plane arithmetic
   int sigma;                                   // orientation sign of the rasterized tet
   // bounding box of the rasterized tet on its grid and the row count
   int lo[3], hi[3];
-  int W, NYb, R;                               // box width - 1, rows per slice, rows
+  int vbase;                                   // padded element of the box corner
+  int W, NYb;                                  // box width - 1, rows per slice
   int active;                                  // the direction has voxels to visit
   int inner;                                   // mapped points stay inside the padded volume
   // the direction's record, completed by the sample loop
@@ -259,47 +267,45 @@ __device__ __forceinline__ bool exact_foreground(const ProblemView& P, const voi
 // x-interval [js, je] (relative to the box start, within [0, W]) of row
 // (yr, zr) of one direction, for tets with extent <= 2^16 (exact FP64 plane
 // values).  Face i with kind != 0 crosses zero at the box-relative x position
-// t_i = TA yr + TB zr + TG.  The first voxel inside a face with kind > 0 is
-// floor(t) + 1 and the last inside a face with kind < 0 is ceil(t) - 1 (a
-// centre on the plane is outside once the tie-break bit is folded in), unless
-// t is within its FP64 error bound TE of an integer r: then the exact plane
-// value at r decides between r and its neighbour.  Branch-free per face.
+// t_i = T.x yr + T.y zr + T.z, in FP32.  With r the integer nearest to t, the
+// sign of t - r says whether the voxel at r is inside the face, hence whether
+// the interval starts (kind > 0) or ends (kind < 0) at r or next to it; where
+// t is within its error bound T.w of r the exact plane value at r decides (a
+// centre on the plane is outside once the tie-break bit is folded in).  The
+// orientation is the same for the whole wave (one item and direction): scalar
+// branches, about 10 instructions a face (23 in FP64, whose exactness only
+// the rare rows near an integer need).  A face whose bound reaches 1/4 voxel
+// (one nearly parallel to x) is solved from its exact values.
 __device__ __forceinline__ void row_span_fast(const DirConst& c, int yr, int zr, int W, int& js, int& je) {
   js = 0;
   je = W;
-  const double y = yr, z = zr;
-  bool empty = false;
+  const float y = static_cast<float>(yr), z = static_cast<float>(zr), top = static_cast<float>(W) + 1.5f;
 #pragma unroll
   for (int i = 0; i < 4; i++) {
-    // the face's orientation is the same for the whole wave (one item and
-    // direction): scalar branches, one rounding path per face
     const int kind = uniform_i(c.kind[i]);
-    const double t = fma(c.TA[i], y, fma(c.TB[i], z, c.TG[i]));
-    if (kind == 0) {
-      // face parallel to x: t holds the plane value itself
-      empty = empty || !(t > 0.0);
-      continue;
-    }
-    // a crossing beyond [-2, W + 1] leaves the row full or empty either way:
-    // floor / ceil of the clamped value decide it without the exact test
-    const double tc = fmin(fmax(t, -2.0), W + 1.0);
-    const double r = rint(tc);
-    const bool near = tc == t && fabs(tc - r) <= c.TE[i];
-    int j = kind > 0 ? static_cast<int>(floor(tc)) + 1 : static_cast<int>(ceil(tc)) - 1;
-    if (__ballot(near)) {
-      // rare: the exact plane value (+ tie-break bit) at x = r decides;
-      // |terms| < 2^50
-      const double e = fma(c.A[i], r, fma(c.PY[i], y, fma(c.PZ[i], z, c.B0[i])));
+    if (kind == 1 || kind == -1) {
+      const float4 T = c.T[i];
+      // beyond [-1.5, W + 1.5] a crossing leaves the row full or empty
+      const float t = __builtin_amdgcn_fmed3f(fmaf(T.x, y, fmaf(T.y, z, T.z)), -1.5f, top);
+      const float r = rintf(t), d = t - r;
       const int ri = static_cast<int>(r);
-      const int jx = kind > 0 ? (e > 0.0 ? ri : ri + 1) : (e > 0.0 ? ri : ri - 1);
-      j = near ? jx : j;
+      bool in = kind > 0 ? d < 0.f : d > 0.f;
+      const bool near = fabsf(d) <= T.w;
+      if (__ballot(near)) {
+        // rare: the exact plane value (+ tie-break bit) at x = r; |terms| < 2^50
+        const double e = fma(c.A[i], static_cast<double>(r), fma(c.PY[i], static_cast<double>(yr),
+                                                                 fma(c.PZ[i], static_cast<double>(zr), c.B0[i])));
+        in = near ? e > 0.0 : in;
+      }
+      if (kind > 0)
+        js = max(js, in ? ri : ri + 1);
+      else
+        je = min(je, in ? ri : ri - 1);
+    } else {
+      const double b = fma(c.PY[i], static_cast<double>(yr), fma(c.PZ[i], static_cast<double>(zr), c.B0[i]));
+      clip_face<double>(kind, c.A[i], c.invA[i], b, W, js, je);
     }
-    if (kind > 0)
-      js = max(js, j);
-    else
-      je = min(je, j);
   }
-  if (empty) je = -1;
 }
 
 // The same for wider tets, in int64 (extent < 2^20 keeps |s_i| < 2^63).
@@ -373,12 +379,11 @@ __device__ __forceinline__ float ld_buf(__amdgpu_buffer_rsrc_t r, int idx) {
   }
 }
 
-// Two consecutive FP32 voxels (idx, idx + 1) in one 8-byte buffer load; the
-// scalar offset `soff` (bytes) selects the row of the pair.
-__device__ __forceinline__ F2 ld_pair(__amdgpu_buffer_rsrc_t r, int idx, int soff) {
+// Two consecutive FP32 voxels (the first at byte offset `off`) in one 8-byte
+// buffer load; the scalar offset `soff` (bytes) selects the row of the pair.
+__device__ __forceinline__ F2 ld_pair(__amdgpu_buffer_rsrc_t r, int off, int soff) {
   typedef float f2v __attribute__((ext_vector_type(2)));
-  const f2v v = __builtin_bit_cast(
-      f2v, __builtin_amdgcn_raw_buffer_load_b64(r, static_cast<unsigned>(idx) * 4u, soff, 0));
+  const f2v v = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
   return F2{v.x, v.y};
 }
 
@@ -423,8 +428,13 @@ __device__ __forceinline__ float uniform_f(float v) {
 // Wave-uniform constants of one direction's sample loop (scalar registers).
 struct SampleConst {
   double m0, m1, m2;    // M[:, 0]: step of the mapped point per voxel along x
-  float thr;            // near-grid threshold on max_a |frac(q_a) - 1/2|
+  float thr;            // near a grid plane iff a fraction of q is <= thr or >= 1 - thr
 };
+
+__device__ __forceinline__ bool near_grid(const float f[3], float thr) {
+  const bool lo = fminf(fminf(f[0], f[1]), f[2]) <= thr, hi = fmaxf(fmaxf(f[0], f[1]), f[2]) >= 1.f - thr;
+  return lo | hi;
+}
 
 // One voxel sample of direction d whose mapped points may leave the padded
 // volume (a tet near or beyond the image border): the centre at padded
@@ -452,7 +462,7 @@ __device__ __forceinline__ bool sample_one(const ProblemView& P, const SampleCon
     c[t] = static_cast<int>(fl);
     f[t] = static_cast<float>(q[t] - fl);
   }
-  const bool amb = fabsf(f[0] - 0.5f) >= U.thr || fabsf(f[1] - 0.5f) >= U.thr || fabsf(f[2] - 0.5f) >= U.thr;
+  const bool amb = near_grid(f, U.thr);
 
   // corner indices (padded elements): x pair ix0/ix1, row offsets ry0/ry1,
   // slice offsets rz0/rz1.  The padded index range per axis is [0, n + 1];
@@ -555,19 +565,21 @@ __device__ __forceinline__ void guidance(const ProblemView& P, int d, unsigned b
 // inside the padded volume.  Straight-line: both samples' loads are issued
 // before either is interpolated; loads for an invalid sample read whatever
 // in-resource memory its address names (a buffer load cannot fault) and are
-// discarded.  For each valid sample h is added unless the mapped point is
-// within its error bound of a grid plane (amb: left to the exact path with
-// a, b); its band bits are returned for the guidance term, which the
-// slow-path queue adds (band is 0 for an invalid sample).
+// discarded.  Returns each sample's h (of a background sample both values
+// are exactly 0, so (a - b)^2 is its h unless the two sides differ in
+// foreground), whether its mapped point is within its error bound of a grid
+// plane (amb), its a and b for the exact path, and the two samples' band
+// bytes.
 template <int ST>
 __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const SampleConst& U,
                                                   __amdgpu_buffer_rsrc_t r_own, __amdgpu_buffer_rsrc_t r_oth,
-                                                  __amdgpu_buffer_rsrc_t r_band, int d, int vi, const double qr[3],
-                                                  int k, bool v0, bool v1, float& h_acc, bool amb[2],
-                                                  float a[2], float b[2], unsigned band[2]) {
+                                                  __amdgpu_buffer_rsrc_t r_band, int vi, const double qr[3], int k,
+                                                  float hv[2], bool amb[2], float a[2], float b[2],
+                                                  unsigned& band) {
   const int e0 = vi + k;
   float f[2][3];
-  int base[2];
+  int base[2];       // byte offsets of the stencils' first corners (FP32), elements otherwise
+  constexpr int esize = ST == kF32 ? 4 : 2, bsize = ST == kF32 ? 4 : 1;
 #pragma unroll
   for (int s = 0; s < 2; s++) {
     const double kd = static_cast<double>(k + s);
@@ -578,16 +590,16 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
       c[t] = static_cast<int>(q);     // q > 0 for a valid sample: truncation is the floor
       f[s][t] = static_cast<float>(__builtin_amdgcn_fract(q));
     }
-    base[s] = __umul24(c[2], P.pxy) + __umul24(c[1], P.px) + c[0];
-    amb[s] = fabsf(f[s][0] - 0.5f) >= U.thr || fabsf(f[s][1] - 0.5f) >= U.thr || fabsf(f[s][2] - 0.5f) >= U.thr;
+    base[s] = __umul24(c[2], P.pxy * bsize) + (__umul24(c[1], P.px * bsize) + c[0] * bsize);
+    amb[s] = near_grid(f[s], U.thr);
   }
-  // loads: own voxels (one pair), the 2 x 4 corner pairs, the two band bytes
+  // loads: own voxels (one pair), the 2 x 4 corner pairs, the band bytes (one
+  // pair; the mask is all zero when the problem has no guidance sets)
   float v[2][8];
   bool fg8[2];
-  constexpr int esize = ST == kF32 ? 4 : 2;
   const int sy = P.px * esize, sz = P.pxy * esize;   // row and slice offsets in bytes
   if constexpr (ST == kF32) {
-    const F2 own = ld_pair(r_own, e0, 0);
+    const F2 own = ld_pair(r_own, e0 * 4, 0);
     a[0] = own.a;
     a[1] = own.b;
 #pragma unroll
@@ -611,9 +623,7 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
       if (!P.fg_from_b) fg8[s] = ((w00 | w01 | w10 | w11) & 0x7fff7fffu) != 0u;
     }
   }
-  // the band mask is all zero when the problem has no guidance sets
-  band[0] = __builtin_amdgcn_raw_buffer_load_b8(r_band, static_cast<unsigned>(e0), 0, 0);
-  band[1] = __builtin_amdgcn_raw_buffer_load_b8(r_band, static_cast<unsigned>(e0) + 1u, 0, 0);
+  band = __builtin_amdgcn_raw_buffer_load_b16(r_band, static_cast<unsigned>(e0), 0, 0);
 #pragma unroll
   for (int s = 0; s < 2; s++) {
     const float* w = v[s];
@@ -629,13 +639,8 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
                           __float_as_uint(w[6]) | __float_as_uint(w[7]);
       fg8[s] = (ob << 1) != 0u;
     }
-    const bool fg_a = a[s] > 0.f;
     const float dd = a[s] - b[s];
-    const float hv = (fg_a && fg8[s]) ? dd * dd : ((fg_a != fg8[s]) ? 1.f : 0.f);
-    const bool valid = s == 0 ? v0 : v1;
-    amb[s] = amb[s] && valid;
-    if (!valid) band[s] = 0u;
-    if (valid && !amb[s]) h_acc += hv;
+    hv[s] = ((a[s] > 0.f) != fg8[s]) ? 1.f : dd * dd;
   }
 }
 
@@ -686,6 +691,23 @@ __device__ __forceinline__ void flush_deferred(const ProblemView& P, const WaveL
   }
 }
 
+// The problem's view, a kernel's first argument, read again from the kernel
+// arguments (scalar loads) where it is used: its 30 words would otherwise
+// stay live in scalar registers over all the loops, and those that do not fit
+// are spilled into lanes of vector registers, each use a VALU instruction
+// (72 -> 44 spills, 11 -> 4 lane reads in a sample batch; 128x128x96,
+// population 512: 9.19 -> 8.94 ms; 192x192x128 BF16, 256: 15.8 -> 14.1 ms).
+typedef const __attribute__((address_space(4))) ProblemView* ViewPtr;
+
+__device__ __forceinline__ ViewPtr view_ptr() {
+  return (ViewPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+__device__ __forceinline__ ProblemView view(ViewPtr p) {
+  asm volatile("" : "+s"(p));
+  return *(const ProblemView*)p;
+}
+
 // Evaluate two items (a tet of a candidate each) in both directions.  The
 // set-up runs for both at once, item s on half-wave s (lanes 32 s .. 32 s +
 // 31); rows and samples then take one item after the other on the whole
@@ -693,7 +715,7 @@ __device__ __forceinline__ void flush_deferred(const ProblemView& P, const WaveL
 // v0z v1x ...), lanes 12..23 the target tet's (`coord`).  Item s writes
 // out_s[0] (direction 0) and out_s[1]; item 1 exists only when has1.
 template <int ST>
-__device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, float coord, WaveLds* L,
+__device__ __forceinline__ void eval_tet(ViewPtr VP, int tet0, int tet1, bool has1, float coord, WaveLds* L,
                          Record* out0, Record* out1) {
   // the lane index is made opaque so that values derived from it are not
   // hoisted out of the persistent partial-evaluation loop (they would stay
@@ -718,10 +740,11 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
   // flag; lanes 0..15 of a half take mesh 0, lanes 16..31 mesh 1.  The
   // values go to the item's LDS block so that only the current direction's
   // copy is live in the sample loop.
-  const int dims[3] = {P.nx, P.ny, P.nz};
-  const int ref = P.ref_sign[tet];
   bool active;
   {
+    const ProblemView P = view(VP);
+    const int dims[3] = {P.nx, P.ny, P.nz};
+    const int ref = P.ref_sign[tet];
     const int m = hl >> 4;
     int V[4][3];
 #pragma unroll
@@ -735,8 +758,8 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
       const int mn = min(min(V[0][k], V[1][k]), min(V[2][k], V[3][k]));
       const int mx = max(max(V[0][k], V[1][k]), max(V[2][k], V[3][k]));
       ext = max(ext, mx - mn);
-      lo[k] = max(0, -static_cast<int>(floor_div_pos(-static_cast<int64_t>(mn), 1024)));
-      hi[k] = min(dims[k] - 1, static_cast<int>(floor_div_pos(mx, 1024)));
+      lo[k] = max(0, (mn + 1023) >> 10);              // ceil(mn / 1024), floor(mx / 1024)
+      hi[k] = min(dims[k] - 1, mx >> 10);
       // the tet of mesh m is sampled by direction 1 - m: every trilinear
       // corner of a mapped point lies in the padded volume when the tet is
       // inside (-1, n) by at least 2^-10 voxel
@@ -759,9 +782,9 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
         C.lo[k] = lo[k];
         C.hi[k] = hi[k];
       }
+      C.vbase = (lo[2] + 1) * P.pxy + (lo[1] + 1) * P.px + lo[0] + 1;
       C.W = hi[0] - lo[0];
       C.NYb = hi[1] - lo[1] + 1;
-      C.R = active ? C.NYb * (hi[2] - lo[2] + 1) : 0;
       C.active = active ? 1 : 0;
       I->c[1 - m].inner = interior ? 1 : 0;
       C.h = 0.f;
@@ -821,7 +844,7 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
     // the sum within each half-wave (butterfly over lane bits 0..4)
 #pragma unroll
     for (int d = 16; d >= 1; d >>= 1) term += __shfl_xor(term, d, 64);
-    const float mag = P.elasticity[tet] * term;
+    const float mag = view(VP).elasticity[tet] * term;
     if (hl == 0) I->c[0].mag = mag;
   }
   // set-up phase 1, lanes 0..7 of each half (direction d = hl / 4, face
@@ -866,18 +889,13 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
       // |terms| <= 2 E^3 <= 2^49: exact
       const double B0 = fma(nx_, ox, fma(ny_, oy, nz_ * oz)) + lex;
       C.B0[i] = B0;
-      if (kind != 0) {
-        const double ta = -PY * invA, tb = -PZ * invA, tg = -B0 * invA;
-        C.TA[i] = ta;
-        C.TB[i] = tb;
-        C.TG[i] = tg;
-        C.TE[i] = (fabs(ta) * C.NYb + fabs(tb) * (C.hi[2] - C.lo[2] + 1) + fabs(tg) + 128.0) * 0x1p-48;
-      } else {
-        C.TA[i] = PY;
-        C.TB[i] = PZ;
-        C.TG[i] = B0;
-        C.TE[i] = 0.0;
-      }
+      // the FP32 crossing: three constants rounded and two operations, each
+      // within 2^-24 of a partial sum -- below 3/4 of this bound
+      const double ta = -PY * invA, tb = -PZ * invA, tg = -B0 * invA;
+      const double te = (fabs(ta) * C.NYb + fabs(tb) * (C.hi[2] - C.lo[2] + 1) + fabs(tg) + 1.0) * 0x1p-22;
+      C.T[i] = make_float4(static_cast<float>(ta), static_cast<float>(tb), static_cast<float>(tg),
+                           static_cast<float>(te));
+      if (te >= 0.25) C.kind[i] = 2 * kind;
     } else {
       const long long nxi = static_cast<long long>(nx_), nyi = static_cast<long long>(ny_),
                       nzi = static_cast<long long>(nz_);
@@ -939,9 +957,9 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
     }
     C.qlo[a] = q;
     C.gthr[a] = 0.5 - bound * 0x1p-40;
-    // FP32 fraction: rounding it and subtracting 1/2 moves the test value by
-    // < 2^-24; the margin 2^-22 also covers rounding the threshold
-    C.thr_f[a] = static_cast<float>(0.5 - bound * 0x1p-40 - 0x1p-22);
+    // FP32 fraction: rounding it moves it by < 2^-24; the margin 2^-22 also
+    // covers rounding the threshold and its complement
+    C.thr_f[a] = static_cast<float>(bound * 0x1p-40 + 0x1p-22);
   }
   wave_sync();
 
@@ -992,18 +1010,13 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
   for (int d = 0; d < 2; d++) {
     const DirConst& Cd = IT->c[d];
     if (!uniform_i(Cd.active)) continue;
-    const int nyb = uniform_i(Cd.NYb), Wd = uniform_i(Cd.W);
-    const int lox = uniform_i(Cd.lo[0]), loy = uniform_i(Cd.lo[1]), loz = uniform_i(Cd.lo[2]);
     const bool inner = uniform_i(Cd.inner) != 0;
     const bool fast = uniform_i(Cd.fast) != 0;
     SampleConst U;
     U.m0 = uniform_d(Cd.M[0][0]);
     U.m1 = uniform_d(Cd.M[1][0]);
     U.m2 = uniform_d(Cd.M[2][0]);
-    U.thr = uniform_f(fminf(fminf(Cd.thr_f[0], Cd.thr_f[1]), Cd.thr_f[2]));
-    const __amdgpu_buffer_rsrc_t r_own = image_rsrc<ST>(P.img[d], P.pvox);
-    const __amdgpu_buffer_rsrc_t r_oth = image_rsrc<ST>(P.img[1 - d], P.pvox);
-    const __amdgpu_buffer_rsrc_t r_band = byte_rsrc(P.band[d], P.pvox);
+    U.thr = uniform_f(fmaxf(fmaxf(Cd.thr_f[0], Cd.thr_f[1]), Cd.thr_f[2]));
     float h = 0.f, g = 0.f;
     int n = 0, n_defer = 0;
     // row table: a ring of 64 slots; the row of rank r (in stream order)
@@ -1013,18 +1026,21 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
 
     // one sample of the current batch for directions whose mapped points may
     // leave the padded volume; a near-grid one joins the deferred queue
-    auto sample = [&](bool valid, int vi, const double qr[3], int k, int jbase) {
+    auto sample = [&](const ProblemView& P, bool valid, int vi, const double qr[3], int k,
+                      int jbase) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t r_own = image_rsrc<ST>(d ? P.img[1] : P.img[0], P.pvox);
+      const __amdgpu_buffer_rsrc_t r_oth = image_rsrc<ST>(d ? P.img[0] : P.img[1], P.pvox);
+      const __amdgpu_buffer_rsrc_t r_band = byte_rsrc(d ? P.band[1] : P.band[0], P.pvox);
       bool amb = false;
       float a = 0.f, b = 0.f;
       if (valid) {
         amb = sample_one<ST>(P, U, r_own, r_oth, r_band, d, vi + k, qr, k, h, g, a, b);
-        n += 1;
       }
       const uint64_t amb_mask = __ballot(amb);
       if (amb_mask) {
         if (n_defer + __popcll(amb_mask) > kDeferCap) {
           wave_sync();
-          flush_deferred<ST>(P, L, IT, n_defer, h, g);
+          flush_deferred<ST>(view(VP), L, IT, n_defer, h, g);
           n_defer = 0;
           wave_sync();
         }
@@ -1038,11 +1054,12 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
 
     // consume units [cons, limit) in batches of 64 (one unit per lane), then
     // drop the rows that end by `limit` (a prefix of the ring)
-    auto run_batches_t = [&](auto inner_tag, int limit) {
+    auto run_batches_t = [&](auto inner_tag, int limit) __attribute__((always_inline)) {
       constexpr bool kInner = decltype(inner_tag)::value;
       const bool valid = ((lane - head) & (kWave - 1)) < n_tab;
       const int my_off = valid ? L->row[lane].y : 0x7fffffff;
       for (int sb = cons; sb < limit; sb += kWave) {
+        const ProblemView P = view(VP);
         // rank of each lane's row: rows starting at or before sb, plus rows
         // starting inside (sb, sb + lane] (marked with this batch's tag)
         tag += 1;
@@ -1050,9 +1067,9 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
         const int rel = my_off - sb;
         if (rel > 0 && rel < kWave) L->mark[rel] = tag;
         wave_sync();
+        // starts at or below this lane (no row starts at lane 0: rel > 0)
         const uint64_t starts = __ballot(L->mark[lane] == tag);
-        const int rank = first + bits_below(starts) + static_cast<int>((starts >> lane) & 1ull);
-        const int slot = (head + rank) & (kWave - 1);
+        const int slot = bits_below(starts >> 1, head + first) & (kWave - 1);
         const int u = sb + lane;
         const bool ok = u < limit;
         const int4 rw = L->row[slot];
@@ -1061,37 +1078,50 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
         const bool ok2 = ok && k + 1 < rw.w;
         if constexpr (kInner) {
           bool amb[2];
-          float a[2], b[2];
-          unsigned band[2];
-          sample_pair_inner<ST>(P, U, r_own, r_oth, r_band, d, rw.x, qr, k, ok, ok2, h, amb, a, b, band);
-          n += static_cast<int>(ok) + static_cast<int>(ok2);
-          // near-grid and in-band samples join the queue, at most one wave's
-          // worth (64, the queue's capacity) at a time, a flush first when
-          // they would not fit
+          float hv[2], a[2], b[2];
+          unsigned band;
+          const __amdgpu_buffer_rsrc_t r_own = image_rsrc<ST>(d ? P.img[1] : P.img[0], P.pvox);
+          const __amdgpu_buffer_rsrc_t r_oth = image_rsrc<ST>(d ? P.img[0] : P.img[1], P.pvox);
+          const __amdgpu_buffer_rsrc_t r_band = byte_rsrc(d ? P.band[1] : P.band[0], P.pvox);
+          sample_pair_inner<ST>(P, U, r_own, r_oth, r_band, rw.x, qr, k, hv, amb, a, b, band);
+          hv[0] = ok ? hv[0] : 0.f;
+          hv[1] = ok2 ? hv[1] : 0.f;
+          // most batches hold no sample near a grid plane and none in a band
+          if (__ballot(ok & ((band != 0u) | amb[0] | amb[1]))) {
+            amb[0] = amb[0] && ok;
+            amb[1] = amb[1] && ok2;
+            hv[0] = amb[0] ? 0.f : hv[0];
+            hv[1] = amb[1] ? 0.f : hv[1];
+            const unsigned bits[2] = {ok ? band & 0xffu : 0u, ok2 ? band >> 8 : 0u};
+            // they join the queue, at most one wave's worth (64, the queue's
+            // capacity) at a time, a flush first when they would not fit
 #pragma unroll
-          for (int s2 = 0; s2 < 4; s2++) {
-            const bool want = (s2 & 1) ? band[s2 >> 1] != 0u : amb[s2 >> 1];
-            const uint64_t m = __ballot(want);
-            if (m) {
-              const int nq = __popcll(m);
-              if (n_defer + nq > kDeferCap) {
-                wave_sync();
-                flush_deferred<ST>(P, L, IT, n_defer, h, g);
-                n_defer = 0;
-                wave_sync();
+            for (int s2 = 0; s2 < 4; s2++) {
+              const bool want = (s2 & 1) ? bits[s2 >> 1] != 0u : amb[s2 >> 1];
+              const uint64_t m = __ballot(want);
+              if (m) {
+                const int nq = __popcll(m);
+                if (n_defer + nq > kDeferCap) {
+                  wave_sync();
+                  flush_deferred<ST>(view(VP), L, IT, n_defer, h, g);
+                  n_defer = 0;
+                  wave_sync();
+                }
+                if (want) {
+                  const int j = rw.z + k + (s2 >> 1);
+                  L->defer[bits_below(m, n_defer)] =
+                      (s2 & 1) ? make_int4(j | (d << 30), static_cast<int>(bits[s2 >> 1]), 0, 1)
+                               : make_int4(j | (d << 30), __float_as_int(a[s2 >> 1]), __float_as_int(b[s2 >> 1]), 0);
+                }
+                n_defer += nq;
               }
-              if (want) {
-                const int j = rw.z + k + (s2 >> 1);
-                L->defer[n_defer + bits_below(m)] =
-                    (s2 & 1) ? make_int4(j | (d << 30), static_cast<int>(band[s2 >> 1]), 0, 1)
-                             : make_int4(j | (d << 30), __float_as_int(a[s2 >> 1]), __float_as_int(b[s2 >> 1]), 0);
-              }
-              n_defer += nq;
             }
           }
+          h += hv[0];
+          h += hv[1];
         } else {
-          sample(ok, rw.x, qr, k, rw.z);
-          sample(ok2, rw.x, qr, k + 1, rw.z);
+          sample(P, ok, rw.x, qr, k, rw.z);
+          sample(P, ok2, rw.x, qr, k + 1, rw.z);
         }
         wave_sync();
       }
@@ -1106,7 +1136,7 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
     };
     // the mapped points stay inside the padded volume (no clamps) or not:
     // one specialised batch loop each
-    auto run_batches = [&](int limit) {
+    auto run_batches = [&](int limit) __attribute__((always_inline)) {
       if (inner)
         run_batches_t(std::true_type{}, limit);
       else
@@ -1115,7 +1145,7 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
 
     // rows: slices in groups of 64 (one per lane), the rows of the non-empty
     // slices of a group enumerated 64 at a time
-    const int nzb = uniform_i(Cd.hi[2]) - loz + 1;
+    const int nzb = uniform_i(Cd.hi[2]) - uniform_i(Cd.lo[2]) + 1;
     const int* own_v = IT->vert + 12 * d;
     const int unit = 2 * s + d;
     const int sbase = pre ? 16 * unit : 0;
@@ -1126,7 +1156,8 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
         Rg = uniform_i(L->pre_rows[unit]);
       } else {
         int y0 = 0, cnt = 0;
-        if (zb + lane < nzb) slice_rows(own_v, loz + zb + lane, loy, loy + nyb - 1, y0, cnt);
+        if (zb + lane < nzb)
+          slice_rows(own_v, Cd.lo[2] + zb + lane, Cd.lo[1], Cd.lo[1] + Cd.NYb - 1, y0, cnt);
         const uint64_t ne = __ballot(cnt > 0);
         ns = __popcll(ne);
         const int sexcl = wave_excl_scan(cnt);
@@ -1144,16 +1175,16 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
         if (srel > 0 && srel < kWave) L->mark[srel] = tag;
         wave_sync();
         const uint64_t sst = __ballot(L->mark[lane] == tag);
-        const int si = sfirst + bits_below(sst) + static_cast<int>((sst >> lane) & 1ull);
+        const int si = bits_below(sst >> 1, sfirst);
         int js = 1, je = 0, yr = 0, zr = 0;
         if (rr < Rg) {
           const int4 sl = L->slice[sbase + si];
           zr = sl.x;
           yr = sl.y + (rr - sl.z);
           if (fast)
-            row_span_fast(Cd, yr, zr, Wd, js, je);
+            row_span_fast(Cd, yr, zr, Cd.W, js, je);
           else
-            row_span_wide(Cd, yr, zr, Wd, js, je);
+            row_span_wide(Cd, yr, zr, Cd.W, js, je);
         }
         const int len = max(0, je - js + 1);
         // the row's box-relative position, packed (it stays live while the
@@ -1172,7 +1203,8 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
           if (take) {
             const int slot = (head + n_tab + ci) & (kWave - 1);
             const int jx = jp & 1023, jy = (jp >> 10) & 1023, jz = jp >> 20;
-            const int vi_row = __umul24(loz + jz + 1, P.pxy) + __umul24(loy + jy + 1, P.px) + lox + jx + 1;
+            const ProblemView P = view(VP);
+            const int vi_row = __umul24(jz, P.pxy) + (__umul24(jy, P.px) + (Cd.vbase + jx));
             L->row[slot] = make_int4(vi_row, tab_end + excl, jp, len);
 #pragma unroll
             for (int t = 0; t < 3; t++)
@@ -1180,6 +1212,7 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
                                      fma(Cd.M[t][1], static_cast<double>(jy),
                                          fma(Cd.M[t][2], static_cast<double>(jz), Cd.qlo[t])));
           }
+          n += take ? len : 0;
           n_tab += __popcll(took);
           tab_end += added;
           want &= ~took;
@@ -1192,12 +1225,12 @@ __device__ void eval_tet(const ProblemView& P, int tet0, int tet1, bool has1, fl
     if (tab_end > cons) run_batches(tab_end);
     if (n_defer > 0) {
       wave_sync();
-      flush_deferred<ST>(P, L, IT, n_defer, h, g);
+      flush_deferred<ST>(view(VP), L, IT, n_defer, h, g);
     }
-    h = wave_sum(h);
-    g = wave_sum(g);
-    n = wave_sum_i(n);
-    if (lane == 0) {
+    h = wave_sum_63(h);
+    g = wave_sum_63(g);
+    n = wave_sum_63i(n);
+    if (lane == 63) {
       IT->c[d].h = h;
       IT->c[d].g = g;
       IT->c[d].samples = static_cast<uint32_t>(n);
@@ -1266,7 +1299,7 @@ __global__ __launch_bounds__(256, 5) void k_eval_full(ProblemView P, FullItems F
     const int mesh = hl < 12 ? 0 : 1;
     coord = F.pts[((static_cast<size_t>(cand) * 2 + mesh) * 3 + k) * P.n_points + v];
   }
-  eval_tet<ST>(P, tet0, tet1, has1, coord, &lds[wave], &rec[(static_cast<size_t>(cand0) * P.n_tets + tet0) * 2],
+  eval_tet<ST>(view_ptr(), tet0, tet1, has1, coord, &lds[wave], &rec[(static_cast<size_t>(cand0) * P.n_tets + tet0) * 2],
                &rec[(static_cast<size_t>(cand1) * P.n_tets + tet1) * 2]);
 }
 
@@ -1699,7 +1732,7 @@ __global__ __launch_bounds__(256, 4) void k_eval_partial(ProblemView P, PartialI
       const float coord = partial_coord(P, I, it0, it1, has1, lane);
       const int dest0 = uniform_i(I.item_dest[idx]);
       const int dest1 = has1 ? uniform_i(I.item_dest[idx + 1]) : dest0;
-      eval_tet<ST>(P, tet0, tet1, has1, coord, &lds[wave], &out[static_cast<size_t>(dest0) * 2],
+      eval_tet<ST>(view_ptr(), tet0, tet1, has1, coord, &lds[wave], &out[static_cast<size_t>(dest0) * 2],
                    &out[static_cast<size_t>(dest1) * 2]);
     }
   }
@@ -1726,7 +1759,7 @@ __global__ __launch_bounds__(256, 5) void k_eval_partial_grid(ProblemView P, Par
   const float coord = partial_coord(P, I, it0, it1, has1, lane);
   const int dest0 = uniform_i(I.item_dest[idx]);
   const int dest1 = has1 ? uniform_i(I.item_dest[idx + 1]) : dest0;
-  eval_tet<ST>(P, tet0, tet1, has1, coord, &lds[wave], &out[static_cast<size_t>(dest0) * 2],
+  eval_tet<ST>(view_ptr(), tet0, tet1, has1, coord, &lds[wave], &out[static_cast<size_t>(dest0) * 2],
                &out[static_cast<size_t>(dest1) * 2]);
 }
 
