@@ -640,13 +640,15 @@ morea_status morea_surrogate_predict_rows(morea_surrogate *s, const float *feats
                                           float *pred, void *stream);
 
 /* Pre-screen: score [pop] of offspring pts [pop][2][3][n_points] with their
- * parents as for morea_surrogate_features (features built on the fly: one
- * launch for the parents' point means, one for the offspring); an offspring
- * without a valid parent scores +inf.  The parents' point means go to a
- * workspace of the surrogate (16 bytes per (parent, tet)), allocated again
- * (hipMalloc, after waiting for the device) when a call needs more than
- * every earlier one; calls on one surrogate that overlap on different
- * streams race on it. */
+ * parents as for morea_surrogate_features (features built on the fly: the
+ * parents' point means, then the offspring, each from a copy of the
+ * coordinates by columns); an offspring without a valid parent scores +inf.
+ * The parents' point means (16 bytes per (parent, tet)), partial scores (8
+ * per offspring and run of 1 to 8 tets) and columns (36 per offspring and
+ * mesh point, at most 256 MiB or 64 offspring at a time) go to a workspace of
+ * the surrogate, allocated again (hipMalloc, after waiting for the device)
+ * when a call needs more than every earlier one; calls on one surrogate that
+ * overlap on different streams race on it. */
 morea_status morea_surrogate_prescreen(morea_surrogate *s, const float *pts, int32_t pop, const float *parent_pts,
                                        int32_t n_parents, const void *parent_cache, const int32_t *parent_of,
                                        float *score, void *stream);

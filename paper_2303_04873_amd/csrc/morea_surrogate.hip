@@ -90,6 +90,17 @@ __device__ void load_net(NetLds* N, const bf16* w1b, const bf16* w2b, const floa
   if (threadIdx.x == 0) N->b3 = params[oB3];
 }
 
+// max(v, 0) as the median of v, 0 and +inf (given by inf_reg): one instruction
+// where fmaxf of a matrix result takes two, the first to quieten a NaN.  0 for
+// a NaN, as fmaxf.
+__device__ __forceinline__ float inf_reg() {
+  float inf;
+  asm("s_mov_b32 %0, 0x7f800000" : "=s"(inf));
+  return inf;
+}
+
+__device__ __forceinline__ float relu(float v, float inf) { return __builtin_amdgcn_fmed3f(v, 0.f, inf); }
+
 // Forward pass of one tile of 32 rows (T->x filled).  Leaves relu(z1) in
 // T->h1 (BF16) unless `red` overlays it, returns the layer-2
 // pre-activations (4 column tiles) in z2 and writes y to T->y.
@@ -173,30 +184,37 @@ struct Parents {
 };
 
 // Trilinear interpolant at (x, y, z) clamped into [0, n - 1] on each axis,
-// from a quad copy `q` of a padded image (entry e holds the FP32 voxels e,
-// e + 1, e + px, e + px + 1 of the padded volume, voxel (i, j, k) at
+// from a quad copy `q` of a padded image (entry e holds FP32 voxel e of the
+// padded volume, voxel e + 1 minus it, voxel e + px, voxel e + px + 1 minus that, voxel (i, j, k) at
 // (k + 1) pxy + (j + 1) px + i + 1), so a sample reads two aligned 16-byte
 // entries instead of eight scattered values.  The cell is the one below the
-// point, capped at n - 2, so the upper corner always lies in the volume or,
-// for an axis of size 1, on its zero border with weight 0.
+// point; at n - 1 its upper corner is on the zero border, with weight 0.
+// With kBig false
+// the copy is below 4 GiB: one 32-bit byte offset serves both loads, from two
+// scalar base addresses (dimensions are at most 1,024, so 24-bit products do).
+template <bool kBig>
 __device__ __forceinline__ float sample_clamped(const ProblemView& P, const float4* q, float x, float y, float z) {
-  const float p[3] = {fminf(fmaxf(x, 0.f), static_cast<float>(P.nx - 1)),
-                      fminf(fmaxf(y, 0.f), static_cast<float>(P.ny - 1)),
-                      fminf(fmaxf(z, 0.f), static_cast<float>(P.nz - 1))};
-  const int n[3] = {P.nx, P.ny, P.nz};
-  int c[3];
-  float f[3];
-#pragma unroll
-  for (int a = 0; a < 3; a++) {
-    c[a] = max(min(static_cast<int>(floorf(p[a])), n[a] - 2), 0);
-    f[a] = p[a] - static_cast<float>(c[a]);
+  // the median is the clamp (also of a NaN, which becomes 0)
+  const float p0 = __builtin_amdgcn_fmed3f(x, 0.f, static_cast<float>(P.nx - 1));
+  const float p1 = __builtin_amdgcn_fmed3f(y, 0.f, static_cast<float>(P.ny - 1));
+  const float p2 = __builtin_amdgcn_fmed3f(z, 0.f, static_cast<float>(P.nz - 1));
+  const unsigned c0 = static_cast<unsigned>(p0), c1 = static_cast<unsigned>(p1), c2 = static_cast<unsigned>(p2);
+  const float f0 = __builtin_amdgcn_fractf(p0), f1 = __builtin_amdgcn_fractf(p1), f2 = __builtin_amdgcn_fractf(p2);
+  const float4 *lo = q + (P.pxy + P.px + 1), *hi = lo + P.pxy;
+  float4 b, b1;
+  if constexpr (kBig) {
+    const size_t e = static_cast<size_t>(c2) * P.pxy + static_cast<size_t>(c1) * P.px + c0;
+    b = lo[e];
+    b1 = hi[e];
+  } else {
+    const uint32_t off = (__umul24(c2, P.pxy) + (__umul24(c1, P.px) + c0)) << 4;
+    b = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(lo) + off);
+    b1 = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(hi) + off);
   }
-  const size_t e = static_cast<size_t>(c[2] + 1) * P.pxy + static_cast<size_t>(c[1] + 1) * P.px + c[0] + 1;
-  const float4 b = q[e], b1 = q[e + P.pxy];
-  const float x00 = fmaf(f[0], b.y - b.x, b.x), x10 = fmaf(f[0], b.w - b.z, b.z);
-  const float x01 = fmaf(f[0], b1.y - b1.x, b1.x), x11 = fmaf(f[0], b1.w - b1.z, b1.z);
-  const float y0 = fmaf(f[1], x10 - x00, x00), y1 = fmaf(f[1], x11 - x01, x01);
-  return fmaf(f[2], y1 - y0, y0);
+  const float x00 = fmaf(f0, b.y, b.x), x10 = fmaf(f0, b.w, b.z);
+  const float x01 = fmaf(f0, b1.y, b1.x), x11 = fmaf(f0, b1.w, b1.z);
+  const float y0 = fmaf(f1, x10 - x00, x00), y1 = fmaf(f1, x11 - x01, x01);
+  return fmaf(f2, y1 - y0, y0);
 }
 
 // A tet's vertices in one candidate: mesh 0 (source) or 1 (target).
@@ -210,94 +228,74 @@ __device__ __forceinline__ void tet_vertices(const ProblemView& P, const float* 
     for (int a = 0; a < 3; a++) d[v][a] = cand[(3 * mesh + a) * P.n_points + vs[v]];
 }
 
+// A tet as its last vertex and the edges from it to the other three.
+struct Edges {
+  float v[3], e[3][3];
+};
+
+__device__ __forceinline__ Edges edges(const float d[4][3]) {
+  Edges t;
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    t.v[a] = d[3][a];
+#pragma unroll
+    for (int k = 0; k < 3; k++) t.e[k][a] = d[k][a] - d[3][a];
+  }
+  return t;
+}
+
 // h at barycentric coordinates l of the tet: (I_s(S l) - I_t(T l))^2.
-__device__ __forceinline__ float h_at(const ProblemView& P, const float4* img_s, const float4* img_t,
-                                      const float S[4][3], const float T[4][3], const float l[4]) {
+template <bool kBig>
+__device__ __forceinline__ float h_at(const ProblemView& P, const float4* img_s, const float4* img_t, const Edges& S,
+                                      const Edges& T, const float4 l) {
   float x[3], y[3];
 #pragma unroll
   for (int a = 0; a < 3; a++) {
-    x[a] = fmaf(l[0], S[0][a], fmaf(l[1], S[1][a], fmaf(l[2], S[2][a], l[3] * S[3][a])));
-    y[a] = fmaf(l[0], T[0][a], fmaf(l[1], T[1][a], fmaf(l[2], T[2][a], l[3] * T[3][a])));
+    x[a] = fmaf(l.z, S.e[2][a], fmaf(l.y, S.e[1][a], fmaf(l.x, S.e[0][a], S.v[a])));
+    y[a] = fmaf(l.z, T.e[2][a], fmaf(l.y, T.e[1][a], fmaf(l.x, T.e[0][a], T.v[a])));
   }
-  const float d = sample_clamped(P, img_s, x[0], x[1], x[2]) - sample_clamped(P, img_t, y[0], y[1], y[2]);
+  const float d = sample_clamped<kBig>(P, img_s, x[0], x[1], x[2]) - sample_clamped<kBig>(P, img_t, y[0], y[1], y[2]);
   return d * d;
 }
 
-// Sums of h over points [j0, j1) of a tet's 26 (the 4 vertices, the edge
-// midpoints (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), then the 16 interior points
-// `bary`) into acc: [0] vertices, [1] edges, [2] interior.  One point at a
-// time.
-__device__ __forceinline__ void point_sums(const ProblemView& P, const float4* img_s, const float4* img_t,
-                                           const float S[4][3], const float T[4][3], const float4* bary, int j0,
-                                           int j1, float acc[3]) {
-  acc[0] = acc[1] = acc[2] = 0.f;
+// The points of a tet behind the estimated changes, as barycentric
+// coordinates `bary`: its 4 vertices, the edge midpoints (0,1) (0,2) (0,3)
+// (1,2) (1,3) (2,3), then 16 interior points.
+constexpr int kPoints = 10 + kHalton;
+
+// Sum of h at points j .. j + N - 1, in order, one at a time.
+template <bool kBig, int N>
+__device__ __forceinline__ float point_run(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                           const Edges& S, const Edges& T, const float4* bary, int j) {
+  float sum = 0.f;
 #pragma unroll 1
-  for (int j = j0; j < j1; j++) {
-    float l[4] = {0.f, 0.f, 0.f, 0.f};
-    if (j < 4) {
-      l[0] = j == 0 ? 1.f : 0.f;
-      l[1] = j == 1 ? 1.f : 0.f;
-      l[2] = j == 2 ? 1.f : 0.f;
-      l[3] = j == 3 ? 1.f : 0.f;
-    } else if (j < 10) {
-      const int e = j - 4, a = e < 3 ? 0 : (e < 5 ? 1 : 2), b = e < 3 ? e + 1 : (e < 5 ? e - 1 : 3);
-#pragma unroll
-      for (int v = 0; v < 4; v++) l[v] = (v == a || v == b) ? .5f : 0.f;
-    } else {
-      const float4 q = bary[j - 10];
-      l[0] = q.x;
-      l[1] = q.y;
-      l[2] = q.z;
-      l[3] = q.w;
-    }
-    const float hv = h_at(P, img_s, img_t, S, T, l);
-    acc[j < 4 ? 0 : (j < 10 ? 1 : 2)] += hv;
-  }
+  for (int q = 0; q < N; q++) sum += h_at<kBig>(P, img_s, img_t, S, T, bary[j + q]);
+  return sum;
 }
 
-// The points are summed in two parts, [0, 13) and [13, 26), added at the end:
-// the pre-screen splits them over two lane halves in the same way, so both
-// paths give the same values.
-constexpr int kPointSplit = 13, kPoints = 10 + kHalton;
-
-__device__ __forceinline__ void combine_means(const float a[3], const float b[3], float m[3]) {
-  m[0] = (a[0] + b[0]) * 0.25f;
-  m[1] = (a[1] + b[1]) * (1.f / 6.f);
-  m[2] = (a[2] + b[2]) * (1.f / kHalton);
-}
-
-// Means of h over the tet's point sets in one candidate: m[0] the 4
-// vertices, m[1] the 6 edge midpoints, m[2] the 16 interior points.
+// Means of h over the point sets of a tet with vertices s (source) and t
+// (target): m[0] the 4 vertices, m[1] the 6 edge midpoints, m[2] the 16
+// interior points.
+template <bool kBig>
 __device__ __forceinline__ void point_means(const ProblemView& P, const float4* img_s, const float4* img_t,
-                                            const float* cand, int tet, const float4* bary, float m[3]) {
-  float S[4][3], T[4][3];
-  tet_vertices(P, cand, tet, 0, S);
-  tet_vertices(P, cand, tet, 1, T);
-  float a[3], b[3];
-  point_sums(P, img_s, img_t, S, T, bary, 0, kPointSplit, a);
-  point_sums(P, img_s, img_t, S, T, bary, kPointSplit, kPoints, b);
-  combine_means(a, b, m);
+                                            const float s[4][3], const float t[4][3], const float4* bary, float m[3]) {
+  const Edges S = edges(s), T = edges(t);
+  m[0] = point_run<kBig, 4>(P, img_s, img_t, S, T, bary, 0) * 0.25f;
+  m[1] = point_run<kBig, 6>(P, img_s, img_t, S, T, bary, 4) * (1.f / 6.f);
+  m[2] = point_run<kBig, kHalton>(P, img_s, img_t, S, T, bary, 10) * (1.f / kHalton);
 }
 
-// |signed volume| of a tet's source and target (voxel^3): the expected
-// samples of the tet in both directions.
-__device__ __forceinline__ float tet_weight(const ProblemView& P, const float* cand, int tet) {
-  float w = 0.f;
+// |signed volume| (voxel^3): the expected samples of the tet in its direction.
+__device__ __forceinline__ float tet_volume(const float d[4][3]) {
+  float e[3][3];
 #pragma unroll
-  for (int mesh = 0; mesh < 2; mesh++) {
-    float d[4][3];
-    tet_vertices(P, cand, tet, mesh, d);
-    float e[3][3];
+  for (int k = 0; k < 3; k++)
 #pragma unroll
-    for (int k = 0; k < 3; k++)
-#pragma unroll
-      for (int a = 0; a < 3; a++) e[k][a] = d[k + 1][a] - d[0][a];
-    const float det = e[0][0] * (e[1][1] * e[2][2] - e[1][2] * e[2][1]) -
-                      e[0][1] * (e[1][0] * e[2][2] - e[1][2] * e[2][0]) +
-                      e[0][2] * (e[1][0] * e[2][1] - e[1][1] * e[2][0]);
-    w += fabsf(det) * (1.f / 6.f);
-  }
-  return w;
+    for (int a = 0; a < 3; a++) e[k][a] = d[k + 1][a] - d[0][a];
+  const float det = e[0][0] * (e[1][1] * e[2][2] - e[1][2] * e[2][1]) -
+                    e[0][1] * (e[1][0] * e[2][2] - e[1][2] * e[2][0]) +
+                    e[0][2] * (e[1][0] * e[2][1] - e[1][1] * e[2][0]);
+  return fabsf(det) * (1.f / 6.f);
 }
 
 // Mean intensity term per sample of a tet over both directions, from its
@@ -321,14 +319,15 @@ __device__ __forceinline__ float stored_voxel(const ProblemView& P, int which, s
   }
 }
 
-// Quad copy of image `which` (0 source, 1 target; any storage): entry e
-// holds the padded voxels e, e + 1, e + px, e + px + 1 as FP32.
+// Quad copy of image `which` (0 source, 1 target; any storage) as FP32: entry
+// e holds padded voxel e, the difference of e + 1 to it, voxel e + px, the
+// difference of e + px + 1 to that (one fused multiply-add per x interpolation).
 template <int ST>
 __global__ void k_image_quads(ProblemView P, int which, float4* out) {
   const size_t e = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (e >= P.pvox) return;
-  out[e] = make_float4(stored_voxel<ST>(P, which, e), stored_voxel<ST>(P, which, e + 1),
-                       stored_voxel<ST>(P, which, e + P.px), stored_voxel<ST>(P, which, e + P.px + 1));
+  const float a = stored_voxel<ST>(P, which, e), b = stored_voxel<ST>(P, which, e + P.px);
+  out[e] = make_float4(a, stored_voxel<ST>(P, which, e + 1) - a, b, stored_voxel<ST>(P, which, e + P.px + 1) - b);
 }
 
 template <int ST>
@@ -432,7 +431,7 @@ __global__ void k_tet_stats(ProblemView P, const float* ref, float* stats, int* 
 struct FeatureInputs {
   const float4* img_s;  // quad copies of the two images
   const float4* img_t;
-  const float4* bary;   // [16] interior points, barycentric
+  const float4* bary;   // [kPoints] points of a tet, barycentric
   const float* stats;   // [n_tets][8]
   float h_scale;
   float inv_h;          // 1 / h_scale
@@ -441,6 +440,7 @@ struct FeatureInputs {
 // One thread per (offspring, tet) row: the 23 features in order.  Threads in
 // tet-major order, so that the threads in flight read the same part of the
 // images.
+template <bool kBig>
 __global__ void k_features(ProblemView P, const float* pts, Parents Q, FeatureInputs F, int pop, float* feats) {
   const long long r = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (r >= static_cast<long long>(pop) * P.n_tets) return;
@@ -461,8 +461,11 @@ __global__ void k_features(ProblemView P, const float* pts, Parents Q, FeatureIn
 #pragma unroll
     for (int a = 0; a < 3; a++) o[3 * v + a] = (d[v][a] - dp[v][a]) * kRelScale;
   float mc[3], mp[3];
-  point_means(P, F.img_s, F.img_t, cp, tet, F.bary, mc);
-  point_means(P, F.img_s, F.img_t, pp, tet, F.bary, mp);
+  float sv[4][3];
+  tet_vertices(P, cp, tet, 0, sv);
+  point_means<kBig>(P, F.img_s, F.img_t, sv, d, F.bary, mc);
+  tet_vertices(P, pp, tet, 0, sv);
+  point_means<kBig>(P, F.img_s, F.img_t, sv, dp, F.bary, mp);
 #pragma unroll
   for (int k = 0; k < 3; k++) o[12 + k] = (mc[k] - mp[k]) * F.inv_h;
 #pragma unroll
@@ -487,16 +490,92 @@ __global__ void k_targets(const Record* rec, int n_tets, int rows, Parents Q, fl
           tet_mean_h(Q.rec + static_cast<size_t>(par) * n_tets * 2, tet)) * inv_h;
 }
 
-// Point means of every (parent, tet): out [n][n_tets] (m0, m1, m2, 0).
-// Threads in tet-major order, so that the threads in flight read the same
-// part of the images.
-__global__ void k_parent_means(ProblemView P, const float* pts, int n, FeatureInputs F, float4* out) {
+// Coordinates by columns, so that lanes on consecutive candidates read
+// consecutive words (as [cand][6][n_points] every lane of such a load lies in
+// a line of its own): out [n_points][C][n] of candidates first .. first + n - 1
+// of pts, rows 0..5 the coordinates (source x y z, target x y z) and, with
+// C = 9, rows 6..8 the target's coordinates minus the parent's
+// (unspecified without a valid parent).  Tiles of 64 candidates by 32 points.
+constexpr int kColCands = 64, kColPoints = 32;
+constexpr size_t kColBytes = size_t{256} << 20;   // of columns at a time (at least 64 candidates)
+
+template <int C>
+__global__ __launch_bounds__(256) void k_columns(const float* pts, int first, int n, int n_points, Parents Q,
+                                                 float* out) {
+  __shared__ float tile[C == 9 ? 2 : 1][kColPoints][kColCands + 1];
+  const int c0 = blockIdx.y * kColCands, c = blockIdx.z;
+  const size_t p0 = static_cast<size_t>(blockIdx.x) * kColPoints;
+  const int pl = threadIdx.x & 31, cl = threadIdx.x >> 5;
+  const size_t p = p0 + pl;
+  // unconditional loads (clamped; unused beyond the edges), all in flight
+  const size_t pc = min(p, static_cast<size_t>(n_points) - 1);
+  float v[kColCands / 8], w[kColCands / 8];
+#pragma unroll
+  for (int q = 0; q < kColCands / 8; q++)
+    v[q] = pts[((static_cast<size_t>(first) + min(c0 + cl + 8 * q, n - 1)) * 6 + c) * n_points + pc];
+  if constexpr (C == 9)
+    if (c >= 3) {
+      int par[kColCands / 8];
+#pragma unroll
+      for (int q = 0; q < kColCands / 8; q++) par[q] = Q.of[static_cast<size_t>(first) + min(c0 + cl + 8 * q, n - 1)];
+#pragma unroll
+      for (int q = 0; q < kColCands / 8; q++) {
+        const bool ok = par[q] >= 0 && par[q] < Q.n;
+        w[q] = v[q];
+        if (Q.n > 0) w[q] = Q.pts[(static_cast<size_t>(ok ? par[q] : 0) * 6 + c) * n_points + pc];
+        if (!ok) w[q] = v[q];
+      }
+#pragma unroll
+      for (int q = 0; q < kColCands / 8; q++) tile[1][pl][cl + 8 * q] = v[q] - w[q];
+    }
+#pragma unroll
+  for (int q = 0; q < kColCands / 8; q++) tile[0][pl][cl + 8 * q] = v[q];
+  __syncthreads();
+  const int ol = threadIdx.x & 63, pr = threadIdx.x >> 6;
+  if (c0 + ol >= n) return;
+  for (int r = pr; r < kColPoints && p0 + r < static_cast<size_t>(n_points); r += 4) {
+    float* o = out + ((p0 + r) * C + c) * n + c0 + ol;
+    o[0] = tile[0][r][ol];
+    if constexpr (C == 9)
+      if (c >= 3) o[static_cast<size_t>(3) * n] = tile[1][r][ol];
+  }
+}
+
+// A tet's vertices in candidate `cand` of a column array of n candidates,
+// rows row .. row + 2 of C (scalar addresses plus one 32-bit byte offset where
+// the tet is the same for the wave: a column is below 2^32 bytes).
+template <int C>
+__device__ __forceinline__ void column_vertices(const float* cols, const int4 tv, int row, int n, unsigned cand,
+                                                float d[4][3]) {
+  const int vs[4] = {tv.x, tv.y, tv.z, tv.w};
+  unsigned off = 4u * cand;
+  asm volatile("" : "+v"(off));   // kept as 32 bits, not widened ahead of a loop
+#pragma unroll
+  for (int v = 0; v < 4; v++)
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      const float* col = cols + (static_cast<size_t>(vs[v]) * C + row + a) * n;
+      d[v][a] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(col) + off);
+    }
+}
+
+// Point means and mean intensity term of every (parent, tet) of parents
+// first .. first + n - 1, whose coordinates are given by columns: out
+// [parent][n_tets] (m0, m1, m2, term).  Threads in tet-major order, so that
+// the threads in flight read the same part of the images.
+template <bool kBig>
+__global__ void k_parent_means(ProblemView P, const float* cols, int first, int n, const Record* rec,
+                               FeatureInputs F, float4* out) {
   const long long r = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (r >= static_cast<long long>(n) * P.n_tets) return;
   const int tet = static_cast<int>(r / n), cand = static_cast<int>(r % n);
-  float m[3];
-  point_means(P, F.img_s, F.img_t, pts + static_cast<size_t>(cand) * 6 * P.n_points, tet, F.bary, m);
-  out[static_cast<size_t>(cand) * P.n_tets + tet] = make_float4(m[0], m[1], m[2], 0.f);
+  const int4 tv = P.tets[tet];
+  float S[4][3], T[4][3], m[3];
+  column_vertices<6>(cols, tv, 0, n, cand, S);
+  column_vertices<6>(cols, tv, 3, n, cand, T);
+  point_means<kBig>(P, F.img_s, F.img_t, S, T, F.bary, m);
+  const size_t par = static_cast<size_t>(first) + cand;
+  out[par * P.n_tets + tet] = make_float4(m[0], m[1], m[2], tet_mean_h(rec + par * P.n_tets * 2, tet));
 }
 
 // ------------------------------------------------------------ prescreen
@@ -515,9 +594,20 @@ __global__ void k_parent_means(ProblemView P, const float* pts, int n, FeatureIn
 // that sum to it in the FP32 accumulator); layer 2's accumulators start at b2.
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
+typedef int i4v __attribute__((ext_vector_type(4)));
+
+// Read-only for the kernel and the same for a wave: scalar loads.
+typedef const __attribute__((address_space(4))) i4v* TetPtr;
+typedef const __attribute__((address_space(4))) float* StatPtr;
 
 constexpr int kPreIn = 32;                 // features padded: 23 + three constant 1s + zeros
-constexpr int kTetRun = 8;                 // tets per pre-screen work item
+constexpr int kPreCands = 64;              // offspring per pre-screen wave: two tiles of the network
+constexpr int kPreWaves = 8;               // per block
+constexpr int kMaxTetRun = 8;              // tets per pre-screen work item
+// Work items that fill the card: 512 blocks of 8 waves.  With fewer, runs are
+// shorter (a wave's tets are a serial chain): 4 offspring of 3,402 tets took
+// 128 us in runs of 8 and take 79 in runs of 1; 64 of 384 tets 85 and 55 us.
+constexpr int kPreItems = 4096;
 constexpr int kW1Row = kPreIn + 8;         // LDS row strides padded against bank conflicts
 constexpr int kW2Row = kHid + 8;
 
@@ -526,6 +616,7 @@ struct alignas(16) PreLds {
   bf16 w2[kHid][kW2Row];   // W2, columns permuted per 16-wide slice
   float b2[kHid];
   float w3[kHid];
+  float4 bary[kPoints];
 };
 
 __device__ __forceinline__ int slot_unit(int j) {   // 16-wide slice: slot j -> unit
@@ -533,15 +624,67 @@ __device__ __forceinline__ int slot_unit(int j) {   // 16-wide slice: slot j -> 
   return kk < 4 ? 4 * h + kk : 8 + 4 * h + (kk - 4);
 }
 
+__device__ __forceinline__ int unit_slot(int u) {   // inverse of slot_unit
+  return u < 8 ? 8 * (u >> 2) + (u & 3) : 8 * ((u - 8) >> 2) + 4 + (u & 3);
+}
+
 __device__ __forceinline__ bf8 ld8(const bf16* p) { return *reinterpret_cast<const bf8*>(p); }
 
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float fl2 __attribute__((ext_vector_type(2)));
+
+// Eight values rounded to BF16 (nearest even, two per instruction).
 __device__ __forceinline__ bf8 pack8(const float v[8]) {
   u4v w;
-  w.x = static_cast<uint32_t>(f2bf(v[0])) | (static_cast<uint32_t>(f2bf(v[1])) << 16);
-  w.y = static_cast<uint32_t>(f2bf(v[2])) | (static_cast<uint32_t>(f2bf(v[3])) << 16);
-  w.z = static_cast<uint32_t>(f2bf(v[4])) | (static_cast<uint32_t>(f2bf(v[5])) << 16);
-  w.w = static_cast<uint32_t>(f2bf(v[6])) | (static_cast<uint32_t>(f2bf(v[7])) << 16);
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const fl2 p = {v[2 * q], v[2 * q + 1]};
+    w[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(p, bf2));
+  }
   return __builtin_bit_cast(bf8, w);
+}
+
+// The network's output without its last bias for a tile of 32 rows whose
+// features are the B operands xb0 (k = 0..15) and xb1 (16..31): this lane's
+// share of the units, to be added to that of lane ^ 32.
+__device__ __forceinline__ float net_tile(const PreLds& N, const bf8 xb0, const bf8 xb1, int i, int h, float inf) {
+  // layer 1: 4 output tiles of 32 units, K = 32 (two slices)
+  bf8 hb[8];
+#pragma unroll
+  for (int n = 0; n < 4; n++) {
+    f16v z = {};
+    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w1[32 * n + i][8 * h]), xb0, z, 0, 0, 0);
+    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w1[32 * n + i][16 + 8 * h]), xb1, z, 0, 0, 0);
+    float v0[8], v1[8];
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+      v0[r] = relu(z[r], inf);
+      v1[r] = relu(z[8 + r], inf);
+    }
+    hb[2 * n] = pack8(v0);
+    hb[2 * n + 1] = pack8(v1);
+  }
+  // layer 2 (K = 128, eight slices) and the output layer
+  float part = 0.f;
+#pragma unroll 1
+  for (int n = 0; n < 4; n++) {
+    f16v z;
+#pragma unroll
+    for (int r = 0; r < 16; r++) z[r] = N.b2[32 * n + 8 * (r >> 2) + 4 * h + (r & 3)];
+#pragma unroll
+    for (int sl = 0; sl < 8; sl++)
+      z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w2[32 * n + i][16 * sl + 8 * h]), hb[sl], z, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 16; r++) part = fmaf(relu(z[r], inf), N.w3[32 * n + 8 * (r >> 2) + 4 * h + (r & 3)], part);
+  }
+  return part;
+}
+
+// Upper half of a and lower half of b exchanged.
+__device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
 }
 
 // Score of each offspring: the predicted intensity objective,
@@ -549,174 +692,181 @@ __device__ __forceinline__ bf8 pack8(const float v[8]) {
 // parent_tet the parent's exact mean term (FP32, from its records), pred_tet
 // the network's predicted change (in units of h_scale) and w_tet the
 // offspring's |volume| of the tet's source plus that of its target (voxel^3,
-// the samples the tet contributes in the two directions).  Blocks of 4 waves loop over candidates; each wave takes tiles of
-// 32 tets; fixed-order reductions.
-__global__ __launch_bounds__(256, 3) void k_prescreen(ProblemView P, const float* pts, Parents Q, FeatureInputs F,
-                                                    const float4* pmeans, const float* params, int pop,
-                                                    float2* partial) {
+// the samples the tet contributes in the two directions).  A wave takes a run
+// of tets of 64 offspring, one offspring per lane: it samples the images and
+// forms the features, which half-wave exchanges turn into the B operands of
+// two tiles of the network.
+//
+// What bounds it: the 104 gathers of a tet's 26 points in two images (about
+// 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) and the
+// 2,500 vector instructions around them, 78% of the issue slots.  128x128x96
+// (3,402 tets), 4,096 offspring: 3,390 us with coordinates read as stored (a
+// line per lane for each of 36 words), half a tet's points per half wave and 3
+// waves per SIMD; 1,580 us with coordinates by columns (k_columns, 44 us);
+// 1,275 us with 4 waves per SIMD (blocks of 8: the weights' 46 KiB of LDS
+// allow two) and one-instruction ReLUs; 1,140 us as it stands, with both
+// points and coordinates of 64 offspring per load and quads of differences.
+template <bool kBig>
+__global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, const float* cols,
+                                                                 const int* parent_of, int n_parents,
+                                                                 FeatureInputs F, const float4* pmeans,
+                                                                 const float* params, const bf16* w1b,
+                                                                 const bf16* w2b, int n, int tet_run,
+                                                                 float2* partial, int stride) {
   __shared__ PreLds N;
-  for (int e = threadIdx.x; e < kHid * kPreIn; e += blockDim.x) {
-    const int j = e / kPreIn, k = e % kPreIn;
-    if (k < kIn) {
-      N.w1[j][k] = f2bf(params[oW1 + j * kIn + k]);
-    } else if (k < kIn + 3) {
-      // b1 = hi + mid + lo, three BF16 terms carrying its 24-bit mantissa
-      const float b = params[oB1 + j];
-      const bf16 hi = f2bf(b), mid = f2bf(b - bf2f(hi)), lo = f2bf(b - bf2f(hi) - bf2f(mid));
-      N.w1[j][k] = k == kIn ? hi : (k == kIn + 1 ? mid : lo);
-    } else {
-      N.w1[j][k] = 0;
-    }
+  constexpr int kThreads = 64 * kPreWaves;
+#pragma unroll
+  for (int e0 = 0; e0 < kHid * kPreIn / 4; e0 += kThreads) {
+    const int e = e0 + threadIdx.x, j = e / (kPreIn / 4), k0 = e % (kPreIn / 4) * 4;
+    const s4 zero = {0, 0, 0, 0};
+    *reinterpret_cast<s4*>(&N.w1[j][k0]) = k0 < kInPad ? ld4(w1b + j * kInPad + k0) : zero;
   }
-  for (int e = threadIdx.x; e < kHid * kHid; e += blockDim.x) {
-    const int j = e / kHid, k = e % kHid;
-    N.w2[j][k] = f2bf(params[oW2 + j * kHid + (k & ~15) + slot_unit(k & 15)]);
+#pragma unroll
+  for (int e0 = 0; e0 < kHid * kHid / 4; e0 += kThreads) {
+    const int e = e0 + threadIdx.x, j = e / (kHid / 4), k0 = e % (kHid / 4) * 4;
+    // four units of a slice are four slots in a row
+    *reinterpret_cast<s4*>(&N.w2[j][(k0 & ~15) + unit_slot(k0 & 15)]) = ld4(w2b + j * kHid + k0);
   }
-  for (int e = threadIdx.x; e < kHid; e += blockDim.x) {
-    N.b2[e] = params[oB2 + e];
-    N.w3[e] = params[oW3 + e];
+  if (threadIdx.x < kPoints) N.bary[threadIdx.x] = F.bary[threadIdx.x];
+  float b1 = 0.f;
+  if (threadIdx.x < kHid) {
+    b1 = params[oB1 + threadIdx.x];
+    N.b2[threadIdx.x] = params[oB2 + threadIdx.x];
+    N.w3[threadIdx.x] = params[oW3 + threadIdx.x];
   }
-  const float b3 = params[oB3];
+  const float b3 = params[oB3], inf = inf_reg();
+  __syncthreads();
+  if (threadIdx.x < kHid) {
+    // b1 = hi + mid + lo, three BF16 terms carrying its 24-bit mantissa
+    const bf16 hi = f2bf(b1), mid = f2bf(b1 - bf2f(hi)), lo = f2bf(b1 - bf2f(hi) - bf2f(mid));
+    N.w1[threadIdx.x][kIn] = hi;
+    N.w1[threadIdx.x][kIn + 1] = mid;
+    N.w1[threadIdx.x][kIn + 2] = lo;
+  }
   __syncthreads();
   const int wave = threadIdx.x >> 6, lane = lane_id(), i = lane & 31, h = lane >> 5;
-  const int n_groups = (pop + kRowTile - 1) / kRowTile;
-  const int n_runs = (P.n_tets + kTetRun - 1) / kTetRun;
+  const int n_groups = (n + kPreCands - 1) / kPreCands;
+  const int n_runs = (P.n_tets + tet_run - 1) / tet_run;
   const long long n_items = static_cast<long long>(n_runs) * n_groups;
-  const long long n_waves = static_cast<long long>(gridDim.x) * 4;
-  // work items (run of kTetRun tets, group of 32 offspring), run-major, one
-  // per wave at a time: a tile of the network is one tet of 32 offspring, so
-  // the lanes of a wave read nearly the same image positions and the waves
-  // in flight share a few runs of tets
-  for (long long w = static_cast<long long>(blockIdx.x) * 4 + wave; w < n_items; w += n_waves) {
-    const int run = static_cast<int>(w / n_groups), grp = static_cast<int>(w % n_groups);
-    const int cand = grp * kRowTile + i;
-    const int par = cand < pop ? Q.of[cand] : -1;
-    const bool ok = par >= 0 && par < Q.n;   // no parent: scored by the reduction
-    const float* cp = pts + static_cast<size_t>(ok ? cand : 0) * 6 * P.n_points;
-    const float* pp = Q.pts + static_cast<size_t>(ok ? par : 0) * 6 * P.n_points;
-    const Record* prec = Q.rec + static_cast<size_t>(ok ? par : 0) * P.n_tets * 2;
+  const long long n_waves = static_cast<long long>(gridDim.x) * kPreWaves;
+  const TetPtr tets = (TetPtr)P.tets;
+  const StatPtr stats = (StatPtr)F.stats;
+  // work items (run of tets, group of 64 offspring), run-major, one per wave
+  // at a time: the lanes of a wave read nearly the same image positions and
+  // the waves in flight share a few runs of tets
+  for (long long w = static_cast<long long>(blockIdx.x) * kPreWaves + wave; w < n_items; w += n_waves) {
+    const int run = __builtin_amdgcn_readfirstlane(static_cast<int>(w / n_groups));
+    const int grp = __builtin_amdgcn_readfirstlane(static_cast<int>(w % n_groups));
+    const int cand = grp * kPreCands + lane;
+    const int par = cand < n ? parent_of[cand] : -1;
+    const bool ok = par >= 0 && par < n_parents;   // no parent: scored by the reduction
+    if (__ballot(ok) == 0) {
+      if (cand < n) partial[static_cast<size_t>(run) * stride + cand] = make_float2(0.f, 0.f);
+      continue;
+    }
+    const unsigned col = cand < n ? cand : 0;
     const float4* pmr = pmeans + static_cast<size_t>(ok ? par : 0) * P.n_tets;
     float acc_s = 0.f, cnt = 0.f;
-    const int t_end = min(P.n_tets, (run + 1) * kTetRun);
-    for (int tet = run * kTetRun; tet < t_end; tet++) {
-      // this lane's half of the tet's features (natural order: 12 vertex
-      // moves, 3 estimated changes, 7 statistics, the parent's mean term,
-      // three constant 1s, zeros): h = 0 holds features 0..7 and 16..23,
-      // h = 1 features 8..15 and 24..31.  The offspring's 26 points behind
-      // the estimated changes are split over the halves (h = 0 points
-      // 0..12, h = 1 points 13..25) and combined in the upper half, which
-      // subtracts the parent's means computed beforehand.
-      float f0[8], f1[8];
-#pragma unroll
-      for (int k = 0; k < 8; k++) f0[k] = f1[k] = 0.f;
-      float acc[3] = {0.f, 0.f, 0.f};
-      float pterm = 0.f, wt = 0.f;
-      float4 pm = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ok) {
-        float d[4][3], dp[4][3];
-        tet_vertices(P, cp, tet, 1, d);
-        tet_vertices(P, pp, tet, 1, dp);
-        {
-          float sv[4][3];
-          tet_vertices(P, cp, tet, 0, sv);
-          point_sums(P, F.img_s, F.img_t, sv, d, F.bary, h == 0 ? 0 : kPointSplit, h == 0 ? kPointSplit : kPoints,
-                     acc);
-        }
-        if (h == 1) pm = pmr[tet];
-        if (h == 0) {
-#pragma unroll
-          for (int k = 0; k < 8; k++) {
-            const int v = k / 3, a = k % 3;
-            f0[k] = (d[v][a] - dp[v][a]) * kRelScale;
-          }
-#pragma unroll
-          for (int k = 0; k < 5; k++) f1[k] = F.stats[8 * tet + 1 + k];
-          f1[5] = F.stats[8 * tet + 6] * F.inv_h;
-          pterm = tet_mean_h(prec, tet);
-          f1[6] = pterm * F.inv_h;
-          f1[7] = 1.f;   // the first term of b1
-          wt = tet_weight(P, cp, tet);
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; k++) {
-            const int fk = 8 + k, v = fk / 3, a = fk % 3;
-            f0[k] = (d[v][a] - dp[v][a]) * kRelScale;
-          }
-          f0[7] = F.stats[8 * tet];
-          f1[0] = f1[1] = 1.f;   // the other two terms of b1
-        }
-      }
+    const int t_end = min(P.n_tets, (run + 1) * tet_run);
+    for (int tet = run * tet_run; tet < t_end; tet++) {
+      const i4v tq = tets[tet];
+      const int4 tv = make_int4(tq.x, tq.y, tq.z, tq.w);
+      const float4 pm = pmr[tet];
+      // features in order: 12 vertex moves, 3 estimated changes, 7
+      // statistics, the parent's mean term, three constant 1s for the terms
+      // of b1, zeros
+      float f[4][8];
+      float wt;
       {
-        float lo[3], m[3];
+        float rel[4][3];
+        column_vertices<9>(cols, tv, 6, n, col, rel);
 #pragma unroll
-        for (int k = 0; k < 3; k++) lo[k] = __shfl_xor(acc[k], 32, 64);
-        if (h == 1) {
-          combine_means(lo, acc, m);
-          f0[4] = (m[0] - pm.x) * F.inv_h;
-          f0[5] = (m[1] - pm.y) * F.inv_h;
-          f0[6] = (m[2] - pm.z) * F.inv_h;
-        }
+        for (int k = 0; k < 12; k++) f[k / 8][k % 8] = rel[k / 3][k % 3] * kRelScale;
       }
-      const bf8 xb0 = pack8(f0), xb1 = pack8(f1);
-      // layer 1: 4 output tiles of 32 units, K = 32 (two slices)
-      bf8 hb[8];
-#pragma unroll
-      for (int n = 0; n < 4; n++) {
-        f16v z = {};
-        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w1[32 * n + i][8 * h]), xb0, z, 0, 0, 0);
-        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w1[32 * n + i][16 + 8 * h]), xb1, z, 0, 0, 0);
-        float v0[8], v1[8];
-#pragma unroll
-        for (int r = 0; r < 8; r++) {
-          v0[r] = fmaxf(z[r], 0.f);
-          v1[r] = fmaxf(z[8 + r], 0.f);
-        }
-        hb[2 * n] = pack8(v0);
-        hb[2 * n + 1] = pack8(v1);
+      const bf8 x0 = pack8(f[0]);
+      {
+        float sv[4][3], d[4][3], m[3];
+        column_vertices<9>(cols, tv, 0, n, col, sv);
+        column_vertices<9>(cols, tv, 3, n, col, d);
+        wt = tet_volume(sv) + tet_volume(d);
+        asm volatile("" : "+v"(wt));   // here, or the vertices stay in registers through the network
+        point_means<kBig>(P, F.img_s, F.img_t, sv, d, N.bary, m);
+        f[1][4] = (m[0] - pm.x) * F.inv_h;
+        f[1][5] = (m[1] - pm.y) * F.inv_h;
+        f[1][6] = (m[2] - pm.z) * F.inv_h;
       }
-      // layer 2 (K = 128, eight slices) and the output layer
-      float part = 0.f;
-#pragma unroll 1
-      for (int n = 0; n < 4; n++) {
-        f16v z;
+      const StatPtr st = stats + 8 * static_cast<size_t>(tet);
+      f[1][7] = st[0];
 #pragma unroll
-        for (int r = 0; r < 16; r++) z[r] = N.b2[32 * n + 8 * (r >> 2) + 4 * h + (r & 3)];
+      for (int k = 0; k < 5; k++) f[2][k] = st[1 + k];
+      f[2][5] = st[6] * F.inv_h;
+      f[2][6] = pm.w * F.inv_h;
+      f[2][7] = f[3][0] = f[3][1] = 1.f;
 #pragma unroll
-        for (int sl = 0; sl < 8; sl++)
-          z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld8(&N.w2[32 * n + i][16 * sl + 8 * h]), hb[sl], z, 0, 0,
-                                                      0);
+      for (int k = 2; k < 8; k++) f[3][k] = 0.f;
+      // lane l of a B operand holds row l % 32 and 8 of 16 k values by its
+      // half: with the halves of features 0..7 and 8..15 exchanged, the
+      // former are the first slice of offspring 0..31, the latter that of
+      // offspring 32..63; likewise 16..23 and 24..31 the second slice
+      u4v a = __builtin_bit_cast(u4v, x0), b = __builtin_bit_cast(u4v, pack8(f[1]));
+      u4v c = __builtin_bit_cast(u4v, pack8(f[2])), e = __builtin_bit_cast(u4v, pack8(f[3]));
 #pragma unroll
-        for (int r = 0; r < 16; r++)
-          part = fmaf(fmaxf(z[r], 0.f), N.w3[32 * n + 8 * (r >> 2) + 4 * h + (r & 3)], part);
+      for (int q = 0; q < 4; q++) {
+        unsigned u = a[q], v = b[q];
+        swap_halves(u, v);
+        a[q] = u;
+        b[q] = v;
+        u = c[q];
+        v = e[q];
+        swap_halves(u, v);
+        c[q] = u;
+        e[q] = v;
       }
-      const float y = part + __shfl_xor(part, 32, 64) + b3;   // the two halves hold different units
-      if (h == 0 && ok) {
-        // the parent's exact term plus the predicted change, weighted by the
-        // offspring's expected samples of the tet
-        acc_s = fmaf(wt, fmaf(y, F.h_scale, pterm), acc_s);
-        cnt += wt;
-      }
+      float y0 = net_tile(N, __builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, c), i, h, inf);
+      float y1 = net_tile(N, __builtin_bit_cast(bf8, b), __builtin_bit_cast(bf8, e), i, h, inf);
+      unsigned s0 = __float_as_uint(y0), s1 = __float_as_uint(y1);
+      swap_halves(s0, s1);   // both shares of this lane's own offspring
+      const float y = __uint_as_float(s0) + __uint_as_float(s1) + b3;
+      // the parent's exact term plus the predicted change, weighted by the
+      // offspring's expected samples of the tet
+      acc_s = fmaf(wt, fmaf(y, F.h_scale, pm.w), acc_s);
+      cnt += wt;
     }
-    if (h == 0 && cand < pop) partial[static_cast<size_t>(run) * pop + cand] = make_float2(acc_s, cnt);
+    if (cand < n) partial[static_cast<size_t>(run) * stride + cand] = make_float2(acc_s, cnt);
   }
 }
 
-// Scores from the per-(run, offspring) partial sums, added in run order.
-__global__ void k_prescreen_reduce(const float2* partial, int n_runs, int pop, Parents Q, float* score) {
-  const int cand = blockIdx.x * blockDim.x + threadIdx.x;
-  if (cand >= pop) return;
-  const int par = Q.of[cand];
-  if (par < 0 || par >= Q.n) {   // no parent: never preferred
-    score[cand] = INFINITY;
-    return;
-  }
+// Scores from the per-(run, offspring) partial sums: 16 threads an offspring
+// take a share of the runs each, in order (a single chain of 426 loads took
+// 106 us for 4,096 offspring, bound by their latency), then the shares in
+// order.
+constexpr int kScoreGroups = 16;
+
+__global__ __launch_bounds__(64 * kScoreGroups) void k_prescreen_reduce(const float2* partial, int n_runs, int pop,
+                                                                       Parents Q, float* score) {
+  __shared__ float2 s_sum[kScoreGroups][64];
+  const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int cand = blockIdx.x * 64 + col;
+  const int per = (n_runs + kScoreGroups - 1) / kScoreGroups, t1 = min(n_runs, (grp + 1) * per);
   float a = 0.f, c = 0.f;
-  for (int t = 0; t < n_runs; t++) {
-    const float2 v = partial[static_cast<size_t>(t) * pop + cand];
-    a += v.x;
-    c += v.y;
+  if (cand < pop) {
+#pragma unroll 8
+    for (int t = grp * per; t < t1; t++) {
+      const float2 v = partial[static_cast<size_t>(t) * pop + cand];
+      a += v.x;
+      c += v.y;
+    }
   }
-  score[cand] = c > 0.f ? a / c : 0.f;
+  s_sum[grp][col] = make_float2(a, c);
+  __syncthreads();
+  if (grp != 0 || cand >= pop) return;
+  for (int q = 1; q < kScoreGroups; q++) {
+    a += s_sum[q][col].x;
+    c += s_sum[q][col].y;
+  }
+  const int par = Q.of[cand];
+  // no parent: never preferred
+  score[cand] = par < 0 || par >= Q.n ? INFINITY : (c > 0.f ? a / c : 0.f);
 }
 
 // Predictions for explicit feature rows (one wave per 32 rows).
@@ -772,10 +922,6 @@ constexpr int kTrainWaves = 4;
 constexpr int kTrainBlocks = 256;                          // one per compute unit
 constexpr int kXRow = kRowTile + 8;
 
-__device__ __forceinline__ int unit_slot(int u) {   // inverse of slot_unit
-  return u < 8 ? 8 * (u >> 2) + (u & 3) : 8 * ((u - 8) >> 2) + 4 + (u & 3);
-}
-
 struct alignas(16) TrainLds {
   bf16 w1[kHid][kW1Row];                   // W1[j][k], zeros beyond the features
   union {
@@ -796,9 +942,6 @@ struct alignas(16) TrainLds {
   };
 };
 static_assert(sizeof(TrainLds) <= 160 * 1024, "one block's LDS");
-
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-typedef float fl2 __attribute__((ext_vector_type(2)));
 
 // Accumulators 8 g .. 8 g + 7 as one operand fragment (rounded to BF16).
 __device__ __forceinline__ bf8 pack_acc(const f16v& z, int g) {
@@ -833,6 +976,7 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, c
                                                               const bf16* w1b, const bf16* w2b, const float* params,
                                                               float* part) {
   __shared__ TrainLds S;
+  const float inf = inf_reg();
   constexpr int kThreads = 64 * kTrainWaves;
 #pragma unroll
   for (int e0 = 0; e0 < kHid * kPreIn / 4; e0 += kThreads) {
@@ -914,8 +1058,8 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, c
       u = mma16(xb[1], w1, mma16(xb[0], w0, u));
 #pragma unroll
       for (int r = 0; r < 16; r++) {
-        z[r] = fmaxf(z[r], 0.f);
-        u[r] = fmaxf(u[r], 0.f);
+        z[r] = relu(z[r], inf);
+        u[r] = relu(u[r], inf);
       }
 #pragma unroll
       for (int g = 0; g < 2; g++) {
@@ -941,7 +1085,7 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, c
       }
       const f16v w3 = acc_rows(S.w3 + 32 * a, h);
 #pragma unroll
-      for (int r = 0; r < 16; r++) y = fmaf(fmaxf(zt[a][r], 0.f), w3[r], y);
+      for (int r = 0; r < 16; r++) y = fmaf(relu(zt[a][r], inf), w3[r], y);
     }
     y += __shfl_xor(y, 32, 64) + b3;
     const float diff = i < rows ? y - target : 0.f;
@@ -963,7 +1107,7 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(const float* X, c
       for (int r = 0; r < 16; r++) {
         zt[a][r] = zt[a][r] > 0.f ? dy * w3r[r] : 0.f;
         const float z = zu[a][r], dz = z > 0.f ? dyr[r] * w3 : 0.f;
-        gw3[a] = fmaf(dyr[r], fmaxf(z, 0.f), gw3[a]);
+        gw3[a] = fmaf(dyr[r], relu(z, inf), gw3[a]);
         gb2[a] += dz;
         zu[a][r] = dz;
       }
@@ -1168,7 +1312,7 @@ struct morea_surrogate {
   float* ref = nullptr;
   float4* img_s = nullptr;  // quad copies of the source and target images
   float4* img_t = nullptr;
-  float4* bary = nullptr;   // [16] interior sample points of a tet, barycentric
+  float4* bary = nullptr;   // [kPoints] sample points of a tet, barycentric
   float h_scale = 1.f;      // mean of (I_s - I_t)^2 over the grid (1 when 0)
   void* work = nullptr;     // pre-screen workspace: the parents' point means,
   size_t work_cap = 0;      // then the per-(tile, offspring) partial sums (bytes)
@@ -1237,12 +1381,19 @@ double radical_inverse(int j, int b) {
   return r;
 }
 
-// The interior sample points: Halton points j = 1..16 in bases 2, 3, 5,
-// each (u1, u2, u3) sorted into a <= b <= c and mapped to the barycentric
-// coordinates (a, b - a, c - b, 1 - c) (the spacings of sorted uniforms,
-// uniform on the simplex).
-std::vector<float4> interior_points() {
+// A tet's sample points as barycentric coordinates: the vertices, the edge
+// midpoints, then Halton points j = 1..16 in bases 2, 3, 5, each (u1, u2, u3)
+// sorted into a <= b <= c and mapped to (a, b - a, c - b, 1 - c) (the spacings
+// of sorted uniforms, uniform on the simplex).
+std::vector<float4> sample_points() {
   std::vector<float4> out;
+  float l[4];
+  for (int v = 0; v < 4; v++) out.push_back(make_float4(v == 0, v == 1, v == 2, v == 3));
+  for (int v = 0; v < 4; v++)
+    for (int w = v + 1; w < 4; w++) {
+      for (int k = 0; k < 4; k++) l[k] = k == v || k == w ? 0.5f : 0.f;
+      out.push_back(make_float4(l[0], l[1], l[2], l[3]));
+    }
   for (int j = 1; j <= kHalton; j++) {
     double u[3] = {radical_inverse(j, 2), radical_inverse(j, 3), radical_inverse(j, 5)};
     std::sort(u, u + 3);
@@ -1251,6 +1402,9 @@ std::vector<float4> interior_points() {
   }
   return out;
 }
+
+// The quad copies reach 4 GiB: sampled with 64-bit offsets.
+bool big_quads(const ProblemView& P) { return P.pvox >= 1u << 28; }
 
 FeatureInputs feature_inputs(const morea_surrogate* s) {
   return FeatureInputs{s->img_s, s->img_t, s->bary, s->stats, s->h_scale, 1.f / s->h_scale};
@@ -1308,7 +1462,7 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
   ok(salloc(s, &s->ref, sizeof(float) * 3 * p->view.n_points));
   ok(salloc(s, &s->img_s, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
   ok(salloc(s, &s->img_t, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
-  ok(salloc(s, &s->bary, sizeof(float4) * kHalton));
+  ok(salloc(s, &s->bary, sizeof(float4) * kPoints));
   float* ref_dev = s->ref;
   if (st == MOREA_OK) {
     // He-normal initial weights, zero biases, from the given seed
@@ -1329,8 +1483,8 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
     ok(sdev(hipGetLastError(), "refresh"));
     ok(sdev(launch_stats(s, ref_dev), "tet statistics"));
     ok(sdev(launch_image_copies(s), "image copies"));
-    const std::vector<float4> bary = interior_points();
-    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kHalton, hipMemcpyHostToDevice), "upload"));
+    const std::vector<float4> bary = sample_points();
+    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kPoints, hipMemcpyHostToDevice), "upload"));
     ok(sdev(hipDeviceSynchronize(), "surrogate set-up"));
   }
   if (st == MOREA_OK) {
@@ -1375,8 +1529,12 @@ morea_status morea_surrogate_features(morea_surrogate* s, const float* pts, int3
     return sfail(MOREA_EINVAL, "NULL argument");
   if (rows > (1LL << 31) / 4) return sfail(MOREA_ERANGE, "too many rows");
   const Parents Q{parent_pts, static_cast<const Record*>(parent_cache), parent_of, n_parents};
-  hipLaunchKernelGGL(k_features, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), s->p->view, pts, Q, feature_inputs(s), pop, feats);
+  const dim3 grid(static_cast<unsigned>((rows + 255) / 256));
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (big_quads(s->p->view))
+    hipLaunchKernelGGL(k_features<true>, grid, dim3(256), 0, st, s->p->view, pts, Q, feature_inputs(s), pop, feats);
+  else
+    hipLaunchKernelGGL(k_features<false>, grid, dim3(256), 0, st, s->p->view, pts, Q, feature_inputs(s), pop, feats);
   return sdev(hipGetLastError(), "features");
 }
 
@@ -1424,10 +1582,18 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   if (!pts || !score || !parent_of || (n_parents > 0 && (!parent_pts || !parent_cache)))
     return sfail(MOREA_EINVAL, "NULL argument");
   const ProblemView& P = s->p->view;
-  const int n_runs = (P.n_tets + kTetRun - 1) / kTetRun;
+  // tets per work item: as many as leave kPreItems items, at most kMaxTetRun
+  const long long groups = (static_cast<long long>(pop) + kPreCands - 1) / kPreCands;
+  const int tet_run = static_cast<int>(std::max(1ll, std::min<long long>(kMaxTetRun, P.n_tets * groups / kPreItems)));
+  const int n_runs = (P.n_tets + tet_run - 1) / tet_run;
   const size_t rows = static_cast<size_t>(n_parents) * P.n_tets;
   const size_t pm_bytes = (sizeof(float4) * rows + 255) / 256 * 256;
-  const size_t need = pm_bytes + sizeof(float2) * static_cast<size_t>(n_runs) * pop;
+  const size_t part_bytes = (sizeof(float2) * static_cast<size_t>(n_runs) * pop + 255) / 256 * 256;
+  // candidates laid out by columns at a time: all, unless that exceeds kColBytes
+  const size_t cand_bytes = 9 * sizeof(float) * static_cast<size_t>(P.n_points);
+  const int slab = static_cast<int>(std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands));
+  const size_t need = pm_bytes + part_bytes +
+                      std::max(cand_bytes * std::min(slab, pop), cand_bytes / 9 * 6 * std::min(slab, n_parents));
   if (need > s->work_cap) {   // grow the workspace (hipFree waits for the device)
     if (s->work) (void)hipFree(s->work);
     s->work = nullptr;
@@ -1440,16 +1606,37 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   }
   float4* pmeans = static_cast<float4*>(s->work);
   float2* partial = reinterpret_cast<float2*>(static_cast<char*>(s->work) + pm_bytes);
+  float* cols = reinterpret_cast<float*>(static_cast<char*>(s->work) + pm_bytes + part_bytes);
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const FeatureInputs F = feature_inputs(s);
-  if (rows > 0)
-    hipLaunchKernelGGL(k_parent_means, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0, st, P,
-                       parent_pts, n_parents, F, pmeans);
   const Parents Q{parent_pts, static_cast<const Record*>(parent_cache), parent_of, n_parents};
-  const long long items = static_cast<long long>(n_runs) * ((pop + kRowTile - 1) / kRowTile);
-  const int blocks = static_cast<int>(std::min<long long>((items + 3) / 4, 768));
-  hipLaunchKernelGGL(k_prescreen, dim3(blocks), dim3(256), 0, st, P, pts, Q, F, pmeans, s->params, pop, partial);
-  hipLaunchKernelGGL(k_prescreen_reduce, dim3((pop + 255) / 256), dim3(256), 0, st, partial, n_runs, pop, Q, score);
+  const unsigned col_tiles = static_cast<unsigned>((P.n_points + kColPoints - 1) / kColPoints);
+  for (int first = 0; first < n_parents; first += slab) {
+    const int n = std::min(slab, n_parents - first);
+    hipLaunchKernelGGL(k_columns<6>, dim3(col_tiles, (n + kColCands - 1) / kColCands, 6), dim3(256), 0, st, parent_pts,
+                       first, n, P.n_points, Q, cols);
+    const dim3 grid(static_cast<unsigned>((static_cast<size_t>(n) * P.n_tets + 255) / 256));
+    if (big_quads(P))
+      hipLaunchKernelGGL(k_parent_means<true>, grid, dim3(256), 0, st, P, cols, first, n, Q.rec, F, pmeans);
+    else
+      hipLaunchKernelGGL(k_parent_means<false>, grid, dim3(256), 0, st, P, cols, first, n, Q.rec, F, pmeans);
+  }
+  for (int first = 0; first < pop; first += slab) {
+    const int n = std::min(slab, pop - first);
+    hipLaunchKernelGGL(k_columns<9>, dim3(col_tiles, (n + kColCands - 1) / kColCands, 6), dim3(256), 0, st, pts, first,
+                       n, P.n_points, Q, cols);
+    const long long items = static_cast<long long>(n_runs) * ((n + kPreCands - 1) / kPreCands);
+    const dim3 grid(static_cast<unsigned>(std::min<long long>((items + kPreWaves - 1) / kPreWaves, kPreItems / kPreWaves)));
+    const dim3 block(64 * kPreWaves);
+    if (big_quads(P))
+      hipLaunchKernelGGL(k_prescreen<true>, grid, block, 0, st, P, cols, parent_of + first, n_parents, F, pmeans,
+                         s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
+    else
+      hipLaunchKernelGGL(k_prescreen<false>, grid, block, 0, st, P, cols, parent_of + first, n_parents, F, pmeans,
+                         s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
+  }
+  hipLaunchKernelGGL(k_prescreen_reduce, dim3((pop + 63) / 64), dim3(64 * kScoreGroups), 0, st, partial, n_runs, pop,
+                     Q, score);
   return sdev(hipGetLastError(), "prescreen");
 }
 
