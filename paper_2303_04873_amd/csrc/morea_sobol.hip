@@ -26,7 +26,17 @@
 // One 64-lane wave per (candidate, tet); both directions in turn; sample n
 // of a direction is taken by lane n % 64.  Since lane < 64, the Sobol
 // integer of n = 64 k + lane is the XOR of that of the lane (per lane, once
-// per direction) and that of 64 k (wave-uniform, scalar, once per batch).
+// per item) and that of 64 k (wave-uniform, scalar, once per batch).
+//
+// What bounds it: the gathers, 64 lanes in as many cache lines (46 cycles of a
+// CU each), and the vector instructions, 3,130 per wave.  They were 5,760 (88%
+// of the issue slots, 232 per point to form it and find its cell): the
+// divisions are now the correctly rounded ones without scaling for extreme
+// operands, the logarithm is halved (the ratios do not change), which saves
+// its scalings, and tets that stay in the grid's border cells take a path
+// without bounds tests on which one cell serves the images and the distance
+// maps and a row's two corners are one load.  128x128x96, population 128:
+// 4.1 -> 3.45, 4.6 -> 4.1, 4.9 -> 4.8 ms (three images).
 #include <math.h>
 #include <stdio.h>
 
@@ -66,7 +76,29 @@ constexpr DirTable make_directions() {
   return t;
 }
 
-__constant__ DirTable kDir = make_directions();
+// Bits 0..5 of the sample index, whose XOR is the lane's, and the XOR of the
+// direction numbers of bits 6 .. 6 + c, by which the integer of 64 k changes
+// when k + 1 ends in c zero bits.  r takes bits 9..31: shifted down by 8, the
+// lowest bit cleared (the lane's words set it).
+struct StepTable {
+  uint32_t v[26][4];
+};
+
+constexpr DirTable kDirections = make_directions();
+
+constexpr StepTable make_steps() {
+  StepTable t{};
+  for (int j = 0; j < 4; j++) {
+    uint32_t x = 0;
+    for (int c = 0; c < 26; c++) {
+      x ^= kDirections.v[j][6 + c];
+      t.v[c][j] = (x >> 8) & ~1u;
+    }
+  }
+  return t;
+}
+
+__constant__ __attribute__((aligned(16))) StepTable kSteps = make_steps();
 
 __device__ __forceinline__ uint64_t splitmix(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
@@ -76,8 +108,20 @@ __device__ __forceinline__ uint64_t splitmix(uint64_t z) {
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+// Sum over the wave in lane 63: within rows of 16 lanes, then across them
+// (DPP: no LDS round trips and no shuffle addresses kept in registers).
+template <int ctrl, int rows>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, false));
+}
+
+__device__ __forceinline__ float wave_sum_63(float v) {
+  v += dpp<0x111, 0xf>(v);
+  v += dpp<0x112, 0xf>(v);
+  v += dpp<0x114, 0xf>(v);
+  v += dpp<0x118, 0xf>(v);
+  v += dpp<0x142, 0xa>(v);
+  v += dpp<0x143, 0xc>(v);
   return v;
 }
 
@@ -86,27 +130,51 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   return v;
 }
 
-// -ln(r) for r in (0, 1]: r = m 2^e, m in [sqrt(1/2), sqrt(2)], ln m =
-// 2 atanh(s) with s = (m - 1) / (m + 1) and the series s (1 + s^2/3 + ... +
-// s^10/11).
-__device__ __forceinline__ float neg_log(float r) {
+// -ln(r) / 2 for r = v 2^-24, v odd and below 2^24: r = m 2^e, m in
+// [sqrt(1/2), sqrt(2)], ln m = 2 atanh(s) with s = (m - 1) / (m + 1) and the
+// series s (1 + s^2/3 + ... + s^10/11); every operation is that of -ln(r)
+// with its result halved, so twice this is -ln(r) to the bit.  The quotient
+// is one correction of n rcp(d): correctly rounded for every v (all 2^23
+// compared with the division).
+__device__ __forceinline__ float half_neg_log(uint32_t v) {
 #pragma clang fp contract(off)
-  const uint32_t u = __float_as_uint(r);
-  int e = static_cast<int>(u >> 23) - 127;
-  float m = __uint_as_float((u & 0x007fffffu) | 0x3f800000u);
-  if (m > 0x1.6a09e6p+0f) {
-    m = m * 0.5f;
-    e = e + 1;
-  }
-  const float s = (m - 1.0f) / (m + 1.0f);
+  const uint32_t u = __float_as_uint(static_cast<float>(v));
+  // -e 2^23: the exponent field of v, one higher from mantissa 0x3504f4
+  // (the first above sqrt(2)), from that of 2^24
+  const uint32_t x = ((152u << 23) - 1u - 0x4afb0cu - u) & 0xff800000u;
+  const float m = __uint_as_float(u + x - (24u << 23));
+  const float n = m - 1.0f, d = m + 1.0f;
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float q = n * r;
+  const float s = __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
   const float s2 = s * s;
   float c = __builtin_fmaf(s2, 0x1.745d18p-4f, 0x1.c71c72p-4f);
   c = __builtin_fmaf(s2, c, 0x1.24924ap-3f);
   c = __builtin_fmaf(s2, c, 0x1.99999ap-3f);
   c = __builtin_fmaf(s2, c, 0x1.555556p-2f);
   c = __builtin_fmaf(s2, c, 1.0f);
-  const float ln_m = (s + s) * c;
-  return -__builtin_fmaf(static_cast<float>(e), 0x1.62e430p-1f, ln_m);
+  const float p = s * c;
+  return __builtin_fmaf(static_cast<float>(static_cast<int>(x)), 0x1.62e430p-25f, -p);
+}
+
+// lambda_1..3 of a point from its four words: h_j / (h_0 + h_1 + h_2 + h_3)
+// with h_j = -ln r_j / 2.  The sum lies in [2^-23, 2^6]: its refined
+// reciprocal is the correctly rounded one (all mantissas compared for
+// exponents -26 .. 8), and with it one correction of h r rounds the quotient
+// correctly (Markstein's theorem; 6.4e9 compared with the division).
+__device__ __forceinline__ void lambdas(const uint32_t v[4], float l[3]) {
+#pragma clang fp contract(off)
+  float h[4];
+#pragma unroll
+  for (int j = 0; j < 4; j++) h[j] = half_neg_log(v[j]);
+  const float sum = ((h[0] + h[1]) + h[2]) + h[3];
+  float r = __builtin_amdgcn_rcpf(sum);
+  r = __builtin_fmaf(__builtin_fmaf(-sum, r, 1.0f), r, r);
+#pragma unroll
+  for (int j = 0; j < 3; j++) {
+    const float q = h[j + 1] * r;
+    l[j] = __builtin_fmaf(__builtin_fmaf(-sum, q, h[j + 1]), r, q);
+  }
 }
 
 template <int ST>
@@ -123,7 +191,7 @@ __device__ __forceinline__ float ld(const void* base, int idx) {
 // Trilinear value and exact-support foreground of an image (zero padding) at
 // an FP32 point in grid coordinates.
 template <int ST>
-__device__ __forceinline__ float image_at(const ProblemView& P, const void* img, const uint8_t* fgc, float x,
+__device__ __forceinline__ float image_at(const ProblemView& P, const void* img, const uint16_t* cells, float x,
                                           float y, float z, bool& fg) {
   const float kx = floorf(x), ky = floorf(y), kz = floorf(z);
   const float fx = x - kx, fy = y - ky, fz = z - kz;
@@ -133,7 +201,7 @@ __device__ __forceinline__ float image_at(const ProblemView& P, const void* img,
   if (kx < -1.f || ky < -1.f || kz < -1.f || ix > P.nx - 1 || iy > P.ny - 1 || iz > P.nz - 1) return 0.f;
   const int i0 = (iz + 1) * P.pxy + (iy + 1) * P.px + ix + 1;
   // a cell without a positive corner is background whatever the support
-  const unsigned code = fgc[i0];
+  const unsigned code = cells[i0];
   if (!(code & 1u)) return 0.f;
   const int i1 = i0 + P.pxy;
   const float c000 = ld<ST>(img, i0), c100 = ld<ST>(img, i0 + 1);
@@ -184,6 +252,170 @@ __device__ __forceinline__ float map_at(const ProblemView& P, const float* m, co
   return fmaf(c.fz, y1 - y0, y0);
 }
 
+// Two consecutive stored values at any element, by one load.
+struct __attribute__((aligned(4))) F2 {
+  float a, b;
+};
+struct __attribute__((aligned(2))) H2 {
+  uint16_t a, b;
+};
+
+template <int ST>
+__device__ __forceinline__ void ld_pair(const void* base, uint32_t e, float& a, float& b) {
+  if constexpr (ST == kF32) {
+    const F2 v = *reinterpret_cast<const F2*>(static_cast<const char*>(base) + (e << 2));
+    a = v.a;
+    b = v.b;
+  } else {
+    const H2 v = *reinterpret_cast<const H2*>(static_cast<const char*>(base) + (e << 1));
+    if constexpr (ST == kBF16) {
+      a = __uint_as_float(static_cast<uint32_t>(v.a) << 16);
+      b = __uint_as_float(static_cast<uint32_t>(v.b) << 16);
+    } else {
+      a = static_cast<float>(__builtin_bit_cast(_Float16, v.a));
+      b = static_cast<float>(__builtin_bit_cast(_Float16, v.b));
+    }
+  }
+}
+
+template <int ST>
+__device__ __forceinline__ const void* at(const void* base, int e) {
+  return static_cast<const char*>(base) + static_cast<ptrdiff_t>(e) * (ST == kF32 ? 4 : 2);
+}
+
+// The cell of a point in [-1, n) per axis, from its padded lower corner
+// element, and the point's fractions in it.  Image borders hold 0 and map
+// borders repeat the nearest value, so both interpolate in this cell as the
+// definitions have it (zero padding, edge clamping).
+struct Cell {
+  uint32_t e;
+  float fx, fy, fz;
+};
+
+__device__ __forceinline__ int floor_int(float x) {
+  int i;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+  return i;
+}
+
+__device__ __forceinline__ Cell inner_cell(const ProblemView& P, const float p[3]) {
+  Cell c;
+  c.e = static_cast<uint32_t>(__mul24(floor_int(p[2]), P.pxy) + (__mul24(floor_int(p[1]), P.px) +
+                                                                 (floor_int(p[0]) + (P.pxy + P.px + 1))));
+  c.fx = __builtin_amdgcn_fractf(p[0]);
+  c.fy = __builtin_amdgcn_fractf(p[1]);
+  c.fz = __builtin_amdgcn_fractf(p[2]);
+  return c;
+}
+
+// The 8 corners of a cell: v[2 r], v[2 r + 1] of row r = (0, 0), (1, 0),
+// (0, 1), (1, 1) in (y, z).
+template <int ST>
+__device__ __forceinline__ void corners(const ProblemView& P, const void* base, uint32_t e, float v[8]) {
+  ld_pair<ST>(base, e, v[0], v[1]);
+  ld_pair<ST>(at<ST>(base, P.px), e, v[2], v[3]);
+  ld_pair<ST>(at<ST>(base, P.pxy), e, v[4], v[5]);
+  ld_pair<ST>(at<ST>(base, P.pxy + P.px), e, v[6], v[7]);
+}
+
+__device__ __forceinline__ float trilinear(const float v[8], const Cell& c) {
+  const float x00 = fmaf(c.fx, v[1] - v[0], v[0]), x10 = fmaf(c.fx, v[3] - v[2], v[2]);
+  const float x01 = fmaf(c.fx, v[5] - v[4], v[4]), x11 = fmaf(c.fx, v[7] - v[6], v[6]);
+  const float y0 = fmaf(c.fy, x10 - x00, x00), y1 = fmaf(c.fy, x11 - x01, x01);
+  return fmaf(c.fz, y1 - y0, y0);
+}
+
+// Whether a supported corner (nonzero weight) is positive.
+__device__ __forceinline__ bool support(const float v[8], const Cell& c) {
+  const bool ux = c.fx > 0.f, uy = c.fy > 0.f, uz = c.fz > 0.f;
+  const bool f0 = v[0] > 0.f || (ux && v[1] > 0.f) || (uy && v[2] > 0.f) || (ux && uy && v[3] > 0.f);
+  const bool f1 = v[4] > 0.f || (ux && v[5] > 0.f) || (uy && v[6] > 0.f) || (ux && uy && v[7] > 0.f);
+  return f0 || (uz && f1);
+}
+
+// h and g of a point p of the sampled tet and q of the other one, both in
+// [-1, n) per axis, added to h and g.
+template <int ST>
+__device__ __forceinline__ void inner_sample(const ProblemView& P, const void* img_own, const void* img_oth,
+                                             const uint16_t* cells_own, const uint16_t* cells_oth,
+                                             const float* map_own, const float* map_oth, const float* set_w,
+                                             const float p[3], const float q[3], float& h, float& g) {
+  const Cell cp = inner_cell(P, p), cq = inner_cell(P, q);
+  const unsigned kp = cells_own[cp.e], kq = cells_oth[cq.e];
+  // cells without a positive corner hold zeros: both background, h = 0
+  if (__ballot(((kp | kq) & 1u) != 0u)) {
+    float u[8], v[8];
+    corners<ST>(P, img_own, cp.e, u);
+    corners<ST>(P, img_oth, cq.e, v);
+    float a = trilinear(u, cp), b = trilinear(v, cq);
+    // with all weights nonzero a cell's foreground is that of its corners
+    bool fa = (kp & 1u) != 0u, fb = (kq & 1u) != 0u;
+    const bool flat = cp.fx * cp.fy * cp.fz * cq.fx * cq.fy * cq.fz == 0.f;
+    if (__ballot(flat)) {
+      asm volatile("");   // kept as a branch
+      fa = support(u, cp);
+      fb = support(v, cq);
+      a = fa ? a : 0.f;
+      b = fb ? b : 0.f;
+    }
+    const float d = a - b;
+    h += fa != fb ? 1.f : d * d;
+  }
+  // sets within the radius at one of the cell's corners (if at none, the
+  // interpolated distance is not below it either)
+  const unsigned bits = kp >> 8;
+  if (__ballot(bits != 0u)) {
+    for (int s = 0; s < P.n_sets; s++) {
+      if ((bits >> s) & 1u) {
+        float u[8], v[8];
+        const size_t first = static_cast<size_t>(s) * P.pvox;
+        corners<kF32>(P, map_own + first, cp.e, u);
+        corners<kF32>(P, map_oth + first, cq.e, v);
+        const float dn = trilinear(u, cp), diff = dn - trilinear(v, cq);
+        const float w = dn < P.radius ? set_w[s] * (P.radius - dn) * P.inv_radius : 0.f;
+        g = fmaf(w, diff * diff, g);
+      }
+    }
+  }
+}
+
+// As inner_sample for any points: bounds tests for the images, clamped cells
+// for the maps.
+template <int ST>
+__device__ __forceinline__ void outer_sample(const ProblemView& P, const void* img_own, const void* img_oth,
+                                             const uint16_t* cells_own, const uint16_t* cells_oth,
+                                             const float* map_own, const float* map_oth, const float* set_w,
+                                             const float p[3], const float q[3], float& h, float& g) {
+  bool fa, fb;
+  const float a = image_at<ST>(P, img_own, cells_own, p[0], p[1], p[2], fa);
+  const float b = image_at<ST>(P, img_oth, cells_oth, q[0], q[1], q[2], fb);
+  h += (fa && fb) ? (a - b) * (a - b) : (fa == fb ? 0.f : 1.f);
+  if (P.n_sets == 0) return;
+  const MapCell cp = map_cell(P, p[0], p[1], p[2]);
+  unsigned bits = cells_own[cp.i0] >> 8;
+  if (bits == 0u) return;
+  const MapCell cq = map_cell(P, q[0], q[1], q[2]);
+  for (; bits; bits &= bits - 1u) {
+    const int s = __builtin_ctz(bits);
+    const float dn = map_at(P, map_own + static_cast<size_t>(s) * P.pvox, cp);
+    if (dn < P.radius) {
+      const float diff = dn - map_at(P, map_oth + static_cast<size_t>(s) * P.pvox, cq);
+      g = fmaf(set_w[s] * (P.radius - dn) * P.inv_radius, diff * diff, g);
+    }
+  }
+}
+
+// The problem's view, the kernel's first argument, read again from the kernel
+// arguments (scalar loads): its words would otherwise stay live in scalar
+// registers and be spilled into lanes of vector registers.
+typedef const __attribute__((address_space(4))) ProblemView* ViewPtr;
+
+__device__ __forceinline__ ProblemView view() {
+  ViewPtr p = (ViewPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const ProblemView*)p;
+}
+
 // 6 x signed volume of snapped vertices (exact: coordinates below 2^19).
 __device__ __forceinline__ int64_t det6(const int v[4][3]) {
   const int64_t a0 = v[1][0] - v[0][0], a1 = v[1][1] - v[0][1], a2 = v[1][2] - v[0][2];
@@ -202,9 +434,8 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
 
 template <int ST>
 __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const float* pts, int pop, double inv_pop,
-                                                  double count_scale, uint64_t seed, const uint8_t* cells0,
-                                                  const uint8_t* cells1, const uint8_t* fgc0, const uint8_t* fgc1,
-                                                  Record* rec, int n_items) {
+                                                  double count_scale, uint64_t seed, const uint16_t* cells0,
+                                                  const uint16_t* cells1, Record* rec, int n_items) {
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int item = xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
   if (item >= n_items) return;
@@ -271,21 +502,20 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
       term = d * d;
     }
   }
-  const float mag = static_cast<float>(static_cast<double>(P.elasticity[tet]) * wave_sum_d(term));
+  const float mag = __int_as_float(__builtin_amdgcn_readfirstlane(
+      __float_as_int(static_cast<float>(static_cast<double>(P.elasticity[tet]) * wave_sum_d(term)))));
 
-  // shift words of both directions: lane d < 2 hashes direction d's tet
-  uint64_t w0 = 0, w1 = 0;
-  {
-    const int m = lane < 2 ? lane : 0;
-    uint64_t hsh = splitmix(seed + kGolden * static_cast<uint64_t>(m + 1));
+  // this lane's Sobol integers (the 6 low bits of the index)
+  uint32_t xlane[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 12; i++) {
-      const int c = __shfl(fix, 12 * m + i, 64);
-      hsh = splitmix(hsh + kGolden + static_cast<uint64_t>(static_cast<uint32_t>(c)));
-    }
-    w0 = splitmix(hsh + kGolden);
-    w1 = splitmix(hsh + 2 * kGolden);
-  }
+  for (int b = 0; b < 6; b++)
+#pragma unroll
+    for (int j = 0; j < 4; j++) xlane[j] ^= kDirections.v[j][b] & (0u - ((static_cast<uint32_t>(lane) >> b) & 1u));
+  // whether each tet stays a 2^-4 voxel inside [-1, n): then so do its points,
+  // whose rounding is below 2^-10 (lambdas sum to 1 within 2^-21)
+  const int axis = lane % 3, extent = axis == 0 ? P.nx : (axis == 1 ? P.ny : P.nz);
+  const bool in = lane >= 24 || (fix >= -960 && fix <= 1024 * extent - 64);
+  const bool inner = __ballot(in) == ~0ull;
   const int ref = P.ref_sign[tet];
 
 #pragma unroll 1
@@ -311,17 +541,19 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
     }
     float h = 0.f, g = 0.f;
     if (N > 0) {
-      // this lane's Sobol integers (its 6 low bits) with the shift applied
-      const uint32_t s0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(w0), d));
-      const uint32_t s1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(w0 >> 32), d));
-      const uint32_t s2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(w1), d));
-      const uint32_t s3 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(w1 >> 32), d));
-      uint32_t xl[4] = {s0, s1, s2, s3};
+      // the four shift words from a hash of the seed, the direction and the
+      // tet (wave-uniform: scalar), applied to the lane's integers; r_j =
+      // v_j 2^-24 with v_j = 2 floor(u_j / 2^9) + 1 of the integer u_j
+      uint64_t hsh = splitmix(seed + kGolden * static_cast<uint64_t>(d + 1));
 #pragma unroll
-      for (int b = 0; b < 6; b++)
-        if ((lane >> b) & 1)
+      for (int i = 0; i < 12; i++)
+        hsh = splitmix(hsh + kGolden + static_cast<uint64_t>(static_cast<uint32_t>(own[i / 3][i % 3])));
+      const uint64_t w0 = splitmix(hsh + kGolden), w1 = splitmix(hsh + 2 * kGolden);
+      const uint32_t shift[4] = {static_cast<uint32_t>(w0), static_cast<uint32_t>(w0 >> 32),
+                                 static_cast<uint32_t>(w1), static_cast<uint32_t>(w1 >> 32)};
+      uint32_t xl[4];
 #pragma unroll
-          for (int j = 0; j < 4; j++) xl[j] ^= kDir.v[j][b];
+      for (int j = 0; j < 4; j++) xl[j] = ((xlane[j] ^ shift[j]) >> 8) | 1u;
       // FP32 base vertex and edge vectors of both tets, in voxels (exact)
       float bo[3], eo[3][3], bt[3], et[3][3];
 #pragma unroll
@@ -334,84 +566,41 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
           et[i][a] = static_cast<float>(oth[i + 1][a] - oth[0][a]) * 0x1p-10f;
         }
       }
-      const void* img_own = d == 0 ? P.img[0] : P.img[1];
-      const void* img_oth = d == 0 ? P.img[1] : P.img[0];
-      const uint8_t* cells = d == 0 ? cells0 : cells1;
-      const uint8_t* fgc_own = d == 0 ? fgc0 : fgc1;
-      const uint8_t* fgc_oth = d == 0 ? fgc1 : fgc0;
-      const float* map_own = d == 0 ? P.dmap[0] : P.dmap[1];
-      const float* map_oth = d == 0 ? P.dmap[1] : P.dmap[0];
-      const float* set_w = P.set_w + d * kMaxSets;
+      uint32_t xk[4] = {0u, 0u, 0u, 0u};   // Sobol integers of 64 k (wave-uniform)
       for (int base = 0; base < N; base += kWave) {
-        // Sobol integers of 64 k (wave-uniform)
-        uint32_t xk[4] = {0u, 0u, 0u, 0u};
-        for (uint32_t t = static_cast<uint32_t>(base) >> 6; t != 0u; t &= t - 1u) {
-          const int b = __builtin_ctz(t) + 6;
+        uint32_t v[4];
 #pragma unroll
-          for (int j = 0; j < 4; j++) xk[j] ^= kDir.v[j][b];
-        }
+        for (int j = 0; j < 4; j++) v[j] = xl[j] ^ xk[j];
+        const int c = __builtin_ctz((static_cast<uint32_t>(base) >> 6) + 1u);
+#pragma unroll
+        for (int j = 0; j < 4; j++) xk[j] ^= kSteps.v[c][j];
         if (base + lane >= N) break;
-        float p[3], q[3];
-        {
-#pragma clang fp contract(off)
-          float e[4];
+        float l[3], p[3], q[3];
+        lambdas(v, l);
 #pragma unroll
-          for (int j = 0; j < 4; j++) {
-            const uint32_t u = xl[j] ^ xk[j];
-            e[j] = neg_log(static_cast<float>(2u * (u >> 9) + 1u) * 0x1p-24f);
-          }
-          const float sum = ((e[0] + e[1]) + e[2]) + e[3];
-          const float l1 = e[1] / sum, l2 = e[2] / sum, l3 = e[3] / sum;
-#pragma unroll
-          for (int a = 0; a < 3; a++) {
-            p[a] = __builtin_fmaf(l3, eo[2][a], __builtin_fmaf(l2, eo[1][a], __builtin_fmaf(l1, eo[0][a], bo[a])));
-            q[a] = __builtin_fmaf(l3, et[2][a], __builtin_fmaf(l2, et[1][a], __builtin_fmaf(l1, et[0][a], bt[a])));
-          }
+        for (int a = 0; a < 3; a++) {
+          p[a] = __builtin_fmaf(l[2], eo[2][a], __builtin_fmaf(l[1], eo[1][a], __builtin_fmaf(l[0], eo[0][a], bo[a])));
+          q[a] = __builtin_fmaf(l[2], et[2][a], __builtin_fmaf(l[1], et[1][a], __builtin_fmaf(l[0], et[0][a], bt[a])));
         }
-        bool fa, fb;
-        const float a = image_at<ST>(P, img_own, fgc_own, p[0], p[1], p[2], fa);
-        const float b = image_at<ST>(P, img_oth, fgc_oth, q[0], q[1], q[2], fb);
-        h += (fa && fb) ? (a - b) * (a - b) : (fa == fb ? 0.f : 1.f);
-        if (P.n_sets > 0) {
-          const MapCell cp = map_cell(P, p[0], p[1], p[2]);
-          // sets within the radius at one of the stencil's corners (if at
-          // none, the interpolated distance is not below it either)
-          unsigned bits = cells[cp.i0];
-          if (bits) {
-            const MapCell cq = map_cell(P, q[0], q[1], q[2]);
-            for (; bits; bits &= bits - 1u) {
-              const int s = __builtin_ctz(bits);
-              const float dn = map_at(P, map_own + static_cast<size_t>(s) * P.pvox, cp);
-              if (dn < P.radius) {
-                const float dq = map_at(P, map_oth + static_cast<size_t>(s) * P.pvox, cq);
-                const float diff = dn - dq;
-                g = fmaf(set_w[s] * (P.radius - dn) * P.inv_radius, diff * diff, g);
-              }
-            }
-          }
-        }
+        const ProblemView V = view();
+        const void* img_own = d == 0 ? V.img[0] : V.img[1];
+        const void* img_oth = d == 0 ? V.img[1] : V.img[0];
+        const uint16_t* cells_own = d == 0 ? cells0 : cells1;
+        const uint16_t* cells_oth = d == 0 ? cells1 : cells0;
+        const float* map_own = d == 0 ? V.dmap[0] : V.dmap[1];
+        const float* map_oth = d == 0 ? V.dmap[1] : V.dmap[0];
+        const float* set_w = V.set_w + d * kMaxSets;
+        if (inner)
+          inner_sample<ST>(V, img_own, img_oth, cells_own, cells_oth, map_own, map_oth, set_w, p, q, h, g);
+        else
+          outer_sample<ST>(V, img_own, img_oth, cells_own, cells_oth, map_own, map_oth, set_w, p, q, h, g);
       }
-      h = wave_sum(h);
-      g = wave_sum(g);
+      h = wave_sum_63(h);
+      g = wave_sum_63(g);
     }
-    if (lane == 0)
+    if (lane_id() == 63)
       out[d] = Record{h, g, static_cast<uint32_t>(N), d == 0 ? mag : 0.f, vol, viol ? 1u : 0u};
   }
-}
-
-// Band mask per grid cell (lower corner at padded element i): the OR of the
-// band bytes of its 8 corners; elements that are no cell's lower corner hold 0.
-__global__ void k_band_cells(ProblemView P, const uint8_t* band, uint8_t* cells) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= static_cast<int>(P.pvox)) return;
-  const int x = i % P.px - 1, y = (i / P.px) % (P.ny + 2) - 1, z = i / P.pxy - 1;
-  uint8_t v = 0;
-  if (x >= 0 && y >= 0 && z >= 0 && x <= max(P.nx - 2, 0) && y <= max(P.ny - 2, 0) && z <= max(P.nz - 2, 0)) {
-    const int j = i + P.pxy;
-    v = band[i] | band[i + 1] | band[i + P.px] | band[i + P.px + 1] | band[j] | band[j + 1] | band[j + P.px] |
-        band[j + P.px + 1];
-  }
-  cells[i] = v;
 }
 
 morea_status fail(morea_status s, const char* msg) {
@@ -426,43 +615,42 @@ morea_status device_fail(hipError_t e, const char* what) {
   return MOREA_EDEVICE;
 }
 
-// Foreground code per cell (lower corner at padded element i): bit 0 when a
-// corner of the cell holds a value > 0, bit 1 when all eight do.
+// Code per cell of the padded volume (lower corner at padded element i): bit
+// 0 when a corner of the image holds a value > 0, bit 1 when all eight do,
+// bits 8..15 the OR of the corners' band bytes.
 template <int ST>
-__global__ void k_fg_cells(ProblemView P, const void* img, uint8_t* cells) {
+__global__ void k_cells(ProblemView P, const void* img, const uint8_t* band, uint16_t* cells) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= static_cast<int>(P.pvox)) return;
   const int x = i % P.px, y = (i / P.px) % (P.ny + 2), z = i / P.pxy;
-  uint8_t v = 0;
+  unsigned v = 0;
   if (x + 1 < P.px && y + 1 < P.ny + 2 && z + 1 < P.nz + 2) {
     const int j = i + P.pxy;
     const int idx[8] = {i, i + 1, i + P.px, i + P.px + 1, j, j + 1, j + P.px, j + P.px + 1};
     bool any = false, all = true;
+    unsigned bits = 0;
 #pragma unroll
     for (int k = 0; k < 8; k++) {
       const bool pos = ld<ST>(img, idx[k]) > 0.f;
       any = any || pos;
       all = all && pos;
+      bits |= band[idx[k]];
     }
-    v = static_cast<uint8_t>((any ? 1 : 0) | (all ? 2 : 0));
+    v = (any ? 1u : 0u) | (all ? 2u : 0u) | bits << 8;
   }
-  cells[i] = v;
+  cells[i] = static_cast<uint16_t>(v);
 }
 
 }  // namespace sobol
 
-hipError_t launch_fg_cells(const ProblemView& P, int storage, const void* img, uint8_t* cells, hipStream_t s) {
+hipError_t launch_cells(const ProblemView& P, int storage, const void* img, const uint8_t* band, uint16_t* cells,
+                        hipStream_t s) {
   const dim3 grid((P.pvox + 255) / 256);
   switch (storage) {
-    case kF32: hipLaunchKernelGGL(sobol::k_fg_cells<kF32>, grid, dim3(256), 0, s, P, img, cells); break;
-    case kBF16: hipLaunchKernelGGL(sobol::k_fg_cells<kBF16>, grid, dim3(256), 0, s, P, img, cells); break;
-    default: hipLaunchKernelGGL(sobol::k_fg_cells<kF16>, grid, dim3(256), 0, s, P, img, cells); break;
+    case kF32: hipLaunchKernelGGL(sobol::k_cells<kF32>, grid, dim3(256), 0, s, P, img, band, cells); break;
+    case kBF16: hipLaunchKernelGGL(sobol::k_cells<kBF16>, grid, dim3(256), 0, s, P, img, band, cells); break;
+    default: hipLaunchKernelGGL(sobol::k_cells<kF16>, grid, dim3(256), 0, s, P, img, band, cells); break;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_band_cells(const ProblemView& P, const uint8_t* band, uint8_t* cells, hipStream_t s) {
-  hipLaunchKernelGGL(sobol::k_band_cells, dim3((P.pvox + 255) / 256), dim3(256), 0, s, P, band, cells);
   return hipGetLastError();
 }
 
@@ -493,20 +681,17 @@ extern "C" morea_status morea_eval_sobol(morea_problem* p, const float* pts, int
     switch (p->storage) {
       case kF32:
         hipLaunchKernelGGL(sobol::k_eval_sobol<kF32>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->band_cell[0], p->band_cell[1], p->fg_cell[0], p->fg_cell[1],
-                           p->work_records,
+                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
                            static_cast<int>(n_items));
         break;
       case kBF16:
         hipLaunchKernelGGL(sobol::k_eval_sobol<kBF16>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->band_cell[0], p->band_cell[1], p->fg_cell[0], p->fg_cell[1],
-                           p->work_records,
+                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
                            static_cast<int>(n_items));
         break;
       default:
         hipLaunchKernelGGL(sobol::k_eval_sobol<kF16>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->band_cell[0], p->band_cell[1], p->fg_cell[0], p->fg_cell[1],
-                           p->work_records,
+                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
                            static_cast<int>(n_items));
         break;
     }
