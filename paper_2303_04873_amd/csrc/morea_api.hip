@@ -126,6 +126,7 @@ morea_status morea_problem_create(const morea_problem_desc* d, morea_problem** o
   for (int i = 0; i < 3 * d->n_points; i++)
     if (!coord_ok(d->ref_points[i])) return fail(MOREA_EINVAL, "ref_points[%d] out of range", i);
   std::vector<int8_t> ref_sign(d->n_tets);
+  double tet_volume = 0.0, tet_box = 0.0;   // sums over the tets
   for (int t = 0; t < d->n_tets; t++) {
     int64_t v[4][3];
     for (int i = 0; i < 4; i++) {
@@ -143,6 +144,13 @@ morea_status morea_problem_create(const morea_problem_desc* d, morea_problem** o
                   a[2] * (b[0] * c[1] - b[1] * c[0]);
     if (det == 0) return fail(MOREA_EINVAL, "reference tet %d is flat", t);
     ref_sign[t] = det > 0 ? 1 : -1;
+    tet_volume += static_cast<double>(det > 0 ? det : -det) / 6442450944.0;
+    double box = 1.0;
+    for (int k = 0; k < 3; k++) {
+      const auto ends = std::minmax({v[0][k], v[1][k], v[2][k], v[3][k]});
+      box *= static_cast<double>(ends.second - ends.first) / 1024.0 + 4.0;
+    }
+    tet_box += box;
     float c_d = d->elasticity[t];
     if (!(c_d > 0.f && c_d < INFINITY)) return fail(MOREA_EINVAL, "elasticity[%d] not positive", t);
   }
@@ -179,6 +187,8 @@ morea_status morea_problem_create(const morea_problem_desc* d, morea_problem** o
   p->storage = d->storage;
   p->max_population = d->max_population;
   p->voxels = V;
+  p->tet_volume = tet_volume / d->n_tets;
+  p->tet_box = tet_box / d->n_tets;
   p->tets_host.assign(d->tets, d->tets + 4 * static_cast<size_t>(d->n_tets));
   p->ref_host.assign(d->ref_points, d->ref_points + 3 * static_cast<size_t>(d->n_points));
   ProblemView& P = p->view;

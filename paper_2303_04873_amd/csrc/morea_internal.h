@@ -123,6 +123,9 @@ struct morea_problem {
   // a corner holds a value > 0, bit 1 when all eight do, bits 8..15 the OR of
   // the corners' band bits
   uint16_t* cells[2] = {nullptr, nullptr};
+  // of the reference tets: mean volume, and mean voxels of their bounding
+  // boxes grown by 4 per axis (the spread of a population's tets)
+  double tet_volume = 0.0, tet_box = 0.0;
   // point -> incident tets (entries tet << 2 | slot) and point -> neighbours
   // (the other vertices of its incident tets, each once, ascending), CSR
   int* d_pinc_off = nullptr;

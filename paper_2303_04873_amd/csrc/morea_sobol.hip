@@ -23,22 +23,27 @@
 // supports depends on its bits, and these are the bits the definition
 // fixes.
 //
-// One 64-lane wave per (candidate, tet); both directions in turn; sample n
+// One 64-lane wave per (candidate, tet); a block's waves take candidates of
+// one tet where the images are staged; both directions in turn; sample n
 // of a direction is taken by lane n % 64.  Since lane < 64, the Sobol
 // integer of n = 64 k + lane is the XOR of that of the lane (per lane, once
 // per item) and that of 64 k (wave-uniform, scalar, once per batch).
 //
-// What bounds it: the gathers, 64 lanes in as many cache lines (46 cycles of a
-// CU each), and the vector instructions, 3,130 per wave.  They were 5,760 (88%
-// of the issue slots, 232 per point to form it and find its cell): the
-// divisions are now the correctly rounded ones without scaling for extreme
-// operands, the logarithm is halved (the ratios do not change), which saves
-// its scalings, and tets that stay in the grid's border cells take a path
-// without bounds tests on which one cell serves the images and the distance
-// maps and a row's two corners are one load.  128x128x96, population 128:
-// 4.1 -> 3.45, 4.6 -> 4.1, 4.9 -> 4.8 ms (three images).
+// What bounds it: the vector instructions, 200 a point, and where the images
+// are not staged in LDS the gathers, each lane in a cache line of its own (46
+// cycles of a CU for 64).  The instructions were 5,760 a wave (88% of the issue
+// slots, 232 per point to form it and find its cell; now 3,390): the divisions
+// are the correctly rounded ones without scaling for extreme operands, the
+// logarithm is halved (the ratios do not change), which saves its scalings,
+// and tets that stay in the grid's border cells take a path without bounds
+// tests on which one cell serves the images and the distance maps, a row's two
+// corners are one load and values are read only where both points are
+// foreground.  128x128x96, population 128, rate 1: 4.11 -> 2.90, 4.62 -> 3.34,
+// 4.94 -> 3.67 ms (three images); with the images in LDS 2.82, 2.96, 3.12 ms.
 #include <math.h>
 #include <stdio.h>
+
+#include <type_traits>
 
 #include "morea_internal.h"
 
@@ -333,6 +338,25 @@ __device__ __forceinline__ bool support(const float v[8], const Cell& c) {
   return f0 || (uz && f1);
 }
 
+// The guidance term of the sets in `bits` at cells cp, cq, added to g.
+__device__ __forceinline__ void map_terms(const ProblemView& P, unsigned bits, const float* map_own,
+                                          const float* map_oth, const float* set_w, const Cell& cp, const Cell& cq,
+                                          float& g) {
+  for (int s = 0; s < P.n_sets; s++) {
+    if ((bits >> s) & 1u) {
+      float v[8];
+      const size_t first = static_cast<size_t>(s) * P.pvox;
+      corners<kF32>(P, map_own + first, cp.e, v);
+      const float dn = trilinear(v, cp);
+      if (dn < P.radius) {
+        corners<kF32>(P, map_oth + first, cq.e, v);
+        const float diff = dn - trilinear(v, cq);
+        g = fmaf(set_w[s] * (P.radius - dn) * P.inv_radius, diff * diff, g);
+      }
+    }
+  }
+}
+
 // h and g of a point p of the sampled tet and q of the other one, both in
 // [-1, n) per axis, added to h and g.
 template <int ST>
@@ -342,15 +366,16 @@ __device__ __forceinline__ void inner_sample(const ProblemView& P, const void* i
                                              const float p[3], const float q[3], float& h, float& g) {
   const Cell cp = inner_cell(P, p), cq = inner_cell(P, q);
   const unsigned kp = cells_own[cp.e], kq = cells_oth[cq.e];
-  // cells without a positive corner hold zeros: both background, h = 0
-  if (__ballot(((kp | kq) & 1u) != 0u)) {
+  // with all weights nonzero a point is foreground where its cell has a
+  // positive corner: h needs the values only where both points are
+  const bool pa = (kp & 1u) != 0u, pb = (kq & 1u) != 0u;
+  const bool flat = cp.fx * cp.fy * cp.fz * cq.fx * cq.fy * cq.fz == 0.f;
+  if ((pa && pb) || (flat && (pa || pb))) {
     float u[8], v[8];
     corners<ST>(P, img_own, cp.e, u);
     corners<ST>(P, img_oth, cq.e, v);
     float a = trilinear(u, cp), b = trilinear(v, cq);
-    // with all weights nonzero a cell's foreground is that of its corners
-    bool fa = (kp & 1u) != 0u, fb = (kq & 1u) != 0u;
-    const bool flat = cp.fx * cp.fy * cp.fz * cq.fx * cq.fy * cq.fz == 0.f;
+    bool fa = pa, fb = pb;
     if (__ballot(flat)) {
       asm volatile("");   // kept as a branch
       fa = support(u, cp);
@@ -360,22 +385,96 @@ __device__ __forceinline__ void inner_sample(const ProblemView& P, const void* i
     }
     const float d = a - b;
     h += fa != fb ? 1.f : d * d;
+  } else {
+    h += pa != pb ? 1.f : 0.f;
   }
   // sets within the radius at one of the cell's corners (if at none, the
   // interpolated distance is not below it either)
   const unsigned bits = kp >> 8;
-  if (__ballot(bits != 0u)) {
-    for (int s = 0; s < P.n_sets; s++) {
-      if ((bits >> s) & 1u) {
-        float u[8], v[8];
-        const size_t first = static_cast<size_t>(s) * P.pvox;
-        corners<kF32>(P, map_own + first, cp.e, u);
-        corners<kF32>(P, map_oth + first, cq.e, v);
-        const float dn = trilinear(u, cp), diff = dn - trilinear(v, cq);
-        const float w = dn < P.radius ? set_w[s] * (P.radius - dn) * P.inv_radius : 0.f;
-        g = fmaf(w, diff * diff, g);
+  if (__ballot(bits != 0u)) map_terms(P, bits, map_own, map_oth, set_w, cp, cq, g);
+}
+
+// The boxes of the two images (0 source, 1 target) that a block's tets lie in:
+// values as FP32 and the cells' band bytes, staged once for the block's
+// candidates (their tets are one mesh tet, moved a little) and both
+// directions.  Two blocks of 12 waves per CU (of 8 waves with more registers
+// each: 14% longer).
+//
+// Staging has a fixed cost, a block's waves waiting for each other twice,
+// which the fuller blocks and the larger tets repay: 512 tets of cells of edge
+// n, `per` waves a block, without -> with: n = 12 (432 samples a tet, rate
+// 1.5), per 12: 918 -> 924 us; n = 13 (366), per 12: 842 -> 864, per 7: 252 ->
+// 341; n = 14 (457), per 12: 1,014 -> 968, per 11: 476 -> 523; n = 15 (562),
+// per 12: 1,234 -> 1,102, per 11: 587 -> 594; 844 samples, per 12: 1,754 ->
+// 1,405; from n = 17 the boxes do not fit.  So from 64,000 samples times per^2.
+// 128x128x96 with 3,402 tets, population 128: 2.90 -> 2.82, 3.34 -> 2.96 and
+// 3.67 -> 3.12 ms (three images).
+constexpr int kBlockWaves = 12;
+constexpr int kBoxVoxels = 16256;
+constexpr double kStageSamples = 64000.0;   // samples a tet times per^2
+
+struct BoxLds {
+  float v[kBoxVoxels];
+  uint8_t band[kBoxVoxels];
+  int lo[2][3], hi[2][3];   // padded cells of the waves' tets
+  int points;               // samples of the block
+  int found[2];             // bit 0: a positive value in the box, bits 8..15: its band bits
+};
+static_assert(sizeof(BoxLds) <= 81920, "two blocks per CU");
+
+// One of them, in scalar registers.
+struct Box {
+  int first, sy, sz;   // element of the padded origin's cell in v / band, strides
+};
+
+__device__ __forceinline__ bool box_corners(const BoxLds& L, int e, float v[8], int sy, int sz) {
+  const float *r0 = L.v + e, *r1 = r0 + sy, *r2 = r0 + sz, *r3 = r1 + sz;
+  v[0] = r0[0];
+  v[1] = r0[1];
+  v[2] = r1[0];
+  v[3] = r1[1];
+  v[4] = r2[0];
+  v[5] = r2[1];
+  v[6] = r3[0];
+  v[7] = r3[1];
+  // a positive corner, by the words as integers (no NaN; -0 is negative)
+  int top = __float_as_int(v[0]);
+#pragma unroll
+  for (int k = 1; k < 8; k++) top = max(top, __float_as_int(v[k]));
+  return top > 0;
+}
+
+// h of inner points from the staged boxes, then g as inner_sample's.
+__device__ __forceinline__ void staged_sample(const ProblemView& P, const BoxLds& L, const Box& bo, const Box& bt,
+                                              bool any_fg, bool any_band, const float* map_own, const float* map_oth,
+                                              const float* set_w, const float p[3], const float q[3], float& h,
+                                              float& g) {
+  const int px = floor_int(p[0]), py = floor_int(p[1]), pz = floor_int(p[2]);
+  const int qx = floor_int(q[0]), qy = floor_int(q[1]), qz = floor_int(q[2]);
+  const int ep = __mul24(pz, bo.sz) + (__mul24(py, bo.sy) + (px + bo.first));
+  const int eq = __mul24(qz, bt.sz) + (__mul24(qy, bt.sy) + (qx + bt.first));
+  const Cell cp{0u, __builtin_amdgcn_fractf(p[0]), __builtin_amdgcn_fractf(p[1]), __builtin_amdgcn_fractf(p[2])};
+  const Cell cq{0u, __builtin_amdgcn_fractf(q[0]), __builtin_amdgcn_fractf(q[1]), __builtin_amdgcn_fractf(q[2])};
+  if (any_fg) {
+    float u[8], v[8];
+    bool fa = box_corners(L, ep, u, bo.sy, bo.sz), fb = box_corners(L, eq, v, bt.sy, bt.sz);
+    if (__ballot(fa || fb)) {
+      float a = trilinear(u, cp), b = trilinear(v, cq);
+      const bool flat = cp.fx * cp.fy * cp.fz * cq.fx * cq.fy * cq.fz == 0.f;
+      if (__ballot(flat)) {
+        asm volatile("");   // kept as a branch
+        fa = support(u, cp);
+        fb = support(v, cq);
+        a = fa ? a : 0.f;
+        b = fb ? b : 0.f;
       }
+      const float d = a - b;
+      h += fa != fb ? 1.f : d * d;
     }
+  }
+  if (any_band) {
+    const unsigned bits = L.band[ep];
+    if (__ballot(bits != 0u)) map_terms(P, bits, map_own, map_oth, set_w, inner_cell(P, p), inner_cell(P, q), g);
   }
 }
 
@@ -432,24 +531,53 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
   return x < rem ? x * (q + 1) + pos : rem * (q + 1) + (x - rem) * q + pos;
 }
 
-template <int ST>
-__global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const float* pts, int pop, double inv_pop,
-                                                  double count_scale, uint64_t seed, const uint16_t* cells0,
-                                                  const uint16_t* cells1, Record* rec, int n_items) {
+// Samples of a tet: its volume times the rate, rounded.
+__device__ __forceinline__ int sample_count(int64_t D, double count_scale) {
+  if (D == 0) return 0;
+  const double x = floor(static_cast<double>(D < 0 ? -D : D) * count_scale + 0.5);
+  return x > 0.0 ? (x >= kMaxSamples ? kMaxSamples : static_cast<int>(x)) : 0;
+}
+
+struct NoLds {};
+
+// kStaged: a block takes one tet of `per` candidates, a wave each, `groups`
+// blocks a tet.  Otherwise `per` = 4 waves take an item each.
+template <int ST, bool kStaged>
+__global__ __launch_bounds__(64 * (kStaged ? kBlockWaves : 4), 6) void k_eval_sobol(
+    ProblemView P, const float* pts, int pop, int per, int groups, double inv_pop, double count_scale, uint64_t seed,
+    const uint16_t* cells0, const uint16_t* cells1, Record* rec) {
+  __shared__ std::conditional_t<kStaged, BoxLds, NoLds> L;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int item = xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
-  if (item >= n_items) return;
-  int tet = static_cast<int>(static_cast<double>(item) * inv_pop);
-  int cand = item - tet * pop;
-  if (cand < 0) {
-    tet -= 1;
-    cand += pop;
-  } else if (cand >= pop) {
-    tet += 1;
-    cand -= pop;
+  const int block = xcd_remap(blockIdx.x, gridDim.x);
+  int tet, cand;
+  bool spare = false;
+  if constexpr (kStaged) {
+    tet = block / groups;
+    const int first = (block - tet * groups) * per, last = min(pop, first + per) - 1;
+    spare = first + wave > last;
+    cand = min(first + wave, last);   // a wave to spare repeats the last
+    if (threadIdx.x < 6) {
+      (&L.lo[0][0])[threadIdx.x] = INT32_MAX;
+      (&L.hi[0][0])[threadIdx.x] = INT32_MIN;
+    }
+    if (threadIdx.x < 2) L.found[threadIdx.x] = 0;
+    if (threadIdx.x == 0) L.points = 0;
+    __syncthreads();
+  } else {
+    const int item = block * 4 + wave;
+    tet = static_cast<int>(static_cast<double>(item) * inv_pop);
+    cand = item - tet * pop;
+    if (cand < 0) {
+      tet -= 1;
+      cand += pop;
+    } else if (cand >= pop) {
+      tet += 1;
+      cand -= pop;
+    }
+    if (tet >= P.n_tets) return;
+    tet = __builtin_amdgcn_readfirstlane(tet);
+    cand = __builtin_amdgcn_readfirstlane(cand);
   }
-  tet = __builtin_amdgcn_readfirstlane(tet);
-  cand = __builtin_amdgcn_readfirstlane(cand);
   const int lane = lane_id();
   Record* out = rec + (static_cast<size_t>(cand) * P.n_tets + tet) * 2;
 
@@ -461,13 +589,38 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
     const int v = i == 0 ? tv.x : (i == 1 ? tv.y : (i == 2 ? tv.z : tv.w));
     coord = pts[((static_cast<size_t>(cand) * 2 + lane / 12) * 3 + k) * P.n_points + v];
   }
-  const bool ok = lane >= 24 || fabsf(coord) < kCoordLimit;
-  if (__ballot(ok) != ~0ull) {
-    if (lane < 2) out[lane] = Record{0.f, 0.f, 0u, 0.f, 0.f, 4u};
-    return;
-  }
+  const bool ok = __ballot(lane >= 24 || fabsf(coord) < kCoordLimit) == ~0ull;
+  if (!ok && !spare && lane < 2) out[lane] = Record{0.f, 0.f, 0u, 0.f, 0.f, 4u};
+  if constexpr (!kStaged)
+    if (!ok) return;
+  if (!ok) coord = 0.f;   // no samples; the block's barriers are passed all the same
   // snapped coordinate of lane l < 24: mesh l / 12, vertex (l % 12) / 3, axis l % 3
   const int fix = lane < 24 ? static_cast<int>(rintf(coord * kFixOne)) : 0;
+
+  // whether each tet stays a 2^-4 voxel inside [-1, n): then so do its points,
+  // whose rounding is below 2^-10 (lambdas sum to 1 within 2^-21)
+  const int axis = lane % 3, extent = axis == 0 ? P.nx : (axis == 1 ? P.ny : P.nz);
+  const bool in = lane >= 24 || (fix >= -960 && fix <= 1024 * extent - 64);
+  const bool inner = ok && __ballot(in) == ~0ull;
+  int count[2];
+  int64_t det[2];
+#pragma unroll
+  for (int d = 0; d < 2; d++) {
+    int v[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int k = 0; k < 3; k++) v[i][k] = __builtin_amdgcn_readlane(fix, 12 * d + 3 * i + k);
+    det[d] = det6(v);
+    count[d] = ok ? sample_count(det[d], count_scale) : 0;
+  }
+  if constexpr (kStaged) {
+    if (inner && lane < 24) {
+      atomicMin(&L.lo[lane / 12][axis], (fix - 1) >> 10);
+      atomicMax(&L.hi[lane / 12][axis], (fix + 1) >> 10);
+    }
+    if (inner && lane == 0) atomicAdd(&L.points, count[0] + count[1]);
+  }
 
   // magnitude (Sec. 4.1.1): lane e < 10 takes edge e (6 edges, then the 4
   // spokes from the centroid), squared lengths exact in FP64
@@ -505,17 +658,67 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
   const float mag = __int_as_float(__builtin_amdgcn_readfirstlane(
       __float_as_int(static_cast<float>(static_cast<double>(P.elasticity[tet]) * wave_sum_d(term)))));
 
+  // stage the boxes, if they fit
+  Box box[2];
+  bool staged = false;
+  int found0 = 0, found1 = 0;
+  if constexpr (kStaged) {
+    __syncthreads();
+    if (L.points > 0) {
+      long long all = 0;
+#pragma unroll
+      for (int m = 0; m < 2; m++) {
+        const int sy = __builtin_amdgcn_readfirstlane(L.hi[m][0] - L.lo[m][0] + 2);
+        const int ly = __builtin_amdgcn_readfirstlane(L.hi[m][1] - L.lo[m][1] + 2);
+        const int lz = __builtin_amdgcn_readfirstlane(L.hi[m][2] - L.lo[m][2] + 2);
+        const int x0 = __builtin_amdgcn_readfirstlane(L.lo[m][0]), y0 = __builtin_amdgcn_readfirstlane(L.lo[m][1]);
+        const int z0 = __builtin_amdgcn_readfirstlane(L.lo[m][2]);
+        box[m] = Box{static_cast<int>(all) - (z0 * ly + y0) * sy - x0, sy, sy * ly};
+        all += static_cast<long long>(sy) * ly * lz;
+      }
+      staged = all <= kBoxVoxels;
+    }
+    if (staged) {
+      // half the threads a box, a thread a column of it
+      const int half = blockDim.x >> 1, m = threadIdx.x >= half ? 1 : 0;
+      const int x0 = L.lo[m][0], y0 = L.lo[m][1], z0 = L.lo[m][2];
+      const int sy = m ? box[1].sy : box[0].sy, sz = m ? box[1].sz : box[0].sz;
+      const int nz = L.hi[m][2] - z0 + 2, origin = (m ? box[1].first : box[0].first) + (z0 * sz + y0 * sy + x0);
+      const void* img = m ? P.img[1] : P.img[0];
+      const uint16_t* cells = m ? cells1 : cells0;
+      const float inv = 1.f / static_cast<float>(sy);
+      float top = 0.f;
+      unsigned bits = 0;
+      for (int c = threadIdx.x - (m ? half : 0); c < sz; c += half) {
+        // exact: the quotient's error, 2^-22 of it, is below half a divisor's share
+        const int y = static_cast<int>((static_cast<float>(c) + 0.5f) * inv), x = c - y * sy;
+        int i = (z0 + 1) * P.pxy + (y0 + 1 + y) * P.px + x0 + 1 + x, e = origin + c;
+#pragma unroll 4
+        for (int z = 0; z < nz; z++, i += P.pxy, e += sz) {
+          const float v = ld<ST>(img, i);
+          const unsigned b = cells[i] >> 8;
+          L.v[e] = v;
+          L.band[e] = static_cast<uint8_t>(b);
+          top = fmaxf(top, v);
+          bits |= b;
+        }
+      }
+      const int seen = (top > 0.f ? 1 : 0) | (bits ? 256 : 0);
+      if (seen) atomicOr(&L.found[m], seen);
+    }
+    __syncthreads();
+    if (!ok || spare) return;
+    found0 = __builtin_amdgcn_readfirstlane(L.found[0]);
+    found1 = __builtin_amdgcn_readfirstlane(L.found[1]);
+  }
+  const bool any_fg = ((found0 | found1) & 1) != 0;
+
   // this lane's Sobol integers (the 6 low bits of the index)
   uint32_t xlane[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int b = 0; b < 6; b++)
 #pragma unroll
     for (int j = 0; j < 4; j++) xlane[j] ^= kDirections.v[j][b] & (0u - ((static_cast<uint32_t>(lane) >> b) & 1u));
-  // whether each tet stays a 2^-4 voxel inside [-1, n): then so do its points,
-  // whose rounding is below 2^-10 (lambdas sum to 1 within 2^-21)
-  const int axis = lane % 3, extent = axis == 0 ? P.nx : (axis == 1 ? P.ny : P.nz);
-  const bool in = lane >= 24 || (fix >= -960 && fix <= 1024 * extent - 64);
-  const bool inner = __ballot(in) == ~0ull;
   const int ref = P.ref_sign[tet];
 
 #pragma unroll 1
@@ -529,16 +732,12 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
         own[i][k] = __builtin_amdgcn_readlane(fix, 12 * d + 3 * i + k);
         oth[i][k] = __builtin_amdgcn_readlane(fix, 12 * (1 - d) + 3 * i + k);
       }
-    const int64_t D = det6(own);
+    const int64_t D = d == 0 ? det[0] : det[1];
+    const int N = d == 0 ? count[0] : count[1];
     const int sg = (D > 0) - (D < 0);
     const bool viol = sg == 0 || sg != ref;
     const int64_t absD = D < 0 ? -D : D;
     const float vol = viol ? static_cast<float>(static_cast<double>(absD) * (1.0 / 6442450944.0)) : 0.f;
-    int N = 0;
-    if (D != 0) {
-      const double x = floor(static_cast<double>(absD) * count_scale + 0.5);
-      N = x > 0.0 ? (x >= kMaxSamples ? kMaxSamples : static_cast<int>(x)) : 0;
-    }
     float h = 0.f, g = 0.f;
     if (N > 0) {
       // the four shift words from a hash of the seed, the direction and the
@@ -590,6 +789,12 @@ __global__ __launch_bounds__(256, 6) void k_eval_sobol(ProblemView P, const floa
         const float* map_own = d == 0 ? V.dmap[0] : V.dmap[1];
         const float* map_oth = d == 0 ? V.dmap[1] : V.dmap[0];
         const float* set_w = V.set_w + d * kMaxSets;
+        if constexpr (kStaged)
+          if (inner && staged) {
+            staged_sample(V, L, d == 0 ? box[0] : box[1], d == 0 ? box[1] : box[0], any_fg,
+                          ((d == 0 ? found0 : found1) >> 8) != 0, map_own, map_oth, set_w, p, q, h, g);
+            continue;
+          }
         if (inner)
           inner_sample<ST>(V, img_own, img_oth, cells_own, cells_oth, map_own, map_oth, set_w, p, q, h, g);
         else
@@ -641,6 +846,26 @@ __global__ void k_cells(ProblemView P, const void* img, const uint8_t* band, uin
   cells[i] = static_cast<uint16_t>(v);
 }
 
+template <int ST>
+hipError_t launch(const morea_problem* p, const float* pts, int pop, float rate, uint64_t seed, hipStream_t s) {
+  const ProblemView& P = p->view;
+  const double count_scale = static_cast<double>(rate) / 6442450944.0;   // rate / (6 * 2^30)
+  const double inv_pop = 1.0 / pop;
+  // candidates spread evenly over the blocks of a tet
+  const int groups = (pop + kBlockWaves - 1) / kBlockWaves, per = (pop + groups - 1) / groups;
+  const bool staged = p->tet_volume * rate * per * per >= kStageSamples && 2.0 * p->tet_box <= kBoxVoxels;
+  if (staged) {
+    const dim3 grid(static_cast<unsigned>(static_cast<size_t>(P.n_tets) * groups));
+    hipLaunchKernelGGL((k_eval_sobol<ST, true>), grid, dim3(64 * per), 0, s, P, pts, pop, per, groups, inv_pop,
+                       count_scale, seed, p->cells[0], p->cells[1], p->work_records);
+  } else {
+    const dim3 grid(static_cast<unsigned>((static_cast<size_t>(P.n_tets) * pop + 3) / 4));
+    hipLaunchKernelGGL((k_eval_sobol<ST, false>), grid, dim3(256), 0, s, P, pts, pop, 4, 0, inv_pop, count_scale, seed,
+                       p->cells[0], p->cells[1], p->work_records);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace sobol
 
 hipError_t launch_cells(const ProblemView& P, int storage, const void* img, const uint8_t* band, uint16_t* cells,
@@ -675,27 +900,12 @@ extern "C" morea_status morea_eval_sobol(morea_problem* p, const float* pts, int
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t n_items = static_cast<size_t>(pop) * P.n_tets;
   if (n_items > 0) {
-    const int blocks = static_cast<int>((n_items + 3) / 4);
-    const double count_scale = static_cast<double>(rate) / 6442450944.0;   // rate / (6 * 2^30)
-    const double inv_pop = 1.0 / pop;
+    hipError_t e;
     switch (p->storage) {
-      case kF32:
-        hipLaunchKernelGGL(sobol::k_eval_sobol<kF32>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
-                           static_cast<int>(n_items));
-        break;
-      case kBF16:
-        hipLaunchKernelGGL(sobol::k_eval_sobol<kBF16>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
-                           static_cast<int>(n_items));
-        break;
-      default:
-        hipLaunchKernelGGL(sobol::k_eval_sobol<kF16>, dim3(blocks), dim3(256), 0, s, P, pts, pop, inv_pop,
-                           count_scale, seed, p->cells[0], p->cells[1], p->work_records,
-                           static_cast<int>(n_items));
-        break;
+      case kF32: e = sobol::launch<kF32>(p, pts, pop, rate, seed, s); break;
+      case kBF16: e = sobol::launch<kBF16>(p, pts, pop, rate, seed, s); break;
+      default: e = sobol::launch<kF16>(p, pts, pop, rate, seed, s); break;
     }
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return sobol::device_fail(e, "Sobol evaluation");
   }
   hipError_t e = launch_finalize(P, pts, pop, p->work_records, obj, flags, severity, counts, nullptr, s);

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
+import synth
 from parity import assert_parity, to_host
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,31 @@ def test_sample_paths(case, storage):
     ref = op.evaluate_sobol(cand, rate=rate, seed=3)
     assert ref["counts"].min() > 100
     assert_parity(to_host(out), ref, what=case)
+
+
+@pytest.mark.parametrize("pop", [1, 11, 12, 13, 40])
+def test_candidates_do_not_depend_on_their_block(pop):
+    """A population large enough for staged images (12 candidates a block, the
+    last block partly filled) scores each candidate as it scores alone, up to
+    the order of FP32 sums; a candidate far off, one partly outside and an
+    invalid one leave their block's others alone."""
+    n, cells = 40, 4
+    pts, tets, fixed = synth.kuhn_grid((n, n, n), (cells, cells, cells))
+    rs = np.random.default_rng(4)
+    img = [(rs.uniform(0, 1, (n, n, n)) * (rs.uniform(0, 1, (n, n, n)) > 0.3)).astype(np.float32) for _ in range(2)]
+    sets = [[rs.uniform(4, n - 5, (40, 3)).astype(np.float32)] for _ in range(2)]
+    prob = morea.Problem((n, n, n), img[0], img[1], tets, pts, np.ones(len(tets), np.float32), sets[0], sets[1],
+                         radius=4.0, max_population=pop)
+    cands = np.stack([np.stack([(pts + np.where(fixed, 0, rs.normal(0, 0.4, pts.shape))).T for _ in range(2)])
+                      for _ in range(pop)]).astype(np.float32)
+    if pop >= 13:
+        cands[3] += 9.0                  # partly outside
+        cands[5, 1] *= 0.5               # other tets than its block's
+        cands[7, 0, 1, 20] = np.nan
+    t = torch.from_numpy(np.ascontiguousarray(cands)).cuda()
+    out = to_host(prob.eval_sobol(t, rate=2.5, seed=6))
+    for k in range(pop):
+        one = to_host(prob.eval_sobol(t[k:k + 1].contiguous(), rate=2.5, seed=6))
+        np.testing.assert_array_equal(out["counts"][k], one["counts"][0])
+        np.testing.assert_array_equal(out["flags"][k], one["flags"][0])
+        np.testing.assert_allclose(out["obj"][k], one["obj"][0], rtol=2e-6)
