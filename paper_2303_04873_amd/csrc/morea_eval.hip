@@ -1309,58 +1309,79 @@ template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int,
 
 // Per-candidate reduction over all tets in a fixed order, with compensated
 // sums; writes the objective vector, flags, severity, counts and (when
-// `totals` is non-null) the candidate totals of the cache.
-__global__ __launch_bounds__(256) void k_finalize(ProblemView P, const float* pts, const Record* rec,
-                                                   float* obj, uint8_t* flags, float* severity,
-                                                   uint32_t* counts, Totals* totals) {
+// `totals` is non-null) the candidate totals of the cache.  Bound by the
+// latency of its loads and of the tree: 1,024 threads and lane exchanges,
+// where 256 threads and eight rounds through LDS took 5.4 -> 3.9 us (16
+// candidates, 384 tets), 9.2 -> 5.1 (37, 1,680) and 21.3 -> 17.6 us (512,
+// 3,402).  Always the same block, so that a candidate's sums do not depend on
+// the population it is in.
+constexpr int kFinalThreads = 1024;
+static_assert(kFinalThreads / kWave == 16, "one row of lanes adds the waves' sums");
+
+struct Sums {
+  float v[8];      // h, g, magnitude, violating volume, each as high and low part
+  uint32_t n[5];   // samples of each direction, violations of each, invalid coordinates
+};
+
+// s plus another lane's, taken by DPP (lanes without a source add zeros).
+template <int ctrl, int rows>
+__device__ __forceinline__ void add_lane(Sums& s) {
+#pragma unroll
+  for (int k = 0; k < 8; k += 2) {
+    const float h = dpp_f<ctrl, rows>(s.v[k]), l = dpp_f<ctrl, rows>(s.v[k + 1]);
+    df_add(s.v[k], s.v[k + 1], h);
+    s.v[k + 1] += l;
+  }
+#pragma unroll
+  for (int k = 0; k < 5; k++)
+    s.n[k] += __builtin_amdgcn_update_dpp(0, static_cast<int>(s.n[k]), ctrl, rows, 0xf, false);
+}
+
+__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, const Record* rec,
+                                                            float* obj, uint8_t* flags, float* severity,
+                                                            uint32_t* counts, Totals* totals) {
   const int cand = blockIdx.x;
   const int tid = threadIdx.x;
-  float hh = 0.f, hl = 0.f, gh = 0.f, gl = 0.f, mh = 0.f, ml = 0.f, vh = 0.f, vl = 0.f;
-  uint32_t ns = 0, nt = 0, vs = 0, vt = 0, bad = 0;
+  Sums S = {};
   const Record* rc = rec + static_cast<size_t>(cand) * P.n_tets * 2;
-  for (int t = tid; t < P.n_tets; t += blockDim.x) {
+  for (int t = tid; t < P.n_tets; t += kFinalThreads) {
     const Record a = rc[2 * t], b = rc[2 * t + 1];
-    df_add(hh, hl, a.h);
-    df_add(hh, hl, b.h);
-    df_add(gh, gl, a.g);
-    df_add(gh, gl, b.g);
-    df_add(mh, ml, a.mag);
-    df_add(vh, vl, a.vol);
-    df_add(vh, vl, b.vol);
-    ns += a.n;
-    nt += b.n;
-    vs += a.bits & 1u;
-    vt += b.bits & 1u;
+    df_add(S.v[0], S.v[1], a.h);
+    df_add(S.v[0], S.v[1], b.h);
+    df_add(S.v[2], S.v[3], a.g);
+    df_add(S.v[2], S.v[3], b.g);
+    df_add(S.v[4], S.v[5], a.mag);
+    df_add(S.v[6], S.v[7], a.vol);
+    df_add(S.v[6], S.v[7], b.vol);
+    S.n[0] += a.n;
+    S.n[1] += b.n;
+    S.n[2] += a.bits & 1u;
+    S.n[3] += b.bits & 1u;
   }
   const float* cp = pts + static_cast<size_t>(cand) * 6 * P.n_points;
-  for (int i = tid; i < 6 * P.n_points; i += blockDim.x) bad += !(fabsf(cp[i]) < kCoordLimit);
+  for (int i = tid; i < 6 * P.n_points; i += kFinalThreads) S.n[4] += !(fabsf(cp[i]) < kCoordLimit);
 
-  __shared__ float sf[8][256];
-  __shared__ uint32_t su[5][256];
-  sf[0][tid] = hh; sf[1][tid] = hl; sf[2][tid] = gh; sf[3][tid] = gl;
-  sf[4][tid] = mh; sf[5][tid] = ml; sf[6][tid] = vh; sf[7][tid] = vl;
-  su[0][tid] = ns; su[1][tid] = nt; su[2][tid] = vs; su[3][tid] = vt; su[4][tid] = bad;
+  // within rows of 16 lanes, across them, then over the waves
+  __shared__ Sums part[kFinalThreads / kWave];
+  add_lane<0x111, 0xf>(S);
+  add_lane<0x112, 0xf>(S);
+  add_lane<0x114, 0xf>(S);
+  add_lane<0x118, 0xf>(S);
+  add_lane<0x142, 0xa>(S);
+  add_lane<0x143, 0xc>(S);
+  if ((tid & 63) == 63) part[tid >> 6] = S;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-#pragma unroll
-      for (int k = 0; k < 8; k += 2) {
-        float h = sf[k][tid], l = sf[k + 1][tid];
-        df_add(h, l, sf[k][tid + s]);
-        l += sf[k + 1][tid + s];
-        sf[k][tid] = h;
-        sf[k + 1][tid] = l;
-      }
-#pragma unroll
-      for (int k = 0; k < 5; k++) su[k][tid] += su[k][tid + s];
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const uint32_t Ns = su[0][0], Nt = su[1][0];
-    const bool invalid = su[4][0] != 0;
-    const float H = sf[0][0] + sf[1][0], G = sf[2][0] + sf[3][0];
-    const float Mg = sf[4][0] + sf[5][0], Vv = sf[6][0] + sf[7][0];
+  if (tid >= kFinalThreads / kWave) return;
+  S = part[tid];
+  add_lane<0x111, 0xf>(S);
+  add_lane<0x112, 0xf>(S);
+  add_lane<0x114, 0xf>(S);
+  add_lane<0x118, 0xf>(S);
+  if (tid == kFinalThreads / kWave - 1) {
+    const uint32_t Ns = S.n[0], Nt = S.n[1];
+    const bool invalid = S.n[4] != 0;
+    const float H = S.v[0] + S.v[1], G = S.v[2] + S.v[3];
+    const float Mg = S.v[4] + S.v[5], Vv = S.v[6] + S.v[7];
     const float N = static_cast<float>(Ns) + static_cast<float>(Nt);
     if (invalid) {
       const float nan = __builtin_nanf("");
@@ -1372,17 +1393,17 @@ __global__ __launch_bounds__(256) void k_finalize(ProblemView P, const float* pt
       obj[3 * cand + 0] = H / N;
       obj[3 * cand + 1] = Mg / (10.0f * static_cast<float>(P.n_tets));
       obj[3 * cand + 2] = G / N;
-      flags[cand] = static_cast<uint8_t>((su[2][0] ? 1 : 0) | (su[3][0] ? 2 : 0));
+      flags[cand] = static_cast<uint8_t>((S.n[2] ? 1 : 0) | (S.n[3] ? 2 : 0));
       severity[cand] = Vv;
       counts[2 * cand] = Ns;
       counts[2 * cand + 1] = Nt;
     }
     if (totals) {
       Totals T;
-      T.h_hi = sf[0][0]; T.h_lo = sf[1][0]; T.g_hi = sf[2][0]; T.g_lo = sf[3][0];
-      T.m_hi = sf[4][0]; T.m_lo = sf[5][0]; T.v_hi = sf[6][0]; T.v_lo = sf[7][0];
-      T.n[0] = Ns; T.n[1] = Nt; T.viol[0] = su[2][0]; T.viol[1] = su[3][0];
-      T.bad = su[4][0];
+      T.h_hi = S.v[0]; T.h_lo = S.v[1]; T.g_hi = S.v[2]; T.g_lo = S.v[3];
+      T.m_hi = S.v[4]; T.m_lo = S.v[5]; T.v_hi = S.v[6]; T.v_lo = S.v[7];
+      T.n[0] = Ns; T.n[1] = Nt; T.viol[0] = S.n[2]; T.viol[1] = S.n[3];
+      T.bad = S.n[4];
       T.pad[0] = T.pad[1] = T.pad[2] = 0;
       totals[cand] = T;
     }
@@ -1472,7 +1493,7 @@ hipError_t launch_finalize(const ProblemView& P, const float* pts, int pop, cons
                            float* obj, uint8_t* flags, float* severity, uint32_t* counts,
                            Totals* totals, hipStream_t s) {
   if (pop == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finalize, dim3(pop), dim3(256), 0, s, P, pts, rec, obj, flags, severity,
+  hipLaunchKernelGGL(k_finalize, dim3(pop), dim3(kFinalThreads), 0, s, P, pts, rec, obj, flags, severity,
                      counts, totals);
   return hipGetLastError();
 }
