@@ -644,8 +644,9 @@ morea_status morea_surrogate_predict_rows(morea_surrogate *s, const float *feats
  * parents' point means, then the offspring, each from a copy of the
  * coordinates by columns); an offspring without a valid parent scores +inf.
  * The parents' point means (16 bytes per (parent, tet)), partial scores (8
- * per offspring and run of 1 to 8 tets) and columns (36 per offspring and
- * mesh point, at most 256 MiB or 64 offspring at a time) go to a workspace of
+ * per offspring and run of 1 to 8 tets), columns and the values that tets
+ * share (36 per offspring and mesh point, 4 per offspring and mesh point or
+ * edge, at most 256 MiB or 64 offspring at a time) go to a workspace of
  * the surrogate, allocated again (hipMalloc, after waiting for the device)
  * when a call needs more than every earlier one; calls on one surrogate that
  * overlap on different streams race on it. */

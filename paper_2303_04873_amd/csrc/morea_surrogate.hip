@@ -244,45 +244,72 @@ __device__ __forceinline__ Edges edges(const float d[4][3]) {
   return t;
 }
 
-// h at barycentric coordinates l of the tet: (I_s(S l) - I_t(T l))^2.
+// h at a source and a target position: (I_s(x) - I_t(y))^2.
 template <bool kBig>
-__device__ __forceinline__ float h_at(const ProblemView& P, const float4* img_s, const float4* img_t, const Edges& S,
-                                      const Edges& T, const float4 l) {
-  float x[3], y[3];
-#pragma unroll
-  for (int a = 0; a < 3; a++) {
-    x[a] = fmaf(l.z, S.e[2][a], fmaf(l.y, S.e[1][a], fmaf(l.x, S.e[0][a], S.v[a])));
-    y[a] = fmaf(l.z, T.e[2][a], fmaf(l.y, T.e[1][a], fmaf(l.x, T.e[0][a], T.v[a])));
-  }
+__device__ __forceinline__ float h_at(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                      const float x[3], const float y[3]) {
   const float d = sample_clamped<kBig>(P, img_s, x[0], x[1], x[2]) - sample_clamped<kBig>(P, img_t, y[0], y[1], y[2]);
   return d * d;
 }
 
-// The points of a tet behind the estimated changes, as barycentric
-// coordinates `bary`: its 4 vertices, the edge midpoints (0,1) (0,2) (0,3)
-// (1,2) (1,3) (2,3), then 16 interior points.
-constexpr int kPoints = 10 + kHalton;
-
-// Sum of h at points j .. j + N - 1, in order, one at a time.
-template <bool kBig, int N>
-__device__ __forceinline__ float point_run(const ProblemView& P, const float4* img_s, const float4* img_t,
-                                           const Edges& S, const Edges& T, const float4* bary, int j) {
-  float sum = 0.f;
-#pragma unroll 1
-  for (int q = 0; q < N; q++) sum += h_at<kBig>(P, img_s, img_t, S, T, bary[j + q]);
-  return sum;
+// h at the midpoint of an edge from its ends' positions (the same bits
+// whichever end comes first).
+template <bool kBig>
+__device__ __forceinline__ float h_mid(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                       const float xa[3], const float xb[3], const float ya[3], const float yb[3]) {
+  float x[3], y[3];
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    x[a] = (xa[a] + xb[a]) * 0.5f;
+    y[a] = (ya[a] + yb[a]) * 0.5f;
+  }
+  return h_at<kBig>(P, img_s, img_t, x, y);
 }
 
-// Means of h over the point sets of a tet with vertices s (source) and t
-// (target): m[0] the 4 vertices, m[1] the 6 edge midpoints, m[2] the 16
-// interior points.
+// The points of a tet behind the estimated changes: its 4 vertices, the edge
+// midpoints (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), and kHalton interior points
+// given by barycentric coordinates `bary`.  Mean of h over the latter, added
+// in order, for a tet with vertices s (source) and t (target).
+template <bool kBig>
+__device__ __forceinline__ float interior_mean(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                               const float s[4][3], const float t[4][3], const float4* bary) {
+  const Edges S = edges(s), T = edges(t);
+  float sum = 0.f;
+#pragma unroll 1
+  for (int q = 0; q < kHalton; q++) {
+    const float4 l = bary[q];
+    float x[3], y[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      x[a] = fmaf(l.z, S.e[2][a], fmaf(l.y, S.e[1][a], fmaf(l.x, S.e[0][a], S.v[a])));
+      y[a] = fmaf(l.z, T.e[2][a], fmaf(l.y, T.e[1][a], fmaf(l.x, T.e[0][a], T.v[a])));
+    }
+    sum += h_at<kBig>(P, img_s, img_t, x, y);
+  }
+  return sum * (1.f / kHalton);
+}
+
+// Means from the values at the 4 vertices and at the 6 midpoints.
+__device__ __forceinline__ void corner_means(const float hv[4], const float he[6], float m[3]) {
+  m[0] = (((hv[0] + hv[1]) + hv[2]) + hv[3]) * 0.25f;
+  m[1] = (((((he[0] + he[1]) + he[2]) + he[3]) + he[4]) + he[5]) * (1.f / 6.f);
+}
+
+// Means of h over the three point sets: m[0] the vertices, m[1] the edge
+// midpoints, m[2] the interior points.
 template <bool kBig>
 __device__ __forceinline__ void point_means(const ProblemView& P, const float4* img_s, const float4* img_t,
                                             const float s[4][3], const float t[4][3], const float4* bary, float m[3]) {
-  const Edges S = edges(s), T = edges(t);
-  m[0] = point_run<kBig, 4>(P, img_s, img_t, S, T, bary, 0) * 0.25f;
-  m[1] = point_run<kBig, 6>(P, img_s, img_t, S, T, bary, 4) * (1.f / 6.f);
-  m[2] = point_run<kBig, kHalton>(P, img_s, img_t, S, T, bary, 10) * (1.f / kHalton);
+  float hv[4], he[6];
+#pragma unroll
+  for (int v = 0; v < 4; v++) hv[v] = h_at<kBig>(P, img_s, img_t, s[v], t[v]);
+  int k = 0;
+#pragma unroll
+  for (int v = 0; v < 4; v++)
+#pragma unroll
+    for (int w = v + 1; w < 4; w++) he[k++] = h_mid<kBig>(P, img_s, img_t, s[v], s[w], t[v], t[w]);
+  corner_means(hv, he, m);
+  m[2] = interior_mean<kBig>(P, img_s, img_t, s, t, bary);
 }
 
 // |signed volume| (voxel^3): the expected samples of the tet in its direction.
@@ -431,7 +458,7 @@ __global__ void k_tet_stats(ProblemView P, const float* ref, float* stats, int* 
 struct FeatureInputs {
   const float4* img_s;  // quad copies of the two images
   const float4* img_t;
-  const float4* bary;   // [kPoints] points of a tet, barycentric
+  const float4* bary;   // [kHalton] interior points, barycentric
   const float* stats;   // [n_tets][8]
   float h_scale;
   float inv_h;          // 1 / h_scale
@@ -559,13 +586,71 @@ __device__ __forceinline__ void column_vertices(const float* cols, const int4 tv
     }
 }
 
+// h at every mesh point and edge midpoint of n candidates given by columns
+// (C rows a point): out [n_points + n_edges][n].  The tets around a point or an
+// edge share its value: in the 800-point mesh 3,402 tets read 34,020 values, of
+// which 5,400 differ.  A wave takes a point or an edge of 64 candidates; bound
+// by the columns it reads (4,096 offspring: 125 us with every candidate's
+// items on all XCDs, 103 us with each XCD's own).
+template <bool kBig, int C>
+__global__ __launch_bounds__(256) void k_shared_points(ProblemView P, const float* cols, int n, const int2* edge_ends,
+                                                       int n_edges, FeatureInputs F, float* out) {
+  const unsigned item_blocks = (static_cast<unsigned>(P.n_points) + n_edges + 3) / 4, groups = (n + 63u) / 64;
+  unsigned ib, group;
+  if (groups >= 8) {
+    // blocks go to the 8 XCDs in turn: each takes its own candidates, whose
+    // columns its L2 holds
+    const unsigned q = blockIdx.x / 8;
+    ib = q % item_blocks;
+    group = q / item_blocks * 8 + blockIdx.x % 8;
+  } else {
+    ib = blockIdx.x / groups;
+    group = blockIdx.x % groups;
+  }
+  const int item = __builtin_amdgcn_readfirstlane(static_cast<int>(ib * 4 + (threadIdx.x >> 6)));
+  const unsigned cand = group * 64 + (threadIdx.x & 63);
+  if (item >= P.n_points + n_edges || cand >= static_cast<unsigned>(n)) return;
+  int a = item, b = item;
+  if (item >= P.n_points) {
+    const int2 e = edge_ends[item - P.n_points];
+    a = __builtin_amdgcn_readfirstlane(e.x);
+    b = __builtin_amdgcn_readfirstlane(e.y);
+  }
+  float va[6], vb[6];
+#pragma unroll
+  for (int k = 0; k < 6; k++) {
+    va[k] = cols[(static_cast<size_t>(a) * C + k) * n + cand];
+    vb[k] = cols[(static_cast<size_t>(b) * C + k) * n + cand];
+  }
+  // a point's two ends are itself: (v + v) / 2 = v
+  out[static_cast<size_t>(item) * n + cand] = h_mid<kBig>(P, F.img_s, F.img_t, va, vb, va + 3, vb + 3);
+}
+
+// The values of a tet's vertices and edges in candidate `cand`, as means.
+__device__ __forceinline__ void shared_means(const float* hs, int n_points, const int4 tv, const int te[6], int n,
+                                             unsigned cand, float m[3]) {
+  const int vs[4] = {tv.x, tv.y, tv.z, tv.w};
+  unsigned off = 4u * cand;
+  asm volatile("" : "+v"(off));   // kept as 32 bits, not widened ahead of a loop
+  float hv[4], he[6];
+#pragma unroll
+  for (int k = 0; k < 4; k++)
+    hv[k] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(hs + static_cast<size_t>(vs[k]) * n) + off);
+#pragma unroll
+  for (int k = 0; k < 6; k++)
+    he[k] = *reinterpret_cast<const float*>(
+        reinterpret_cast<const char*>(hs + (static_cast<size_t>(n_points) + te[k]) * n) + off);
+  corner_means(hv, he, m);
+}
+
 // Point means and mean intensity term of every (parent, tet) of parents
-// first .. first + n - 1, whose coordinates are given by columns: out
-// [parent][n_tets] (m0, m1, m2, term).  Threads in tet-major order, so that
-// the threads in flight read the same part of the images.
+// first .. first + n - 1, whose coordinates are given by columns and whose
+// shared points' values by hs: out [parent][n_tets] (m0, m1, m2, term).
+// Threads in tet-major order, so that the threads in flight read the same part
+// of the images.
 template <bool kBig>
-__global__ void k_parent_means(ProblemView P, const float* cols, int first, int n, const Record* rec,
-                               FeatureInputs F, float4* out) {
+__global__ void k_parent_means(ProblemView P, const float* cols, const float* hs, const int* tet_edges, int first,
+                               int n, const Record* rec, FeatureInputs F, float4* out) {
   const long long r = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (r >= static_cast<long long>(n) * P.n_tets) return;
   const int tet = static_cast<int>(r / n), cand = static_cast<int>(r % n);
@@ -573,7 +658,11 @@ __global__ void k_parent_means(ProblemView P, const float* cols, int first, int 
   float S[4][3], T[4][3], m[3];
   column_vertices<6>(cols, tv, 0, n, cand, S);
   column_vertices<6>(cols, tv, 3, n, cand, T);
-  point_means<kBig>(P, F.img_s, F.img_t, S, T, F.bary, m);
+  int te[6];
+#pragma unroll
+  for (int k = 0; k < 6; k++) te[k] = tet_edges[8 * static_cast<size_t>(tet) + k];
+  shared_means(hs, P.n_points, tv, te, n, cand, m);
+  m[2] = interior_mean<kBig>(P, F.img_s, F.img_t, S, T, F.bary);
   const size_t par = static_cast<size_t>(first) + cand;
   out[par * P.n_tets + tet] = make_float4(m[0], m[1], m[2], tet_mean_h(rec + par * P.n_tets * 2, tet));
 }
@@ -595,10 +684,12 @@ __global__ void k_parent_means(ProblemView P, const float* cols, int first, int 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
 typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i8v __attribute__((ext_vector_type(8)));
 
 // Read-only for the kernel and the same for a wave: scalar loads.
 typedef const __attribute__((address_space(4))) i4v* TetPtr;
 typedef const __attribute__((address_space(4))) float* StatPtr;
+typedef const __attribute__((address_space(4))) i8v* TetEdgePtr;
 
 constexpr int kPreIn = 32;                 // features padded: 23 + three constant 1s + zeros
 constexpr int kPreCands = 64;              // offspring per pre-screen wave: two tiles of the network
@@ -616,7 +707,7 @@ struct alignas(16) PreLds {
   bf16 w2[kHid][kW2Row];   // W2, columns permuted per 16-wide slice
   float b2[kHid];
   float w3[kHid];
-  float4 bary[kPoints];
+  float4 bary[kHalton];
 };
 
 __device__ __forceinline__ int slot_unit(int j) {   // 16-wide slice: slot j -> unit
@@ -697,17 +788,20 @@ __device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {
 // forms the features, which half-wave exchanges turn into the B operands of
 // two tiles of the network.
 //
-// What bounds it: the 104 gathers of a tet's 26 points in two images (about
-// 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) and the
-// 2,500 vector instructions around them, 78% of the issue slots.  128x128x96
-// (3,402 tets), 4,096 offspring: 3,390 us with coordinates read as stored (a
-// line per lane for each of 36 words), half a tet's points per half wave and 3
-// waves per SIMD; 1,580 us with coordinates by columns (k_columns, 44 us);
-// 1,275 us with 4 waves per SIMD (blocks of 8: the weights' 46 KiB of LDS
-// allow two) and one-instruction ReLUs; 1,140 us as it stands, with both
-// points and coordinates of 64 offspring per load and quads of differences.
+// What bounds it: the 64 gathers of a tet's 16 interior points in two images
+// (about 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) and
+// the 2,000 vector instructions around them, about 75% of the issue slots.
+// 128x128x96 (3,402 tets), 4,096 offspring: 3,390 us with coordinates read as
+// stored (a line per lane for each of 36 words), half a tet's points per half
+// wave and 3 waves per SIMD; 1,580 us with coordinates by columns (k_columns,
+// 43 us); 1,275 us with 4 waves per SIMD (blocks of 8: the weights' 46 KiB of
+// LDS allow two) and one-instruction ReLUs; 1,140 us with both points and
+// coordinates of 64 offspring per load and quads of differences; 930 us as it
+// stands, the vertices' and midpoints' values taken from k_shared_points (103
+// us, and 155 -> 118 us in k_parent_means).
 template <bool kBig>
-__global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, const float* cols,
+__global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, const float* cols, const float* hs,
+                                                                 const int* tet_edges,
                                                                  const int* parent_of, int n_parents,
                                                                  FeatureInputs F, const float4* pmeans,
                                                                  const float* params, const bf16* w1b,
@@ -727,7 +821,7 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
     // four units of a slice are four slots in a row
     *reinterpret_cast<s4*>(&N.w2[j][(k0 & ~15) + unit_slot(k0 & 15)]) = ld4(w2b + j * kHid + k0);
   }
-  if (threadIdx.x < kPoints) N.bary[threadIdx.x] = F.bary[threadIdx.x];
+  if (threadIdx.x < kHalton) N.bary[threadIdx.x] = F.bary[threadIdx.x];
   float b1 = 0.f;
   if (threadIdx.x < kHid) {
     b1 = params[oB1 + threadIdx.x];
@@ -751,6 +845,7 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
   const long long n_waves = static_cast<long long>(gridDim.x) * kPreWaves;
   const TetPtr tets = (TetPtr)P.tets;
   const StatPtr stats = (StatPtr)F.stats;
+  const TetEdgePtr edge_ids = (TetEdgePtr)tet_edges;
   // work items (run of tets, group of 64 offspring), run-major, one per wave
   // at a time: the lanes of a wave read nearly the same image positions and
   // the waves in flight share a few runs of tets
@@ -790,7 +885,10 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
         column_vertices<9>(cols, tv, 3, n, col, d);
         wt = tet_volume(sv) + tet_volume(d);
         asm volatile("" : "+v"(wt));   // here, or the vertices stay in registers through the network
-        point_means<kBig>(P, F.img_s, F.img_t, sv, d, N.bary, m);
+        const i8v eq = edge_ids[tet];
+        const int te[6] = {eq[0], eq[1], eq[2], eq[3], eq[4], eq[5]};
+        shared_means(hs, P.n_points, tv, te, n, col, m);
+        m[2] = interior_mean<kBig>(P, F.img_s, F.img_t, sv, d, N.bary);
         f[1][4] = (m[0] - pm.x) * F.inv_h;
         f[1][5] = (m[1] - pm.y) * F.inv_h;
         f[1][6] = (m[2] - pm.z) * F.inv_h;
@@ -1312,10 +1410,13 @@ struct morea_surrogate {
   float* ref = nullptr;
   float4* img_s = nullptr;  // quad copies of the source and target images
   float4* img_t = nullptr;
-  float4* bary = nullptr;   // [kPoints] sample points of a tet, barycentric
+  float4* bary = nullptr;   // [kHalton] interior sample points of a tet, barycentric
+  int n_edges = 0;          // edges of the mesh, each once
+  int2* edge_ends = nullptr;   // [n_edges]
+  int* tet_edges = nullptr;    // [n_tets][8] a tet's edges (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), two unused
   float h_scale = 1.f;      // mean of (I_s - I_t)^2 over the grid (1 when 0)
   void* work = nullptr;     // pre-screen workspace: the parents' point means,
-  size_t work_cap = 0;      // then the per-(tile, offspring) partial sums (bytes)
+  size_t work_cap = 0;      // then the partial sums, columns and shared points' values (bytes)
   float* part = nullptr;    // training: the blocks' partial sums
   int steps = 0;
   std::vector<void*> allocs;
@@ -1381,19 +1482,12 @@ double radical_inverse(int j, int b) {
   return r;
 }
 
-// A tet's sample points as barycentric coordinates: the vertices, the edge
-// midpoints, then Halton points j = 1..16 in bases 2, 3, 5, each (u1, u2, u3)
-// sorted into a <= b <= c and mapped to (a, b - a, c - b, 1 - c) (the spacings
-// of sorted uniforms, uniform on the simplex).
-std::vector<float4> sample_points() {
+// The interior sample points: Halton points j = 1..16 in bases 2, 3, 5, each
+// (u1, u2, u3) sorted into a <= b <= c and mapped to the barycentric
+// coordinates (a, b - a, c - b, 1 - c) (the spacings of sorted uniforms,
+// uniform on the simplex).
+std::vector<float4> interior_points() {
   std::vector<float4> out;
-  float l[4];
-  for (int v = 0; v < 4; v++) out.push_back(make_float4(v == 0, v == 1, v == 2, v == 3));
-  for (int v = 0; v < 4; v++)
-    for (int w = v + 1; w < 4; w++) {
-      for (int k = 0; k < 4; k++) l[k] = k == v || k == w ? 0.5f : 0.f;
-      out.push_back(make_float4(l[0], l[1], l[2], l[3]));
-    }
   for (int j = 1; j <= kHalton; j++) {
     double u[3] = {radical_inverse(j, 2), radical_inverse(j, 3), radical_inverse(j, 5)};
     std::sort(u, u + 3);
@@ -1401,6 +1495,31 @@ std::vector<float4> sample_points() {
                               static_cast<float>(u[2] - u[1]), static_cast<float>(1.0 - u[2])));
   }
   return out;
+}
+
+// The mesh's edges, each once, in ascending order of their ends, and the tets'.
+void mesh_edges(const std::vector<int>& tets, std::vector<int2>& ends, std::vector<int>& of_tet) {
+  const size_t n_tets = tets.size() / 4;
+  std::vector<std::pair<std::pair<int, int>, size_t>> all;   // ends, place in of_tet
+  all.reserve(6 * n_tets);
+  for (size_t t = 0; t < n_tets; t++) {
+    size_t k = 8 * t;
+    for (int v = 0; v < 4; v++)
+      for (int w = v + 1; w < 4; w++) all.push_back({std::minmax(tets[4 * t + v], tets[4 * t + w]), k++});
+  }
+  std::sort(all.begin(), all.end());
+  of_tet.assign(8 * n_tets, 0);
+  for (size_t i = 0; i < all.size(); i++) {
+    if (i == 0 || all[i].first != all[i - 1].first) ends.push_back(make_int2(all[i].first.first, all[i].first.second));
+    of_tet[all[i].second] = static_cast<int>(ends.size()) - 1;
+  }
+}
+
+// Blocks of k_shared_points: 4 points or edges of 64 candidates each; from 8
+// groups of candidates on, a multiple of 8 groups.
+unsigned shared_blocks(size_t n_shared, int n) {
+  const size_t groups = (static_cast<size_t>(n) + 63) / 64;
+  return static_cast<unsigned>((n_shared + 3) / 4 * (groups >= 8 ? (groups + 7) / 8 * 8 : groups));
 }
 
 // The quad copies reach 4 GiB: sampled with 64-bit offsets.
@@ -1462,7 +1581,13 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
   ok(salloc(s, &s->ref, sizeof(float) * 3 * p->view.n_points));
   ok(salloc(s, &s->img_s, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
   ok(salloc(s, &s->img_t, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
-  ok(salloc(s, &s->bary, sizeof(float4) * kPoints));
+  ok(salloc(s, &s->bary, sizeof(float4) * kHalton));
+  std::vector<int2> ends;
+  std::vector<int> of_tet;
+  mesh_edges(p->tets_host, ends, of_tet);
+  s->n_edges = static_cast<int>(ends.size());
+  ok(salloc(s, &s->edge_ends, sizeof(int2) * ends.size()));
+  ok(salloc(s, &s->tet_edges, sizeof(int) * of_tet.size()));
   float* ref_dev = s->ref;
   if (st == MOREA_OK) {
     // He-normal initial weights, zero biases, from the given seed
@@ -1483,8 +1608,10 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
     ok(sdev(hipGetLastError(), "refresh"));
     ok(sdev(launch_stats(s, ref_dev), "tet statistics"));
     ok(sdev(launch_image_copies(s), "image copies"));
-    const std::vector<float4> bary = sample_points();
-    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kPoints, hipMemcpyHostToDevice), "upload"));
+    const std::vector<float4> bary = interior_points();
+    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kHalton, hipMemcpyHostToDevice), "upload"));
+    ok(sdev(hipMemcpy(s->edge_ends, ends.data(), sizeof(int2) * ends.size(), hipMemcpyHostToDevice), "upload"));
+    ok(sdev(hipMemcpy(s->tet_edges, of_tet.data(), sizeof(int) * of_tet.size(), hipMemcpyHostToDevice), "upload"));
     ok(sdev(hipDeviceSynchronize(), "surrogate set-up"));
   }
   if (st == MOREA_OK) {
@@ -1590,10 +1717,12 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   const size_t pm_bytes = (sizeof(float4) * rows + 255) / 256 * 256;
   const size_t part_bytes = (sizeof(float2) * static_cast<size_t>(n_runs) * pop + 255) / 256 * 256;
   // candidates laid out by columns at a time: all, unless that exceeds kColBytes
-  const size_t cand_bytes = 9 * sizeof(float) * static_cast<size_t>(P.n_points);
+  const size_t col_bytes = 9 * sizeof(float) * static_cast<size_t>(P.n_points);
+  const size_t n_shared = static_cast<size_t>(P.n_points) + s->n_edges;
+  const size_t cand_bytes = col_bytes + sizeof(float) * n_shared;
   const int slab = static_cast<int>(std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands));
-  const size_t need = pm_bytes + part_bytes +
-                      std::max(cand_bytes * std::min(slab, pop), cand_bytes / 9 * 6 * std::min(slab, n_parents));
+  const size_t most = static_cast<size_t>(std::min(slab, std::max(pop, n_parents)));
+  const size_t need = pm_bytes + part_bytes + cand_bytes * most;
   if (need > s->work_cap) {   // grow the workspace (hipFree waits for the device)
     if (s->work) (void)hipFree(s->work);
     s->work = nullptr;
@@ -1607,6 +1736,7 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   float4* pmeans = static_cast<float4*>(s->work);
   float2* partial = reinterpret_cast<float2*>(static_cast<char*>(s->work) + pm_bytes);
   float* cols = reinterpret_cast<float*>(static_cast<char*>(s->work) + pm_bytes + part_bytes);
+  float* hs = cols + col_bytes / sizeof(float) * most;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const FeatureInputs F = feature_inputs(s);
   const Parents Q{parent_pts, static_cast<const Record*>(parent_cache), parent_of, n_parents};
@@ -1616,10 +1746,18 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
     hipLaunchKernelGGL(k_columns<6>, dim3(col_tiles, (n + kColCands - 1) / kColCands, 6), dim3(256), 0, st, parent_pts,
                        first, n, P.n_points, Q, cols);
     const dim3 grid(static_cast<unsigned>((static_cast<size_t>(n) * P.n_tets + 255) / 256));
-    if (big_quads(P))
-      hipLaunchKernelGGL(k_parent_means<true>, grid, dim3(256), 0, st, P, cols, first, n, Q.rec, F, pmeans);
-    else
-      hipLaunchKernelGGL(k_parent_means<false>, grid, dim3(256), 0, st, P, cols, first, n, Q.rec, F, pmeans);
+    const dim3 shared_grid(shared_blocks(n_shared, n));
+    if (big_quads(P)) {
+      hipLaunchKernelGGL((k_shared_points<true, 6>), shared_grid, dim3(256), 0, st, P, cols, n, s->edge_ends,
+                         s->n_edges, F, hs);
+      hipLaunchKernelGGL(k_parent_means<true>, grid, dim3(256), 0, st, P, cols, hs, s->tet_edges, first, n, Q.rec, F,
+                         pmeans);
+    } else {
+      hipLaunchKernelGGL((k_shared_points<false, 6>), shared_grid, dim3(256), 0, st, P, cols, n, s->edge_ends,
+                         s->n_edges, F, hs);
+      hipLaunchKernelGGL(k_parent_means<false>, grid, dim3(256), 0, st, P, cols, hs, s->tet_edges, first, n, Q.rec, F,
+                         pmeans);
+    }
   }
   for (int first = 0; first < pop; first += slab) {
     const int n = std::min(slab, pop - first);
@@ -1628,12 +1766,18 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
     const long long items = static_cast<long long>(n_runs) * ((n + kPreCands - 1) / kPreCands);
     const dim3 grid(static_cast<unsigned>(std::min<long long>((items + kPreWaves - 1) / kPreWaves, kPreItems / kPreWaves)));
     const dim3 block(64 * kPreWaves);
-    if (big_quads(P))
-      hipLaunchKernelGGL(k_prescreen<true>, grid, block, 0, st, P, cols, parent_of + first, n_parents, F, pmeans,
-                         s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
-    else
-      hipLaunchKernelGGL(k_prescreen<false>, grid, block, 0, st, P, cols, parent_of + first, n_parents, F, pmeans,
-                         s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
+    const dim3 shared_grid(shared_blocks(n_shared, n));
+    if (big_quads(P)) {
+      hipLaunchKernelGGL((k_shared_points<true, 9>), shared_grid, dim3(256), 0, st, P, cols, n, s->edge_ends,
+                         s->n_edges, F, hs);
+      hipLaunchKernelGGL(k_prescreen<true>, grid, block, 0, st, P, cols, hs, s->tet_edges, parent_of + first, n_parents,
+                         F, pmeans, s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
+    } else {
+      hipLaunchKernelGGL((k_shared_points<false, 9>), shared_grid, dim3(256), 0, st, P, cols, n, s->edge_ends,
+                         s->n_edges, F, hs);
+      hipLaunchKernelGGL(k_prescreen<false>, grid, block, 0, st, P, cols, hs, s->tet_edges, parent_of + first,
+                         n_parents, F, pmeans, s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
+    }
   }
   hipLaunchKernelGGL(k_prescreen_reduce, dim3((pop + 63) / 64), dim3(64 * kScoreGroups), 0, st, partial, n_runs, pop,
                      Q, score);
