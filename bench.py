@@ -40,7 +40,7 @@ HBM_PEAK = 8.0e12
 # changed since, and the traffic is reported as null
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_eval_full_128x128x96_pop512_counters.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2303_04873_amd", "csrc", f)
-                  for f in ("morea_eval.hip", "morea_internal.h")]
+                  for f in ("morea_eval.hip", "morea_raster.h", "morea_internal.h")]
 
 
 def kernel_source_hash():

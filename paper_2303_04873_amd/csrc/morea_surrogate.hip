@@ -589,7 +589,7 @@ __device__ __forceinline__ void column_vertices(const float* cols, const int4 tv
 // h at every mesh point and edge midpoint of n candidates given by columns
 // (C rows a point): out [n_points + n_edges][n].  The tets around a point or an
 // edge share its value: in the 800-point mesh 3,402 tets read 34,020 values, of
-// which 5,400 differ.  A wave takes a point or an edge of 64 candidates; bound
+// which 5,415 differ.  A wave takes a point or an edge of 64 candidates; bound
 // by the columns it reads (4,096 offspring: 125 us with every candidate's
 // items on all XCDs, 103 us with each XCD's own).
 template <bool kBig, int C>
