@@ -266,17 +266,18 @@ __device__ __forceinline__ float h_mid(const ProblemView& P, const float4* img_s
   return h_at<kBig>(P, img_s, img_t, x, y);
 }
 
-// The points of a tet behind the estimated changes: its 4 vertices, the edge
-// midpoints (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), and kHalton interior points
-// given by barycentric coordinates `bary`.  Mean of h over the latter, added
-// in order, for a tet with vertices s (source) and t (target).
-template <bool kBig>
-__device__ __forceinline__ float interior_mean(const ProblemView& P, const float4* img_s, const float4* img_t,
-                                               const float s[4][3], const float t[4][3], const float4* bary) {
-  const Edges S = edges(s), T = edges(t);
+// The points of a tet behind the estimated changes, as barycentric
+// coordinates `bary`: its 4 vertices, the edge midpoints (0,1) (0,2) (0,3)
+// (1,2) (1,3) (2,3), then kHalton interior points from kInner on.
+constexpr int kInner = 10, kPoints = kInner + kHalton;
+
+// Sum of h at N points of a tet, in order, one at a time.
+template <bool kBig, int N>
+__device__ __forceinline__ float point_run(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                           const Edges& S, const Edges& T, const float4* bary) {
   float sum = 0.f;
 #pragma unroll 1
-  for (int q = 0; q < kHalton; q++) {
+  for (int q = 0; q < N; q++) {
     const float4 l = bary[q];
     float x[3], y[3];
 #pragma unroll
@@ -286,7 +287,15 @@ __device__ __forceinline__ float interior_mean(const ProblemView& P, const float
     }
     sum += h_at<kBig>(P, img_s, img_t, x, y);
   }
-  return sum * (1.f / kHalton);
+  return sum;
+}
+
+// Mean of h over the interior points (`inner`) of a tet with vertices s
+// (source) and t (target).
+template <bool kBig>
+__device__ __forceinline__ float interior_mean(const ProblemView& P, const float4* img_s, const float4* img_t,
+                                               const float s[4][3], const float t[4][3], const float4* inner) {
+  return point_run<kBig, kHalton>(P, img_s, img_t, edges(s), edges(t), inner) * (1.f / kHalton);
 }
 
 // Means from the values at the 4 vertices and at the 6 midpoints.
@@ -300,16 +309,10 @@ __device__ __forceinline__ void corner_means(const float hv[4], const float he[6
 template <bool kBig>
 __device__ __forceinline__ void point_means(const ProblemView& P, const float4* img_s, const float4* img_t,
                                             const float s[4][3], const float t[4][3], const float4* bary, float m[3]) {
-  float hv[4], he[6];
-#pragma unroll
-  for (int v = 0; v < 4; v++) hv[v] = h_at<kBig>(P, img_s, img_t, s[v], t[v]);
-  int k = 0;
-#pragma unroll
-  for (int v = 0; v < 4; v++)
-#pragma unroll
-    for (int w = v + 1; w < 4; w++) he[k++] = h_mid<kBig>(P, img_s, img_t, s[v], s[w], t[v], t[w]);
-  corner_means(hv, he, m);
-  m[2] = interior_mean<kBig>(P, img_s, img_t, s, t, bary);
+  const Edges S = edges(s), T = edges(t);
+  m[0] = point_run<kBig, 4>(P, img_s, img_t, S, T, bary) * 0.25f;
+  m[1] = point_run<kBig, 6>(P, img_s, img_t, S, T, bary + 4) * (1.f / 6.f);
+  m[2] = point_run<kBig, kHalton>(P, img_s, img_t, S, T, bary + kInner) * (1.f / kHalton);
 }
 
 // |signed volume| (voxel^3): the expected samples of the tet in its direction.
@@ -458,7 +461,7 @@ __global__ void k_tet_stats(ProblemView P, const float* ref, float* stats, int* 
 struct FeatureInputs {
   const float4* img_s;  // quad copies of the two images
   const float4* img_t;
-  const float4* bary;   // [kHalton] interior points, barycentric
+  const float4* bary;   // [kPoints] points of a tet, barycentric
   const float* stats;   // [n_tets][8]
   float h_scale;
   float inv_h;          // 1 / h_scale
@@ -662,7 +665,7 @@ __global__ void k_parent_means(ProblemView P, const float* cols, const float* hs
 #pragma unroll
   for (int k = 0; k < 6; k++) te[k] = tet_edges[8 * static_cast<size_t>(tet) + k];
   shared_means(hs, P.n_points, tv, te, n, cand, m);
-  m[2] = interior_mean<kBig>(P, F.img_s, F.img_t, S, T, F.bary);
+  m[2] = interior_mean<kBig>(P, F.img_s, F.img_t, S, T, F.bary + kInner);
   const size_t par = static_cast<size_t>(first) + cand;
   out[par * P.n_tets + tet] = make_float4(m[0], m[1], m[2], tet_mean_h(rec + par * P.n_tets * 2, tet));
 }
@@ -821,7 +824,7 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
     // four units of a slice are four slots in a row
     *reinterpret_cast<s4*>(&N.w2[j][(k0 & ~15) + unit_slot(k0 & 15)]) = ld4(w2b + j * kHid + k0);
   }
-  if (threadIdx.x < kHalton) N.bary[threadIdx.x] = F.bary[threadIdx.x];
+  if (threadIdx.x < kHalton) N.bary[threadIdx.x] = F.bary[kInner + threadIdx.x];
   float b1 = 0.f;
   if (threadIdx.x < kHid) {
     b1 = params[oB1 + threadIdx.x];
@@ -1410,7 +1413,7 @@ struct morea_surrogate {
   float* ref = nullptr;
   float4* img_s = nullptr;  // quad copies of the source and target images
   float4* img_t = nullptr;
-  float4* bary = nullptr;   // [kHalton] interior sample points of a tet, barycentric
+  float4* bary = nullptr;   // [kPoints] sample points of a tet, barycentric
   int n_edges = 0;          // edges of the mesh, each once
   int2* edge_ends = nullptr;   // [n_edges]
   int* tet_edges = nullptr;    // [n_tets][8] a tet's edges (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), two unused
@@ -1482,12 +1485,19 @@ double radical_inverse(int j, int b) {
   return r;
 }
 
-// The interior sample points: Halton points j = 1..16 in bases 2, 3, 5, each
-// (u1, u2, u3) sorted into a <= b <= c and mapped to the barycentric
-// coordinates (a, b - a, c - b, 1 - c) (the spacings of sorted uniforms,
-// uniform on the simplex).
-std::vector<float4> interior_points() {
+// A tet's sample points as barycentric coordinates: the vertices, the edge
+// midpoints, then Halton points j = 1..16 in bases 2, 3, 5, each (u1, u2, u3)
+// sorted into a <= b <= c and mapped to (a, b - a, c - b, 1 - c) (the spacings
+// of sorted uniforms, uniform on the simplex).
+std::vector<float4> sample_points() {
   std::vector<float4> out;
+  float l[4];
+  for (int v = 0; v < 4; v++) out.push_back(make_float4(v == 0, v == 1, v == 2, v == 3));
+  for (int v = 0; v < 4; v++)
+    for (int w = v + 1; w < 4; w++) {
+      for (int k = 0; k < 4; k++) l[k] = k == v || k == w ? 0.5f : 0.f;
+      out.push_back(make_float4(l[0], l[1], l[2], l[3]));
+    }
   for (int j = 1; j <= kHalton; j++) {
     double u[3] = {radical_inverse(j, 2), radical_inverse(j, 3), radical_inverse(j, 5)};
     std::sort(u, u + 3);
@@ -1581,7 +1591,7 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
   ok(salloc(s, &s->ref, sizeof(float) * 3 * p->view.n_points));
   ok(salloc(s, &s->img_s, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
   ok(salloc(s, &s->img_t, sizeof(float4) * static_cast<size_t>(p->view.pvox)));
-  ok(salloc(s, &s->bary, sizeof(float4) * kHalton));
+  ok(salloc(s, &s->bary, sizeof(float4) * kPoints));
   std::vector<int2> ends;
   std::vector<int> of_tet;
   mesh_edges(p->tets_host, ends, of_tet);
@@ -1608,8 +1618,8 @@ morea_status morea_surrogate_create(morea_problem* p, int32_t max_rows, uint64_t
     ok(sdev(hipGetLastError(), "refresh"));
     ok(sdev(launch_stats(s, ref_dev), "tet statistics"));
     ok(sdev(launch_image_copies(s), "image copies"));
-    const std::vector<float4> bary = interior_points();
-    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kHalton, hipMemcpyHostToDevice), "upload"));
+    const std::vector<float4> bary = sample_points();
+    ok(sdev(hipMemcpy(s->bary, bary.data(), sizeof(float4) * kPoints, hipMemcpyHostToDevice), "upload"));
     ok(sdev(hipMemcpy(s->edge_ends, ends.data(), sizeof(int2) * ends.size(), hipMemcpyHostToDevice), "upload"));
     ok(sdev(hipMemcpy(s->tet_edges, of_tet.data(), sizeof(int) * of_tet.size(), hipMemcpyHostToDevice), "upload"));
     ok(sdev(hipDeviceSynchronize(), "surrogate set-up"));
@@ -1720,15 +1730,22 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   const size_t col_bytes = 9 * sizeof(float) * static_cast<size_t>(P.n_points);
   const size_t n_shared = static_cast<size_t>(P.n_points) + s->n_edges;
   const size_t cand_bytes = col_bytes + sizeof(float) * n_shared;
-  const int slab = static_cast<int>(std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands));
-  const size_t most = static_cast<size_t>(std::min(slab, std::max(pop, n_parents)));
-  const size_t need = pm_bytes + part_bytes + cand_bytes * most;
+  int slab = static_cast<int>(std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands));
+  size_t most = static_cast<size_t>(std::min(slab, std::max(pop, n_parents)));
+  size_t need = pm_bytes + part_bytes + cand_bytes * most;
   if (need > s->work_cap) {   // grow the workspace (hipFree waits for the device)
     if (s->work) (void)hipFree(s->work);
     s->work = nullptr;
     s->work_cap = 0;
     void* d = nullptr;
-    const hipError_t e = hipMalloc(&d, need);
+    hipError_t e = hipMalloc(&d, need);
+    if (e != hipSuccess && most > kPreCands) {   // the smallest slabs then
+      (void)hipGetLastError();
+      slab = kPreCands;
+      most = kPreCands;
+      need = pm_bytes + part_bytes + cand_bytes * most;
+      e = hipMalloc(&d, need);
+    }
     if (e != hipSuccess) return sfail(MOREA_ENOMEM, "hipMalloc(%zu): %s", need, hipGetErrorString(e));
     s->work = d;
     s->work_cap = need;
