@@ -287,13 +287,14 @@ morea_status morea_reserve_partial(morea_problem *p, int32_t max_evals);
  *                 evaluations in order; [k][m][a] = mesh m, axis a (an
  *                 evaluation whose group index is out of range owns no rows)
  *   obj, flags, severity, counts: [n_evals] as in morea_eval_full
- * All arrays are device pointers.  The three kernels of a call (list prefix
- * sums, one persistent launch that takes (evaluation, dependent tet,
- * direction) items from a device work queue, and the per-evaluation
- * reduction) are captured into a HIP graph and replayed while the pointer
- * arguments and sizes match one of the last 8 argument sets (see
- * morea_partial_graphs); other calls capture a new graph.  Out-of-range eval_parent / eval_group entries give
- * that evaluation flags bit 2 and NaN objectives.  The evaluation list is
+ * All arrays are device pointers.  The kernels of a call (list prefix sums,
+ * one launch over the (evaluation, dependent tet) items -- a grid, or
+ * persistent blocks that take them from a device work queue -- and the
+ * per-evaluation reduction) are captured into a HIP graph and replayed while
+ * the pointer arguments and sizes match one of the last 8 argument sets (see
+ * morea_partial_graphs); other calls capture a new graph.  Out-of-range
+ * eval_parent / eval_group entries give that evaluation flags bit 2 and NaN
+ * objectives.  The evaluation list is
  * staged through a library-owned device workspace, so calls on one problem
  * must not overlap (use one stream per problem).  Errors: MOREA_ESTATE (no groups or no
  * reservation), MOREA_ERANGE (n_evals or rows beyond the reservation),

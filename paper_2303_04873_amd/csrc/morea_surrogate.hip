@@ -10,9 +10,10 @@
 // surrogate has no counterpart in the paper; it sits in front of the exact
 // evaluation, which stays the judge of every selected candidate.
 //
-// Dense layers run on the matrix cores: v_mfma_f32_32x32x8_bf16 with BF16
-// operands and FP32 accumulation, one 64-lane wave per tile of 32 rows.
-// Lane l holds row (A) / column (B) l % 32 and the k-quad 4 * (l / 32);
+// Dense layers run on the matrix cores with BF16 operands and FP32
+// accumulation; the pre-screen and the training on v_mfma_f32_32x32x16_bf16
+// (layouts below), explicit rows' predictions on v_mfma_f32_32x32x8_bf16, one
+// 64-lane wave per tile of 32 rows: lane l holds row (A) / column (B) l % 32 and the k-quad 4 * (l / 32);
 // accumulator element r of lane l is row 8 (r / 4) + 4 (l / 32) + r % 4,
 // column l % 32.  Master weights, gradients and the Adam state are FP32.
 #include <math.h>
@@ -713,12 +714,8 @@ struct alignas(16) PreLds {
   float4 bary[kHalton];
 };
 
-__device__ __forceinline__ int slot_unit(int j) {   // 16-wide slice: slot j -> unit
-  const int h = j >> 3, kk = j & 7;
-  return kk < 4 ? 4 * h + kk : 8 + 4 * h + (kk - 4);
-}
-
-__device__ __forceinline__ int unit_slot(int u) {   // inverse of slot_unit
+// Slot of unit u of a 16-wide slice in that order.
+__device__ __forceinline__ int unit_slot(int u) {
   return u < 8 ? 8 * (u >> 2) + (u & 3) : 8 * ((u - 8) >> 2) + 4 + (u & 3);
 }
 
@@ -1007,7 +1004,7 @@ __global__ __launch_bounds__(256) void k_predict_rows(const float* X, int n, con
 // as whole fragments, because wave w sums rows 32 w .. of dW2 over the rows of
 // all four waves (64 accumulators a wave; all of dW2 in every wave would take
 // 256 and spill).  The k slots of an accumulator used as an operand are in
-// the order of slot_unit, so W2 and its transpose are stored in that order.
+// the order of unit_slot, so W2 and its transpose are stored in that order.
 //
 // Bound: 154 KB of LDS (both orders of W2 and the fragments) leave one block
 // on a compute unit, one wave on a SIMD, so it is the chain of a block's
