@@ -524,20 +524,22 @@ morea_status morea_debug_distance_map(morea_problem *p, int32_t image, int32_t s
  * waves beyond the actual item count returning at once) on the given inputs
  * with HIP events and keeps the fastest for later morea_eval_partial calls.
  * Synchronous; overwrites the output arrays.  *best_ms (may be NULL) receives
- * the best time.  Untuned, every call takes the grid form unless its bound is
- * far above the items, and else 4 persistent blocks per compute unit (at most
- * the occupancy limit) and 8 items per pop, the shape that
- * morea_partial_shape reports until one is tuned or set.  Errors as
- * morea_eval_partial. */
+ * the best time.  Untuned, calls take the grid form unless its bound is far
+ * above the items (the largest dependent-tet list is more than 64 times the
+ * average one) or its largest launch, that of the reservation, would not be
+ * possible, and else 4 persistent blocks per compute unit (at most the
+ * occupancy limit) and 8 items per pop.  Errors as morea_eval_partial. */
 morea_status morea_tune_partial(morea_problem *p, const float *parent_pts, int32_t n_parents,
                                 const void *parent_cache, int32_t n_evals,
                                 const int32_t *eval_parent, const int32_t *eval_group,
                                 const float *new_coords, float *obj, uint8_t *flags,
                                 float *severity, uint32_t *counts, void *stream, float *best_ms);
 
-/* Current launch shape of partial evaluation: persistent blocks of 256
- * threads and items per queue pop, or *chunk = 0 (and *blocks = 0) for the
- * grid form.  Errors: MOREA_EINVAL. */
+/* Launch shape that morea_eval_partial takes, tuned, set or by default:
+ * persistent blocks of 256 threads and items per queue pop, or *chunk = 0
+ * (and *blocks = 0) for the grid form; setting it changes nothing.  Before
+ * the first morea_reserve_partial, unless one is set: *blocks = 0, *chunk =
+ * -1.  Errors: MOREA_EINVAL. */
 morea_status morea_partial_shape(const morea_problem *p, int32_t *blocks, int32_t *chunk);
 
 /* Set the launch shape of partial evaluation (as morea_tune_partial would):

@@ -501,7 +501,7 @@ morea_status morea_set_groups(morea_problem* p, int32_t n_groups, const int32_t*
   }
   p->n_groups = n_groups;
   p->max_dep = max_dep;
-  p->mean_dep = (dep_off[n_groups] + n_groups - 1) / n_groups;
+  p->mean_dep = static_cast<int>((static_cast<long long>(dep_off[n_groups]) + n_groups - 1) / n_groups);
   p->max_group = max_group;
   return MOREA_OK;
 }
@@ -596,16 +596,25 @@ static hipError_t partial_launch(morea_problem* p, const float* parent_pts, int3
                         counts, s);
 }
 
-// Shape of a call without a tuned or set one: the grid form, which launches
-// waves for n_evals x the largest dependent-tet list (128x128x96, 512 x 64
-// groups: 37.8 ms, 4 persistent blocks per compute unit with 8 items per pop
-// 40.5; 32^3, 16 x 8 groups: 55 us against 154, where a wave takes its 8
-// items one after the other).  The waves beyond the items return at once:
-// 21 million of them cost 0.3 ms beside 0.36 million items in 5.9 ms (6.7 ms
-// persistent), so the forms meet where the bound is about 150 times the items;
-// the line is at 64, and where a launch would exceed 2^32 threads.
-static bool grid_bound_ok(const morea_problem* p, int32_t n_evals) {
-  return p->max_dep <= 64 * p->mean_dep && static_cast<long long>(n_evals) * p->max_dep <= (1LL << 26);
+// Whether partial evaluation takes the grid form as long as no shape is tuned
+// or set.  It launches waves for n_evals x the largest dependent-tet list
+// (128x128x96, 512 x 64 groups: 37.8 ms, 4 persistent blocks per compute unit
+// with 8 items per pop 40.5; 32^3, 16 x 8 groups: 55 us against 154, where a
+// wave takes its 8 items one after the other).  The waves beyond the items
+// return at once: 21 million of them cost 0.3 ms beside 0.36 million items in
+// 5.9 ms (6.7 ms persistent), so the forms meet where the bound is about 150
+// times the items; the line is at 64, and where a launch would exceed 2^32
+// threads.  It looks at the groups and the reservation alone, so that every
+// call takes the form that morea_partial_shape reports.
+static bool grid_by_default(const morea_problem* p) {
+  return p->max_dep <= 64LL * p->mean_dep && static_cast<long long>(p->max_evals) * p->max_dep <= (1LL << 26);
+}
+
+// The shape that a call takes.
+static void current_shape(const morea_problem* p, int& blocks, int& chunk) {
+  const bool grid = !p->partial_chosen && p->max_evals > 0 && grid_by_default(p);
+  blocks = grid ? 0 : p->partial_blocks;
+  chunk = grid ? 0 : p->partial_chunk;
 }
 
 morea_status morea_eval_partial(morea_problem* p, const float* parent_pts, int32_t n_parents,
@@ -622,8 +631,8 @@ morea_status morea_eval_partial(morea_problem* p, const float* parent_pts, int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   const void* key[9] = {parent_pts, parent_cache, eval_parent, eval_group, new_coords, obj, flags,
                         severity, counts};
-  const bool grid = !p->partial_chosen && grid_bound_ok(p, n_evals);
-  const int use_blocks = grid ? 0 : p->partial_blocks, use_chunk = grid ? 0 : p->partial_chunk;
+  int use_blocks, use_chunk;
+  current_shape(p, use_blocks, use_chunk);
   const int key_n[4] = {n_parents, n_evals, use_blocks, use_chunk};
   morea_problem::GraphSlot* slot = nullptr;
   for (auto& g : p->graphs)
@@ -753,8 +762,7 @@ morea_status morea_set_partial_shape(morea_problem* p, int32_t blocks, int32_t c
 
 morea_status morea_partial_shape(const morea_problem* p, int32_t* blocks, int32_t* chunk) {
   if (!p || !blocks || !chunk) return fail(MOREA_EINVAL, "NULL argument");
-  *blocks = p->partial_blocks;
-  *chunk = p->partial_chunk;
+  current_shape(p, *blocks, *chunk);
   return MOREA_OK;
 }
 
