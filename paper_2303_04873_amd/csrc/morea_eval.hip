@@ -1317,6 +1317,9 @@ template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int,
 // the population it is in.
 constexpr int kFinalThreads = 1024;
 static_assert(kFinalThreads / kWave == 16, "one row of lanes adds the waves' sums");
+// candidates along the grid's x axis: a launch holds less than 2^32 threads per
+// axis, so larger populations take further rows of it
+constexpr int kFinalColumns = 1 << 21;
 
 struct Sums {
   float v[8];      // h, g, magnitude, violating volume, each as high and low part
@@ -1337,10 +1340,11 @@ __device__ __forceinline__ void add_lane(Sums& s) {
     s.n[k] += __builtin_amdgcn_update_dpp(0, static_cast<int>(s.n[k]), ctrl, rows, 0xf, false);
 }
 
-__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, const Record* rec,
-                                                            float* obj, uint8_t* flags, float* severity,
-                                                            uint32_t* counts, Totals* totals) {
-  const int cand = blockIdx.x;
+__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, int pop,
+                                                            const Record* rec, float* obj, uint8_t* flags,
+                                                            float* severity, uint32_t* counts, Totals* totals) {
+  const int cand = static_cast<int>(blockIdx.y * kFinalColumns + blockIdx.x);
+  if (cand >= pop) return;
   const int tid = threadIdx.x;
   Sums S = {};
   const Record* rc = rec + static_cast<size_t>(cand) * P.n_tets * 2;
@@ -1493,8 +1497,9 @@ hipError_t launch_finalize(const ProblemView& P, const float* pts, int pop, cons
                            float* obj, uint8_t* flags, float* severity, uint32_t* counts,
                            Totals* totals, hipStream_t s) {
   if (pop == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finalize, dim3(pop), dim3(kFinalThreads), 0, s, P, pts, rec, obj, flags, severity,
-                     counts, totals);
+  const dim3 grid(pop < kFinalColumns ? pop : kFinalColumns, (pop - 1) / kFinalColumns + 1);
+  hipLaunchKernelGGL(k_finalize, grid, dim3(kFinalThreads), 0, s, P, pts, pop, rec, obj, flags, severity, counts,
+                     totals);
   return hipGetLastError();
 }
 
