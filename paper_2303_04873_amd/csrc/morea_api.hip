@@ -588,7 +588,8 @@ static hipError_t partial_launch(morea_problem* p, const float* parent_pts, int3
   int per_wave = 2;
   if (chunk == 0) {   // grid form: waves up to the bound n_evals x max_dep of the item count
     const long long bound = static_cast<long long>(n_evals) * std::max(p->max_dep, 1);
-    per_wave = items_per_wave(p->view, static_cast<long long>(n_evals) * p->mean_dep);
+    // one item a wave for few items, if the launch stays below 2^32 threads
+    per_wave = bound <= 4LL * ((1 << 24) - 1) ? items_per_wave(p->view, static_cast<long long>(n_evals) * p->mean_dep) : 2;
     blocks = static_cast<int>(std::min<long long>((bound + 4 * per_wave - 1) / (4 * per_wave), 0x7fffffffLL));
   }
   return launch_partial(p->view, p->storage, I, n_parents, p->n_groups, prec, ptot,

@@ -115,3 +115,38 @@ def test_untuned_parts_equal_the_whole(count):
     for first in (0, n - count):
         part = lists.run(first, first + count)
         same(part, {k: v[first:first + count] for k, v in whole.items()}, f"{first}")
+
+
+def test_grid_form_with_a_wide_bound():
+    """2,400 evaluations with 2,000 items of two tets on average, but one group
+    of 30,000: the grid covers 72 million items, whose waves fit a launch at
+    two items each only."""
+    rs = np.random.default_rng(11)
+    n_tets, n_pts, n = 30000, 400, 2400
+    pts = rs.uniform(1, 30, (n_pts, 3)).astype(np.float32)
+    tets = np.stack([np.concatenate([[0], 2 + rs.choice(n_pts - 2, 3, replace=False)]) for _ in range(n_tets)])
+    tets[0, 3] = 1                                    # the only tet of point 1
+    v = pts[tets].astype(np.float64)
+    tets = tets[np.abs(np.linalg.det(v[:, 1:] - v[:, :1])) > 1e-2].astype(np.int32)
+    assert (tets == 1).sum() == 1
+    dep = len(tets)
+    img = [rs.uniform(0, 1, (32, 32, 32)).astype(np.float32) for _ in range(2)]
+    prob = morea.Problem((32, 32, 32), img[0], img[1], tets, pts, np.ones(dep, np.float32), [], [], radius=1.0,
+                         max_population=2)
+    groups = np.ones(dep, np.int32)                   # point 1, but the first: point 0
+    groups[0] = 0
+    prob.set_groups(np.arange(dep + 1, dtype=np.int32), groups)
+    prob.reserve_partial(n)
+    assert prob.partial_shape() != (0, 0)             # uneven
+    assert 1 << 26 <= n * dep < 1 << 27 and 2 * n <= 5120
+    par = torch.from_numpy(np.stack([np.stack([pts.T, pts.T + np.float32(0.25)])] * 2)).cuda().contiguous()
+    cache = prob.new_cache(2)
+    prob.eval_full(par, cache=cache)
+    ep = torch.from_numpy(rs.integers(0, 2, n).astype(np.int32)).cuda()
+    eg = torch.from_numpy(np.where(np.arange(n) == 1200, 0, 5).astype(np.int32)).cuda()
+    new = torch.from_numpy(rs.uniform(1, 30, (n, 2, 3)).astype(np.float32)).cuda()
+    outs = []
+    for shape in [(0, 0), (256, 8)]:
+        prob.set_partial_shape(*shape)
+        outs.append(to_host(prob.eval_partial(par, cache, ep, eg, new)))
+    same(outs[0], outs[1], "grid and persistent")
