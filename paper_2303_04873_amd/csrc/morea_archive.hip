@@ -40,8 +40,9 @@
 // registers, counts the boxes of each resolution in a hash table in LDS (the
 // number of different keys does not depend on the order of insertion; the
 // earliest candidate of a box is the smallest order value written to its
-// entry, a member's stamp or, above all stamps, the offer's index) and hands
-// out the slots by block prefixes.
+// entry, a member's stamp and slot or, above all stamps, the offer's index:
+// no two alike, whatever the caller's stamps) and hands out the slots by block
+// prefixes.
 #include <math.h>
 #include <stdio.h>
 
@@ -65,8 +66,8 @@ __device__ __forceinline__ bool pareto(float a0, float a1, float a2, float b0, f
 }
 
 struct Shared {
-  uint32_t key[kTable];      // box keys present
-  uint32_t order[kTable];    // smallest order value of the box
+  uint32_t key[kTable];              // box keys present
+  unsigned long long order[kTable];  // smallest order value of the box
   int free_slot[kMax];       // free slots in ascending order
   int wsum[kThreads / 64];
   float wmin[kThreads / 64];
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(kThreads) void k_update(int n_off, const float* __r
   // candidates of this thread: slots t, t + 1024, .. and offer t
   bool held[kPer], stay[kPer + 1];
   float v[kPer + 1][3];
-  uint32_t order[kPer + 1];
+  unsigned long long order[kPer + 1];
   int n_mine = 0;
 #pragma unroll
   for (int j = 0; j < kPer; j++) {
@@ -233,12 +234,12 @@ __global__ __launch_bounds__(kThreads) void k_update(int n_off, const float* __r
     const int st = s < cap ? arc_stamp[s] : -1;
     held[j] = st >= 0 || st == kGone;
     stay[j] = st >= 0;
-    order[j] = static_cast<uint32_t>(st);
+    order[j] = static_cast<unsigned long long>(static_cast<uint32_t>(st)) << 32 | static_cast<uint32_t>(s);
 #pragma unroll
     for (int o = 0; o < 3; o++) v[j][o] = stay[j] ? arc_obj[3 * s + o] : 0.f;
   }
   stay[kPer] = t < n_off && inserted[t] != 0;
-  order[kPer] = 0x80000000u + t;                // after every member
+  order[kPer] = (0x80000000ull + t) << 32;      // after every member
 #pragma unroll
   for (int o = 0; o < 3; o++) v[kPer][o] = stay[kPer] ? offer_obj[3 * t + o] : 0.f;
 #pragma unroll
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void k_update(int n_off, const float* __r
 #pragma unroll
       for (int q = 0; q < kTable / kThreads; q++) {
         S.key[t + q * kThreads] = kNoKey;
-        S.order[t + q * kThreads] = 0xffffffffu;
+        if (a == b) S.order[t + q * kThreads] = ~0ull;
       }
       __syncthreads();
       int fresh = 0, entry[kPer + 1];
