@@ -23,6 +23,7 @@
 // lane).  Samples whose mapped point lies within its error bound of a grid
 // plane, and samples inside a guidance band, are queued and resolved a full
 // wave at a time.
+#include <algorithm>
 #include <type_traits>
 
 #include "morea_internal.h"
@@ -1317,9 +1318,7 @@ template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int,
 // the population it is in.
 constexpr int kFinalThreads = 1024;
 static_assert(kFinalThreads / kWave == 16, "one row of lanes adds the waves' sums");
-// candidates along the grid's x axis: a launch holds less than 2^32 threads per
-// axis, so larger populations take further rows of it
-constexpr int kFinalColumns = 1 << 21;
+constexpr int kFinalLaunch = 1 << 21;   // candidates per launch: it holds less than 2^32 threads
 
 struct Sums {
   float v[8];      // h, g, magnitude, violating volume, each as high and low part
@@ -1340,11 +1339,10 @@ __device__ __forceinline__ void add_lane(Sums& s) {
     s.n[k] += __builtin_amdgcn_update_dpp(0, static_cast<int>(s.n[k]), ctrl, rows, 0xf, false);
 }
 
-__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, int pop,
-                                                            const Record* rec, float* obj, uint8_t* flags,
-                                                            float* severity, uint32_t* counts, Totals* totals) {
-  const int cand = static_cast<int>(blockIdx.y * kFinalColumns + blockIdx.x);
-  if (cand >= pop) return;
+__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, const Record* rec,
+                                                            float* obj, uint8_t* flags, float* severity,
+                                                            uint32_t* counts, Totals* totals) {
+  const int cand = blockIdx.x;
   const int tid = threadIdx.x;
   Sums S = {};
   const Record* rc = rec + static_cast<size_t>(cand) * P.n_tets * 2;
@@ -1497,9 +1495,12 @@ hipError_t launch_finalize(const ProblemView& P, const float* pts, int pop, cons
                            float* obj, uint8_t* flags, float* severity, uint32_t* counts,
                            Totals* totals, hipStream_t s) {
   if (pop == 0) return hipSuccess;
-  const dim3 grid(pop < kFinalColumns ? pop : kFinalColumns, (pop - 1) / kFinalColumns + 1);
-  hipLaunchKernelGGL(k_finalize, grid, dim3(kFinalThreads), 0, s, P, pts, pop, rec, obj, flags, severity, counts,
-                     totals);
+  for (size_t c = 0; c < static_cast<size_t>(pop); c += kFinalLaunch) {
+    const unsigned n = static_cast<unsigned>(std::min<size_t>(kFinalLaunch, pop - c));
+    hipLaunchKernelGGL(k_finalize, dim3(n), dim3(kFinalThreads), 0, s, P, pts + c * 6 * P.n_points,
+                       rec + c * P.n_tets * 2, obj + 3 * c, flags + c, severity + c, counts + 2 * c,
+                       totals ? totals + c : nullptr);
+  }
   return hipGetLastError();
 }
 

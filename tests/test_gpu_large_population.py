@@ -16,7 +16,7 @@ DISTINCT = 7
 @pytest.mark.parametrize("pop", [(1 << 21) - 1, 1 << 21, (1 << 22) + 3])
 def test_repeated_candidates_score_alike(pop):
     """A mesh of one tet; `pop` candidates repeat seven, whose outputs alone
-    they equal to the bit, with both estimators."""
+    they equal to the bit, with both estimators; so do their caches."""
     rs = np.random.default_rng(3)
     img = [rs.uniform(0, 1, (6, 6, 6)).astype(np.float32) for _ in range(2)]
     pts = np.array([[0.5, 0.25, 0.5], [4.5, 0.5, 1.0], [1.0, 4.25, 0.5], [1.5, 1.0, 4.75]], np.float32)
@@ -33,3 +33,11 @@ def test_repeated_candidates_score_alike(pop):
         for k, v in out.items():
             want = torch.from_numpy(alone[k]).cuda()[idx]
             assert torch.equal(torch.nan_to_num(v.float(), nan=-7.0), torch.nan_to_num(want.float(), nan=-7.0)), k
+    caches = []
+    for t in (few, many):
+        caches.append(prob.new_cache(len(t)))
+        prob.eval_full(t, cache=caches[-1])
+    for first, size in ((0, 48), (48, 64)):           # two records a candidate, then its totals
+        part = [c.view(torch.uint8)[first * n:(first + size) * n].view(n, size)
+                for c, n in zip(caches, (DISTINCT, pop))]
+        assert torch.equal(part[1], part[0][idx])
