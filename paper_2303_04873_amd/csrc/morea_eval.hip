@@ -380,9 +380,10 @@ __device__ __forceinline__ float ld_buf(__amdgpu_buffer_rsrc_t r, int idx) {
   }
 }
 
-// Two consecutive FP32 voxels (the first at byte offset `off`) in one 8-byte
-// buffer load; the scalar offset `soff` (bytes) selects the row of the pair.
-__device__ __forceinline__ F2 ld_pair(__amdgpu_buffer_rsrc_t r, int off, int soff) {
+// Two consecutive FP32 voxels (the first at byte offset `off`, which passes
+// 2^31 at the end of the largest volumes) in one 8-byte buffer load; the scalar
+// offset `soff` (bytes) selects the row of the pair.
+__device__ __forceinline__ F2 ld_pair(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
   typedef float f2v __attribute__((ext_vector_type(2)));
   const f2v v = __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
   return F2{v.x, v.y};
@@ -579,8 +580,9 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
                                                   unsigned& band) {
   const int e0 = vi + k;
   float f[2][3];
-  int base[2];       // byte offsets of the stencils' first corners (FP32), elements otherwise
-  constexpr int esize = ST == kF32 ? 4 : 2, bsize = ST == kF32 ? 4 : 1;
+  unsigned base[2];  // byte offsets of the stencils' first corners (FP32), elements otherwise
+  constexpr int esize = ST == kF32 ? 4 : 2;
+  constexpr unsigned bsize = ST == kF32 ? 4 : 1;
 #pragma unroll
   for (int s = 0; s < 2; s++) {
     const double kd = static_cast<double>(k + s);
@@ -591,7 +593,7 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
       c[t] = static_cast<int>(q);     // q > 0 for a valid sample: truncation is the floor
       f[s][t] = static_cast<float>(__builtin_amdgcn_fract(q));
     }
-    base[s] = __umul24(c[2], P.pxy * bsize) + (__umul24(c[1], P.px * bsize) + c[0] * bsize);
+    base[s] = __umul24(c[2], P.pxy * bsize) + (__umul24(c[1], P.px * bsize) + static_cast<unsigned>(c[0]) * bsize);
     amb[s] = near_grid(f[s], U.thr);
   }
   // loads: own voxels (one pair), the 2 x 4 corner pairs, the band bytes (one
@@ -600,7 +602,7 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
   bool fg8[2];
   const int sy = P.px * esize, sz = P.pxy * esize;   // row and slice offsets in bytes
   if constexpr (ST == kF32) {
-    const F2 own = ld_pair(r_own, e0 * 4, 0);
+    const F2 own = ld_pair(r_own, static_cast<unsigned>(e0) * 4u, 0);
     a[0] = own.a;
     a[1] = own.b;
 #pragma unroll
@@ -616,7 +618,7 @@ __device__ __forceinline__ void sample_pair_inner(const ProblemView& P, const Sa
     a[1] = hi16<ST>(own);
 #pragma unroll
     for (int s = 0; s < 2; s++) {
-      const uint32_t sh = static_cast<uint32_t>(base[s] & 1) << 4;
+      const uint32_t sh = (base[s] & 1u) << 4;
       const uint32_t w00 = ld_pair16(r_oth, base[s], 0, sh), w01 = ld_pair16(r_oth, base[s], sy, sh);
       const uint32_t w10 = ld_pair16(r_oth, base[s], sz, sh), w11 = ld_pair16(r_oth, base[s], sy + sz, sh);
       v[s][0] = lo16<ST>(w00); v[s][1] = hi16<ST>(w00); v[s][2] = lo16<ST>(w01); v[s][3] = hi16<ST>(w01);
