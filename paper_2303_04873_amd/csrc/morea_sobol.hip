@@ -338,10 +338,15 @@ __device__ __forceinline__ bool support(const float v[8], const Cell& c) {
   return f0 || (uz && f1);
 }
 
+// The terms of a point are rounded alike in every form (no contraction), so
+// that a candidate's sums do not depend on the form, hence the population, it
+// is evaluated in.
+
 // The guidance term of the sets in `bits` at cells cp, cq, added to g.
 __device__ __forceinline__ void map_terms(const ProblemView& P, unsigned bits, const float* map_own,
                                           const float* map_oth, const float* set_w, const Cell& cp, const Cell& cq,
                                           float& g) {
+#pragma clang fp contract(off)
   for (int s = 0; s < P.n_sets; s++) {
     if ((bits >> s) & 1u) {
       float v[8];
@@ -364,6 +369,7 @@ __device__ __forceinline__ void inner_sample(const ProblemView& P, const void* i
                                              const uint16_t* cells_own, const uint16_t* cells_oth,
                                              const float* map_own, const float* map_oth, const float* set_w,
                                              const float p[3], const float q[3], float& h, float& g) {
+#pragma clang fp contract(off)
   const Cell cp = inner_cell(P, p), cq = inner_cell(P, q);
   const unsigned kp = cells_own[cp.e], kq = cells_oth[cq.e];
   // with all weights nonzero a point is foreground where its cell has a
@@ -401,17 +407,27 @@ __device__ __forceinline__ void inner_sample(const ProblemView& P, const void* i
 // each: 14% longer).
 //
 // Staging has a fixed cost, a block's waves waiting for each other twice,
-// which the fuller blocks and the larger tets repay: 512 tets of cells of edge
-// n, `per` waves a block, without -> with: n = 12 (432 samples a tet, rate
-// 1.5), per 12: 918 -> 924 us; n = 13 (366), per 12: 842 -> 864, per 7: 252 ->
-// 341; n = 14 (457), per 12: 1,014 -> 968, per 11: 476 -> 523; n = 15 (562),
-// per 12: 1,234 -> 1,102, per 11: 587 -> 594; 844 samples, per 12: 1,754 ->
-// 1,405; from n = 17 the boxes do not fit.  So from 64,000 samples times per^2.
-// 128x128x96 with 3,402 tets, population 128: 2.90 -> 2.82, 3.34 -> 2.96 and
-// 3.67 -> 3.12 ms (three images).
+// which many samples in a block repay; and a block whose waves do not divide
+// over the four SIMDs leaves some of them waiting, where the waves of the plain
+// form fill them.  Plain against staged in us, 3,072 tets of cells of edge n,
+// `per` waves a block, 60 candidates (per 12) or 22 (per 11):
+//   per 12: n = 12, 432 samples a tet: 1,134 : 1,125; n = 14, 366: 1,071 : 1,053;
+//           n = 15, 450: 1,281 : 1,176, 844: 2,182 : 1,686
+//   per 11: n = 14, 457: 498 : 511; n = 15, 562: 602 : 581
+// and as the quotient, n = 15: per 9, 562 samples: 0.98, 703: 1.07; per 8, 450:
+// 0.98, 562: 1.08; per 7, 844: 1.10; per 4, 1,125: 0.99, 1,688: 1.10; per 3,
+// 1,688: 0.99, 2,812: 1.08; per 2, 9,000: 0.81; per 1: 0.63.
+// So from 4,900 samples of a block's candidates, times the share of the SIMDs'
+// turns that its waves take, and from 3 waves on: over 925 sizes (1 to 128
+// candidates, 173 to 10,900 samples) 0.3% slower than the better form of each.
+// With fewer blocks than the chip holds the line is higher (384 tets, 12
+// candidates, n = 14: 0.96 at 457 samples, 1.01 at 686); from n = 17 on the
+// boxes do not fit.  128x128x96 with 3,402 tets, population 128: 2.90 -> 2.82,
+// 3.34 -> 2.96 and 3.67 -> 3.12 ms (three images).
 constexpr int kBlockWaves = 12;
 constexpr int kBoxVoxels = 16256;
-constexpr double kStageSamples = 64000.0;   // samples a tet times per^2
+constexpr double kStageSamples = 4900.0;   // of a block's candidates
+constexpr int kStageWaves = 3;
 
 struct BoxLds {
   float v[kBoxVoxels];
@@ -449,6 +465,7 @@ __device__ __forceinline__ void staged_sample(const ProblemView& P, const BoxLds
                                               bool any_fg, bool any_band, const float* map_own, const float* map_oth,
                                               const float* set_w, const float p[3], const float q[3], float& h,
                                               float& g) {
+#pragma clang fp contract(off)
   const int px = floor_int(p[0]), py = floor_int(p[1]), pz = floor_int(p[2]);
   const int qx = floor_int(q[0]), qy = floor_int(q[1]), qz = floor_int(q[2]);
   const int ep = __mul24(pz, bo.sz) + (__mul24(py, bo.sy) + (px + bo.first));
@@ -485,6 +502,7 @@ __device__ __forceinline__ void outer_sample(const ProblemView& P, const void* i
                                              const uint16_t* cells_own, const uint16_t* cells_oth,
                                              const float* map_own, const float* map_oth, const float* set_w,
                                              const float p[3], const float q[3], float& h, float& g) {
+#pragma clang fp contract(off)
   bool fa, fb;
   const float a = image_at<ST>(P, img_own, cells_own, p[0], p[1], p[2], fa);
   const float b = image_at<ST>(P, img_oth, cells_oth, q[0], q[1], q[2], fb);
@@ -523,8 +541,8 @@ __device__ __forceinline__ int64_t det6(const int v[4][3]) {
   return a0 * (b1 * c2 - b2 * c1) - a1 * (b0 * c2 - b2 * c0) + a2 * (b0 * c1 - b1 * c0);
 }
 
-// Blocks of 4 waves; each XCD (blocks dealt round-robin) gets one contiguous
-// range of items, so neighbouring tets share its L2.
+// Each XCD (blocks dealt round-robin) gets one contiguous range of blocks, so
+// neighbouring tets share its L2.
 __device__ __forceinline__ int xcd_remap(int b, int nb) {
   const int q = nb / 8, rem = nb % 8;
   const int x = b % 8, pos = b / 8;
@@ -853,9 +871,13 @@ hipError_t launch(const morea_problem* p, const float* pts, int pop, float rate,
   const double inv_pop = 1.0 / pop;
   // candidates spread evenly over the blocks of a tet
   const int groups = (pop + kBlockWaves - 1) / kBlockWaves, per = (pop + groups - 1) / groups;
-  const bool staged = p->tet_volume * rate * per * per >= kStageSamples && 2.0 * p->tet_box <= kBoxVoxels;
+  const int turns = (per + 3) / 4 * 4;   // waves that would fill the same turns of four SIMDs
+  const size_t blocks = static_cast<size_t>(P.n_tets) * groups;
+  // spare waves must not take the launch to 2^32 threads
+  const bool staged = per >= kStageWaves && p->tet_volume * rate * per * per / turns >= kStageSamples &&
+                      2.0 * p->tet_box <= kBoxVoxels && blocks * 64 * per <= UINT32_MAX;
   if (staged) {
-    const dim3 grid(static_cast<unsigned>(static_cast<size_t>(P.n_tets) * groups));
+    const dim3 grid(static_cast<unsigned>(blocks));
     hipLaunchKernelGGL((k_eval_sobol<ST, true>), grid, dim3(64 * per), 0, s, P, pts, pop, per, groups, inv_pop,
                        count_scale, seed, p->cells[0], p->cells[1], p->work_records);
   } else {
