@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "morea_internal.h"
+#include "morea_workspace.h"
 
 namespace morea {
 namespace surr {
@@ -1415,8 +1416,9 @@ struct morea_surrogate {
   int2* edge_ends = nullptr;   // [n_edges]
   int* tet_edges = nullptr;    // [n_tets][8] a tet's edges (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), two unused
   float h_scale = 1.f;      // mean of (I_s - I_t)^2 over the grid (1 when 0)
-  void* work = nullptr;     // pre-screen workspace: the parents' point means,
-  size_t work_cap = 0;      // then the partial sums, columns and shared points' values (bytes)
+  // pre-screen: the parents' point means, then the partial sums, columns and
+  // shared points' values
+  morea::Workspace work;
   float* part = nullptr;    // training: the blocks' partial sums
   int steps = 0;
   std::vector<void*> allocs;
@@ -1649,7 +1651,7 @@ void morea_surrogate_destroy(morea_surrogate* s) {
   if (!s) return;
   (void)hipDeviceSynchronize();
   for (void* a : s->allocs) (void)hipFree(a);
-  if (s->work) (void)hipFree(s->work);
+  if (s->work.data) (void)hipFree(s->work.data);
   delete s;
 }
 
@@ -1727,29 +1729,26 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   const size_t col_bytes = 9 * sizeof(float) * static_cast<size_t>(P.n_points);
   const size_t n_shared = static_cast<size_t>(P.n_points) + s->n_edges;
   const size_t cand_bytes = col_bytes + sizeof(float) * n_shared;
-  int slab = static_cast<int>(std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands));
-  size_t most = static_cast<size_t>(std::min(slab, std::max(pop, n_parents)));
-  size_t need = pm_bytes + part_bytes + cand_bytes * most;
-  if (need > s->work_cap) {   // grow the workspace (hipFree waits for the device)
-    if (s->work) (void)hipFree(s->work);
-    s->work = nullptr;
-    s->work_cap = 0;
-    void* d = nullptr;
-    hipError_t e = hipMalloc(&d, need);
-    if (e != hipSuccess && most > kPreCands) {   // the smallest slabs then
-      (void)hipGetLastError();
-      slab = kPreCands;
-      most = kPreCands;
-      need = pm_bytes + part_bytes + cand_bytes * most;
-      e = hipMalloc(&d, need);
-    }
-    if (e != hipSuccess) return sfail(MOREA_ENOMEM, "hipMalloc(%zu): %s", need, hipGetErrorString(e));
-    s->work = d;
-    s->work_cap = need;
-  }
-  float4* pmeans = static_cast<float4*>(s->work);
-  float2* partial = reinterpret_cast<float2*>(static_cast<char*>(s->work) + pm_bytes);
-  float* cols = reinterpret_cast<float*>(static_cast<char*>(s->work) + pm_bytes + part_bytes);
+  const size_t fits = std::max<size_t>(kPreCands, kColBytes / cand_bytes / kPreCands * kPreCands);
+  const size_t all = static_cast<size_t>(std::max(pop, n_parents));
+  hipError_t e = hipSuccess;
+  size_t asked = 0;
+  const size_t most = reserve_slab(
+      s->work, pm_bytes + part_bytes, cand_bytes, kPreCands, std::min(fits, all),
+      [&](size_t bytes) {
+        void* d = nullptr;
+        asked = bytes;
+        e = hipMalloc(&d, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess ? d : nullptr;
+      },
+      [](void* d) { (void)hipFree(d); });   // waits for the device
+  if (most == 0) return sfail(MOREA_ENOMEM, "hipMalloc(%zu): %s", asked, hipGetErrorString(e));
+  const int slab = static_cast<int>(most);
+  char* work = static_cast<char*>(s->work.data);
+  float4* pmeans = reinterpret_cast<float4*>(work);
+  float2* partial = reinterpret_cast<float2*>(work + pm_bytes);
+  float* cols = reinterpret_cast<float*>(work + pm_bytes + part_bytes);
   float* hs = cols + col_bytes / sizeof(float) * most;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   const FeatureInputs F = feature_inputs(s);
