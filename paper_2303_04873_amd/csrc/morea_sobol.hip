@@ -46,6 +46,7 @@
 #include <type_traits>
 
 #include "morea_internal.h"
+#include "morea_sobol_point.h"
 
 namespace morea {
 namespace sobol {
@@ -133,53 +134,6 @@ __device__ __forceinline__ float wave_sum_63(float v) {
 __device__ __forceinline__ double wave_sum_d(double v) {
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
   return v;
-}
-
-// -ln(r) / 2 for r = v 2^-24, v odd and below 2^24: r = m 2^e, m in
-// [sqrt(1/2), sqrt(2)], ln m = 2 atanh(s) with s = (m - 1) / (m + 1) and the
-// series s (1 + s^2/3 + ... + s^10/11); every operation is that of -ln(r)
-// with its result halved, so twice this is -ln(r) to the bit.  The quotient
-// is one correction of n rcp(d): correctly rounded for every v (all 2^23
-// compared with the division).
-__device__ __forceinline__ float half_neg_log(uint32_t v) {
-#pragma clang fp contract(off)
-  const uint32_t u = __float_as_uint(static_cast<float>(v));
-  // -e 2^23: the exponent field of v, one higher from mantissa 0x3504f4
-  // (the first above sqrt(2)), from that of 2^24
-  const uint32_t x = ((152u << 23) - 1u - 0x4afb0cu - u) & 0xff800000u;
-  const float m = __uint_as_float(u + x - (24u << 23));
-  const float n = m - 1.0f, d = m + 1.0f;
-  const float r = __builtin_amdgcn_rcpf(d);
-  const float q = n * r;
-  const float s = __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
-  const float s2 = s * s;
-  float c = __builtin_fmaf(s2, 0x1.745d18p-4f, 0x1.c71c72p-4f);
-  c = __builtin_fmaf(s2, c, 0x1.24924ap-3f);
-  c = __builtin_fmaf(s2, c, 0x1.99999ap-3f);
-  c = __builtin_fmaf(s2, c, 0x1.555556p-2f);
-  c = __builtin_fmaf(s2, c, 1.0f);
-  const float p = s * c;
-  return __builtin_fmaf(static_cast<float>(static_cast<int>(x)), 0x1.62e430p-25f, -p);
-}
-
-// lambda_1..3 of a point from its four words: h_j / (h_0 + h_1 + h_2 + h_3)
-// with h_j = -ln r_j / 2.  The sum lies in [2^-23, 2^6]: its refined
-// reciprocal is the correctly rounded one (all mantissas compared for
-// exponents -26 .. 8), and with it one correction of h r rounds the quotient
-// correctly (Markstein's theorem; 6.4e9 compared with the division).
-__device__ __forceinline__ void lambdas(const uint32_t v[4], float l[3]) {
-#pragma clang fp contract(off)
-  float h[4];
-#pragma unroll
-  for (int j = 0; j < 4; j++) h[j] = half_neg_log(v[j]);
-  const float sum = ((h[0] + h[1]) + h[2]) + h[3];
-  float r = __builtin_amdgcn_rcpf(sum);
-  r = __builtin_fmaf(__builtin_fmaf(-sum, r, 1.0f), r, r);
-#pragma unroll
-  for (int j = 0; j < 3; j++) {
-    const float q = h[j + 1] * r;
-    l[j] = __builtin_fmaf(__builtin_fmaf(-sum, q, h[j + 1]), r, q);
-  }
 }
 
 template <int ST>
@@ -793,7 +747,7 @@ __global__ __launch_bounds__(64 * (kStaged ? kBlockWaves : 4), 6) void k_eval_so
         for (int j = 0; j < 4; j++) xk[j] ^= kSteps.v[c][j];
         if (base + lane >= N) break;
         float l[3], p[3], q[3];
-        lambdas(v, l);
+        lambdas(v, l, [](float x) { return __builtin_amdgcn_rcpf(x); });
 #pragma unroll
         for (int a = 0; a < 3; a++) {
           p[a] = __builtin_fmaf(l[2], eo[2][a], __builtin_fmaf(l[1], eo[1][a], __builtin_fmaf(l[0], eo[0][a], bo[a])));
