@@ -646,6 +646,7 @@ morea_status morea_surrogate_predict_rows(morea_surrogate *s, const float *feats
  * parents as for morea_surrogate_features (features built on the fly: the
  * parents' point means, then the offspring, each from a copy of the
  * coordinates by columns); an offspring without a valid parent scores +inf.
+ * A score has the same bits in a call of any size.
  * The parents' point means (16 bytes per (parent, tet)), partial scores (8
  * per offspring and run of 1 to 8 tets), columns and the values that tets
  * share (36 per offspring and mesh point, 4 per offspring and mesh point or

@@ -699,7 +699,7 @@ typedef const __attribute__((address_space(4))) i8v* TetEdgePtr;
 constexpr int kPreIn = 32;                 // features padded: 23 + three constant 1s + zeros
 constexpr int kPreCands = 64;              // offspring per pre-screen wave: two tiles of the network
 constexpr int kPreWaves = 8;               // per block
-constexpr int kMaxTetRun = 8;              // tets per pre-screen work item
+constexpr int kMaxTetRun = 8;              // tets per pre-screen work item, or 4, 2, 1
 // Work items that fill the card: 512 blocks of 8 waves.  With fewer, runs are
 // shorter (a wave's tets are a serial chain): 4 offspring of 3,402 tets took
 // 128 us in runs of 8 and take 79 in runs of 1; 64 of 384 tets 85 and 55 us.
@@ -707,12 +707,22 @@ constexpr int kPreItems = 4096;
 constexpr int kW1Row = kPreIn + 8;         // LDS row strides padded against bank conflicts
 constexpr int kW2Row = kHid + 8;
 
+// A score's numerator and denominator are added in one order, whatever the
+// length of the runs, so that a score does not depend on the size of the call:
+// a tree over 8 tets at a time (aligned, tets beyond the last adding zero), of
+// which a run of 8, 4, 2 or 1 is a part, then chains over those eights.
+constexpr int kSumLevels = 4;
+static_assert(1 << (kSumLevels - 1) == kMaxTetRun, "a run's tree");
+
+__device__ __forceinline__ float2 add2(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+
 struct alignas(16) PreLds {
   bf16 w1[kHid][kW1Row];   // W1 | b1 (three terms) | 0
   bf16 w2[kHid][kW2Row];   // W2, columns permuted per 16-wide slice
   float b2[kHid];
   float w3[kHid];
   float4 bary[kHalton];
+  float2 sum[kSumLevels][64 * kPreWaves];   // per thread: sums of 1, 2, 4, 8 tets of the run
 };
 
 // Slot of unit u of a 16-wide slice in that order.
@@ -862,7 +872,6 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
     }
     const unsigned col = cand < n ? cand : 0;
     const float4* pmr = pmeans + static_cast<size_t>(ok ? par : 0) * P.n_tets;
-    float acc_s = 0.f, cnt = 0.f;
     const int t_end = min(P.n_tets, (run + 1) * tet_run);
     for (int tet = run * tet_run; tet < t_end; tet++) {
       const i4v tq = tets[tet];
@@ -928,44 +937,65 @@ __global__ __launch_bounds__(64 * kPreWaves, 4) void k_prescreen(ProblemView P, 
       const float y = __uint_as_float(s0) + __uint_as_float(s1) + b3;
       // the parent's exact term plus the predicted change, weighted by the
       // offspring's expected samples of the tet
-      acc_s = fmaf(wt, fmaf(y, F.h_scale, pm.w), acc_s);
-      cnt += wt;
+      const float term = fmaf(y, F.h_scale, pm.w);
+      {
+#pragma clang fp contract(off)
+        float2 x = make_float2(wt * term, wt);
+        int lv = 0;
+        for (int q = tet - run * tet_run; q & 1; q >>= 1) x = add2(N.sum[lv++][threadIdx.x], x);
+        N.sum[lv][threadIdx.x] = x;
+      }
     }
-    if (cand < n) partial[static_cast<size_t>(run) * stride + cand] = make_float2(acc_s, cnt);
+    float2 x = make_float2(0.f, 0.f);
+    for (int lv = 0; lv < kSumLevels; lv++)
+      if (((t_end - run * tet_run) >> lv) & 1) x = add2(N.sum[lv][threadIdx.x], x);
+    if (cand < n) partial[static_cast<size_t>(run) * stride + cand] = x;
   }
 }
 
-// Scores from the per-(run, offspring) partial sums: 16 threads an offspring
-// take a share of the runs each, in order (a single chain of 426 loads took
-// 106 us for 4,096 offspring, bound by their latency), then the shares in
-// order.
+// Scores from the per-(run, offspring) partial sums, kRuns runs to 8 tets: 16
+// threads an offspring take a share of the eights each, in order (a single
+// chain of 426 loads took 106 us for 4,096 offspring, bound by their latency),
+// then the shares in order.
 constexpr int kScoreGroups = 16;
 
+// Sum of the first `have` runs of an eight (the others add zero).
+template <int kRuns>
+__device__ __forceinline__ float2 eight_sum(const float2* at, int stride, int have) {
+  float2 v[kRuns];
+#pragma unroll
+  for (int q = 0; q < kRuns; q++) v[q] = q < have ? at[static_cast<size_t>(q) * stride] : make_float2(0.f, 0.f);
+#pragma unroll
+  for (int d = 1; d < kRuns; d *= 2)
+#pragma unroll
+    for (int q = 0; q < kRuns; q += 2 * d) v[q] = add2(v[q], v[q + d]);
+  return v[0];
+}
+
+template <int kRuns>
 __global__ __launch_bounds__(64 * kScoreGroups) void k_prescreen_reduce(const float2* partial, int n_runs, int pop,
                                                                        Parents Q, float* score) {
   __shared__ float2 s_sum[kScoreGroups][64];
   const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
   const int cand = blockIdx.x * 64 + col;
-  const int per = (n_runs + kScoreGroups - 1) / kScoreGroups, t1 = min(n_runs, (grp + 1) * per);
-  float a = 0.f, c = 0.f;
+  const int n_eights = (n_runs + kRuns - 1) / kRuns;
+  const int per = (n_eights + kScoreGroups - 1) / kScoreGroups, t1 = min(n_eights, (grp + 1) * per);
+  const int whole = min(t1, n_runs / kRuns);
+  float2 a = make_float2(0.f, 0.f);
   if (cand < pop) {
-#pragma unroll 8
-    for (int t = grp * per; t < t1; t++) {
-      const float2 v = partial[static_cast<size_t>(t) * pop + cand];
-      a += v.x;
-      c += v.y;
-    }
+    const float2* at = partial + static_cast<size_t>(grp) * per * kRuns * pop + cand;
+    int t = grp * per;
+#pragma unroll 8 / kRuns + (kRuns > 4)
+    for (; t < whole; t++, at += static_cast<size_t>(kRuns) * pop) a = add2(a, eight_sum<kRuns>(at, pop, kRuns));
+    if (t < t1) a = add2(a, eight_sum<kRuns>(at, pop, n_runs - t * kRuns));
   }
-  s_sum[grp][col] = make_float2(a, c);
+  s_sum[grp][col] = a;
   __syncthreads();
   if (grp != 0 || cand >= pop) return;
-  for (int q = 1; q < kScoreGroups; q++) {
-    a += s_sum[q][col].x;
-    c += s_sum[q][col].y;
-  }
+  for (int q = 1; q < kScoreGroups; q++) a = add2(a, s_sum[q][col]);
   const int par = Q.of[cand];
   // no parent: never preferred
-  score[cand] = par < 0 || par >= Q.n ? INFINITY : (c > 0.f ? a / c : 0.f);
+  score[cand] = par < 0 || par >= Q.n ? INFINITY : (a.y > 0.f ? a.x / a.y : 0.f);
 }
 
 // Predictions for explicit feature rows (one wave per 32 rows).
@@ -1718,9 +1748,10 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
   if (!pts || !score || !parent_of || (n_parents > 0 && (!parent_pts || !parent_cache)))
     return sfail(MOREA_EINVAL, "NULL argument");
   const ProblemView& P = s->p->view;
-  // tets per work item: as many as leave kPreItems items, at most kMaxTetRun
+  // tets per work item: as many as leave kPreItems items, a power of two up to kMaxTetRun
   const long long groups = (static_cast<long long>(pop) + kPreCands - 1) / kPreCands;
-  const int tet_run = static_cast<int>(std::max(1ll, std::min<long long>(kMaxTetRun, P.n_tets * groups / kPreItems)));
+  int tet_run = 1;
+  while (tet_run < kMaxTetRun && 2 * tet_run * kPreItems <= P.n_tets * groups) tet_run *= 2;
   const int n_runs = (P.n_tets + tet_run - 1) / tet_run;
   const size_t rows = static_cast<size_t>(n_parents) * P.n_tets;
   const size_t pm_bytes = (sizeof(float4) * rows + 255) / 256 * 256;
@@ -1792,8 +1823,9 @@ morea_status morea_surrogate_prescreen(morea_surrogate* s, const float* pts, int
                          n_parents, F, pmeans, s->params, s->w1b, s->w2b, n, tet_run, partial + first, pop);
     }
   }
-  hipLaunchKernelGGL(k_prescreen_reduce, dim3((pop + 63) / 64), dim3(64 * kScoreGroups), 0, st, partial, n_runs, pop,
-                     Q, score);
+  const auto reduce = tet_run == 8 ? k_prescreen_reduce<1> : (tet_run == 4 ? k_prescreen_reduce<2> :
+                      (tet_run == 2 ? k_prescreen_reduce<4> : k_prescreen_reduce<8>));
+  hipLaunchKernelGGL(reduce, dim3((pop + 63) / 64), dim3(64 * kScoreGroups), 0, st, partial, n_runs, pop, Q, score);
   return sdev(hipGetLastError(), "prescreen");
 }
 
