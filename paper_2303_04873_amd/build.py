@@ -19,7 +19,8 @@ FLAGS = [
 # Schedule for instruction-level parallelism where long straight-line samples
 # bound the kernel: 128x128x96, 512 candidates 8.39 -> 8.28 ms, 32,768 partial
 # evaluations 33.96 -> 33.14 ms, Sobol points of 128 candidates 2.82 -> 2.74 ms.
-# The training kernel loses by it (35.4 -> 37.1 us), the others do not change.
+# Training loses by it (65,536 rows, calls one by one: 35.4 -> 37.1 us), the
+# others do not change.
 ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 FILE_FLAGS = {"morea_eval.hip": ILP, "morea_sobol.hip": ILP}
 

@@ -698,8 +698,9 @@ __device__ __forceinline__ void flush_deferred(const ProblemView& P, const WaveL
 // arguments (scalar loads) where it is used: its 30 words would otherwise
 // stay live in scalar registers over all the loops, and those that do not fit
 // are spilled into lanes of vector registers, each use a VALU instruction
-// (72 -> 44 spills, 11 -> 4 lane reads in a sample batch; 128x128x96,
-// population 512: 9.19 -> 8.94 ms; 192x192x128 BF16, 256: 15.8 -> 14.1 ms).
+// (72 -> 44 spills in the compiler's default schedule, 51 in the one that is
+// built; 11 -> 4 lane reads in a sample batch; 128x128x96, population 512: 9.19
+// -> 8.94 ms; 192x192x128 BF16, 256: 15.8 -> 14.1 ms).
 typedef const __attribute__((address_space(4))) ProblemView* ViewPtr;
 
 __device__ __forceinline__ ViewPtr view_ptr() {
@@ -1629,7 +1630,7 @@ __global__ __launch_bounds__(1024) void k_prep_groups(PartialItems I, int n_grou
 
 // The four launches as one block, for lists of at most 1,024 evaluations: a
 // launch costs 4.5 us there and its work less (32^3, 16 x 8 groups: 55 us a
-// call with four, XX with one).
+// call with four, 41 with one).
 constexpr int kPrepSmall = 1024;
 
 // Exclusive prefix sums of a pair over the block; totals to every thread.

@@ -29,17 +29,22 @@
 // integer of n = 64 k + lane is the XOR of that of the lane (per lane, once
 // per item) and that of 64 k (wave-uniform, scalar, once per batch).
 //
-// What bounds it: the vector instructions, 200 a point, and where the images
-// are not staged in LDS the gathers, each lane in a cache line of its own (46
-// cycles of a CU for 64).  The instructions were 5,760 a wave (88% of the issue
-// slots, 232 per point to form it and find its cell; now 3,390): the divisions
-// are the correctly rounded ones without scaling for extreme operands, the
-// logarithm is halved (the ratios do not change), which saves its scalings,
-// and tets that stay in the grid's border cells take a path without bounds
-// tests on which one cell serves the images and the distance maps, a row's two
-// corners are one load and values are read only where both points are
-// foreground.  128x128x96, population 128, rate 1: 4.11 -> 2.90, 4.62 -> 3.34,
-// 4.94 -> 3.67 ms (three images); with the images in LDS 2.82, 2.96, 3.12 ms.
+// What bounds it: the vector instructions, 243 lane instructions a point, and
+// where the images are not staged in LDS the gathers, each lane in a cache line
+// of its own (46 cycles of a CU for 64).  The instructions were 5,760 a wave (88%
+// of the issue slots, 232 per point to form it and find its cell; now 3,510, 87%
+// of the slots): the divisions are the correctly rounded ones without scaling
+// for extreme operands, the logarithm is halved (the ratios do not change),
+// which saves its scalings, and tets that stay in the grid's border cells take
+// a path without bounds tests on which one cell serves the images and the
+// distance maps, a row's two corners are one load and values are read only
+// where both points are foreground.  128x128x96, population 128, rate 1: 4.11
+// -> 2.90, 4.62 -> 3.34, 4.94 -> 3.67 ms (three images); with the images in LDS
+// 2.82, 2.96, 3.12 ms.
+// At six waves a SIMD the staged form spills 14 scalar registers into lanes of
+// vector registers and 5 vector registers to scratch (24 bytes a lane, most of
+// the 1.2 GB that a launch of 512 candidates writes, 2% of the copy rate), the
+// other form 1 (none in the compiler's default schedule).
 #include <math.h>
 #include <stdio.h>
 

@@ -800,8 +800,9 @@ __device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {
 // two tiles of the network.
 //
 // What bounds it: the 64 gathers of a tet's 16 interior points in two images
-// (about 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) and
-// the 2,000 vector instructions around them, about 75% of the issue slots.
+// (about 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) of
+// 111 loads, and the 1,770 vector instructions around them, 62% of the issue
+// slots.
 // 128x128x96 (3,402 tets), 4,096 offspring: 3,390 us with coordinates read as
 // stored (a line per lane for each of 36 words), half a tet's points per half
 // wave and 3 waves per SIMD; 1,580 us with coordinates by columns (k_columns,
@@ -1040,9 +1041,10 @@ __global__ __launch_bounds__(256) void k_predict_rows(const float* X, int n, con
 // Bound: 154 KB of LDS (both orders of W2 and the fragments) leave one block
 // on a compute unit, one wave on a SIMD, so it is the chain of a block's
 // steps (152 MFMAs of 32 cycles and as long reading fragments) after loading
-// the weights: 8.3 us per 32,768 rows after 15 us.  65,536 rows: 32 us, then
-// 4.7 us to add the blocks' sums; a batch's loss and gradients went from 723
-// to 38 us (activations through memory, 320 waves for the weight gradients,
+// the weights: 8.3 us per 32,768 rows after 15 us.  65,536 rows: 32 us in a
+// kernel trace, then 4.8 us to add the blocks' sums; a batch's loss and
+// gradients went from 723 to 31 us, 35 in calls that a host issues one by one
+// (activations through memory, 320 waves for the weight gradients,
 // and one thread adding 2,048 partial sums per bias took 175 + 76 + 476 us).
 constexpr int kPartTiles = kGradTiles * 1024;              // entries of dW2 (16 tiles) and dW1 (4)
 constexpr int kPartSums = 3 * kHid + 2;                    // dw3, db2, db1, db3, loss
