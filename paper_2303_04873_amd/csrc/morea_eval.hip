@@ -1317,10 +1317,12 @@ template __global__ void k_eval_full<kF16>(ProblemView, FullItems, Record*, int,
 // latency of its loads and of the tree: 1,024 threads and lane exchanges,
 // where 256 threads and eight rounds through LDS took 5.4 -> 3.9 us (16
 // candidates, 384 tets), 9.2 -> 5.1 (37, 1,680) and 21.3 -> 17.6 us (512,
-// 3,402).  Always the same block, so that a candidate's sums do not depend on
-// the population it is in.
-constexpr int kFinalThreads = 1024;
-static_assert(kFinalThreads / kWave == 16, "one row of lanes adds the waves' sums");
+// 3,402).  Meshes of at most 256 or 64 tets take a block of so many threads,
+// the others would be idle (48 tets, 8,000 candidates: a full evaluation 1,605 ->
+// 1,547 us; 6 tets, 30,000: 36.2 -> 35.9 ms, as with 256 threads for all).  The
+// block depends on the mesh alone, and a thread without a tet adds zeros in the
+// same places of the tree, so that a candidate's sums depend neither on the
+// population it is in nor on the block.
 constexpr int kFinalLaunch = 1 << 21;   // candidates per launch: it holds less than 2^32 threads
 
 struct Sums {
@@ -1342,14 +1344,16 @@ __device__ __forceinline__ void add_lane(Sums& s) {
     s.n[k] += __builtin_amdgcn_update_dpp(0, static_cast<int>(s.n[k]), ctrl, rows, 0xf, false);
 }
 
-__global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const float* pts, const Record* rec,
-                                                            float* obj, uint8_t* flags, float* severity,
-                                                            uint32_t* counts, Totals* totals) {
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void k_finalize(ProblemView P, const float* pts, const Record* rec, float* obj,
+                                                       uint8_t* flags, float* severity, uint32_t* counts,
+                                                       Totals* totals) {
+  static_assert(kThreads / kWave <= 16, "one row of lanes adds the waves' sums");
   const int cand = blockIdx.x;
   const int tid = threadIdx.x;
   Sums S = {};
   const Record* rc = rec + static_cast<size_t>(cand) * P.n_tets * 2;
-  for (int t = tid; t < P.n_tets; t += kFinalThreads) {
+  for (int t = tid; t < P.n_tets; t += kThreads) {
     const Record a = rc[2 * t], b = rc[2 * t + 1];
     df_add(S.v[0], S.v[1], a.h);
     df_add(S.v[0], S.v[1], b.h);
@@ -1364,10 +1368,10 @@ __global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const
     S.n[3] += b.bits & 1u;
   }
   const float* cp = pts + static_cast<size_t>(cand) * 6 * P.n_points;
-  for (int i = tid; i < 6 * P.n_points; i += kFinalThreads) S.n[4] += !(fabsf(cp[i]) < kCoordLimit);
+  for (int i = tid; i < 6 * P.n_points; i += kThreads) S.n[4] += !(fabsf(cp[i]) < kCoordLimit);
 
   // within rows of 16 lanes, across them, then over the waves
-  __shared__ Sums part[kFinalThreads / kWave];
+  __shared__ Sums part[kThreads / kWave];
   add_lane<0x111, 0xf>(S);
   add_lane<0x112, 0xf>(S);
   add_lane<0x114, 0xf>(S);
@@ -1376,13 +1380,13 @@ __global__ __launch_bounds__(kFinalThreads) void k_finalize(ProblemView P, const
   add_lane<0x143, 0xc>(S);
   if ((tid & 63) == 63) part[tid >> 6] = S;
   __syncthreads();
-  if (tid >= kFinalThreads / kWave) return;
+  if (tid >= kThreads / kWave) return;
   S = part[tid];
   add_lane<0x111, 0xf>(S);
   add_lane<0x112, 0xf>(S);
   add_lane<0x114, 0xf>(S);
   add_lane<0x118, 0xf>(S);
-  if (tid == kFinalThreads / kWave - 1) {
+  if (tid == kThreads / kWave - 1) {
     const uint32_t Ns = S.n[0], Nt = S.n[1];
     const bool invalid = S.n[4] != 0;
     const float H = S.v[0] + S.v[1], G = S.v[2] + S.v[3];
@@ -1498,9 +1502,12 @@ hipError_t launch_finalize(const ProblemView& P, const float* pts, int pop, cons
                            float* obj, uint8_t* flags, float* severity, uint32_t* counts,
                            Totals* totals, hipStream_t s) {
   if (pop == 0) return hipSuccess;
+  const auto fits = [&](int threads) { return P.n_tets <= threads && 6LL * P.n_points <= 4 * threads; };
+  const int threads = fits(64) ? 64 : (fits(256) ? 256 : 1024);
+  const auto kernel = threads == 64 ? k_finalize<64> : (threads == 256 ? k_finalize<256> : k_finalize<1024>);
   for (size_t c = 0; c < static_cast<size_t>(pop); c += kFinalLaunch) {
     const unsigned n = static_cast<unsigned>(std::min<size_t>(kFinalLaunch, pop - c));
-    hipLaunchKernelGGL(k_finalize, dim3(n), dim3(kFinalThreads), 0, s, P, pts + c * 6 * P.n_points,
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, s, P, pts + c * 6 * P.n_points,
                        rec + c * P.n_tets * 2, obj + 3 * c, flags + c, severity + c, counts + 2 * c,
                        totals ? totals + c : nullptr);
   }
