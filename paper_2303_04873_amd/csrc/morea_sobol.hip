@@ -32,7 +32,7 @@
 // What bounds it: the vector instructions, 243 lane instructions a point, and
 // where the images are not staged in LDS the gathers, each lane in a cache line
 // of its own (46 cycles of a CU for 64).  The instructions were 5,760 a wave (88%
-// of the issue slots, 232 per point to form it and find its cell; now 3,510, 87%
+// of the issue slots, 232 per point to form it and find its cell; now 3,510, 86%
 // of the slots): the divisions are the correctly rounded ones without scaling
 // for extreme operands, the logarithm is halved (the ratios do not change),
 // which saves its scalings, and tets that stay in the grid's border cells take

@@ -801,7 +801,7 @@ __device__ __forceinline__ void swap_halves(unsigned& a, unsigned& b) {
 //
 // What bounds it: the 64 gathers of a tet's 16 interior points in two images
 // (about 30 cycles of a CU's L1 each, from how far apart 64 offspring lie) of
-// 111 loads, and the 1,770 vector instructions around them, 62% of the issue
+// 111 loads, and the 1,770 vector instructions around them, 61% of the issue
 // slots.
 // 128x128x96 (3,402 tets), 4,096 offspring: 3,390 us with coordinates read as
 // stored (a line per lane for each of 36 words), half a tet's points per half
